@@ -49,7 +49,10 @@ typedef enum {
 
 typedef enum {
   QAX_FP64 = 0,   /* every step in FP64                                        */
-  QAX_MIXED = 1   /* inter-body pair sum in FP32 with compensated accumulation,
+  QAX_MIXED = 1   /* inter-body pair sum in FP32 with compensated accumulation
+                     (several right-hand sides: matrix products of the FP32
+                     factors split in two FP16 parts, FP32 sums of at most 256
+                     sources added up in FP64),
                      self blocks and their inverses applied from FP32 copies,
                      inside FP64 iterative refinement                          */
 } qax_prec;

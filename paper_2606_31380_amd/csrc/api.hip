@@ -229,6 +229,7 @@ static void free_geometry(qax_problem* p, bool keep_plans = false) {
   p->d_ew = nullptr; p->d_ew32 = nullptr;
   dev_release(p, p->d_gemm_tasks);
   p->d_gemm_tasks = nullptr;
+  free_mm_plan(p);
   if (!keep_plans) free_pair_plans(p);
   free_sym_apply(p);
   p->gemm_tasks.clear();
@@ -283,6 +284,7 @@ extern "C" qax_status qax_set_formulation(qax_problem* p, int32_t formulation, d
   QCHECK(hipSetDevice(p->device), "hipSetDevice");
   QCHECK(hipStreamSynchronize(p->stream), "sync");
   lattice_free(p);
+  free_mm_plan(p);
   for (auto& d : p->hbodies) d.eta = p->eta_of(d.k);
   QCHECK(hipMemcpyAsync(p->d_bodies, p->hbodies.data(), sizeof(BodyDev) * p->hbodies.size(),
                         hipMemcpyHostToDevice, p->stream), "copy bodies");
@@ -598,6 +600,7 @@ static qax_status check_vec_call(qax_problem* p, const void* a, const void* b, i
 
 static qax_status pair_sum_into(qax_problem* p, int prec, const double* mu, double* out, int nrhs,
                                 bool accumulate) {
+  QCHECK(ensure_pair_plan(p, prec, nrhs), "pair-sum plan");
   QBUF(partial, double, "pair_partial", pair_work_bytes(p, prec, nrhs));
   QCHECK(launch_pair_sum(p, prec, mu, out, nrhs, partial, accumulate), "pair_sum");
   return QAX_OK;
@@ -939,6 +942,8 @@ static qax_status solve_core(qax_problem* p, qax_prec prec, const double* dirs, 
   // pair-sum workspace sized before any capture (no allocation inside a
   // graph), large enough for the FP64 residual's pair sum too, so that the
   // shared buffer is never reallocated under the captured steps
+  QCHECK(ensure_pair_plan(p, inner_prec, nrhs), "pair-sum plan");
+  QCHECK(ensure_pair_plan(p, QAX_FP64, nrhs), "pair-sum plan");
   QBUF(ppart, double, "pair_partial",
        std::max(pair_work_bytes(p, inner_prec, nrhs), pair_work_bytes(p, QAX_FP64, nrhs)));
   if (p->h_flags_n < m + 1) {
@@ -1275,6 +1280,8 @@ extern "C" qax_status qax_autotune(qax_problem* p, int32_t nrhs_max, const char*
     // kernel off (it serves one right-hand side whenever it applies)
     p->sym.enabled = false;
     auto run = [&](int nrhs) -> hipError_t {
+      const hipError_t pe = ensure_pair_plan(p, prec, nrhs);
+      if (pe != hipSuccess) return pe;
       qax_status s = QAX_OK;
       double* part = (double*)dbuf(p, "pair_partial", pair_work_bytes(p, prec, nrhs), &s);
       if (!part) return hipErrorOutOfMemory;
@@ -1644,6 +1651,8 @@ static qax_status solve_block(qax_problem* p, qax_prec prec, const double* dirs,
   QBUF(cd, double, "bk_c", (size_t)(m + 1) * P * P * 16);
   QBUF(dpart, double, "bk_dots", block_dots_work_bytes(N, m + 1));
   const int inner_prec = prec;
+  QCHECK(ensure_pair_plan(p, inner_prec, P), "pair-sum plan");
+  QCHECK(ensure_pair_plan(p, QAX_FP64, P), "pair-sum plan");
   QBUF(ppart, double, "pair_partial",
        std::max(pair_work_bytes(p, inner_prec, P), pair_work_bytes(p, QAX_FP64, P)));
   double* X = (double*)d_mu_out;

@@ -38,6 +38,22 @@ struct BlockDev {
   int64_t elem_off;   // offset (in complex elements) in the block pools
 };
 
+// Task of the matrix-core pair sums (several right-hand sides): targets
+// [t0, t0 + nt) of one problem against the source chunks [c0, c1) of MM_C
+// nodes each, writing partial slot `slot`; body: the body that holds every
+// target, or -1.
+constexpr int MM_T = 128;
+constexpr int MM_C = 32;
+struct MmTask {
+  int64_t t0;
+  int32_t nt;
+  int32_t c0, c1;
+  int32_t slot;
+  int32_t body;
+  int32_t problem;
+  double k;
+};
+
 // A chunk of pair-sum work: targets [t0, t1) against source bodies
 // [b0, b1) of the same problem, writing partial slot `slot`.
 struct PairTask {
@@ -230,6 +246,16 @@ struct qax_problem {
       int64_t* d_list = nullptr;
     } plan[2];                        // [0] FP64, [1] FP32
   } sym;
+  // matrix-core pair sums (several right-hand sides, k > 0 in every problem):
+  // made on first use after a build, one allocation from d_tasks on
+  struct Mm {
+    qax::MmTask* d_tasks = nullptr;
+    void* d_bodies = nullptr;           // scale and near distance per body
+    void* d_rec = nullptr;              // FP32 source records, 32 bytes per node
+    float* d_ewk = nullptr;
+    int n_tasks = 0;
+    int slots = 1;
+  } mm;
   qax::Tune tune;
 
   // block-Toeplitz apply of the inter-body sum on a regular array of
@@ -319,6 +345,9 @@ hipError_t launch_gemm_tables(hipStream_t s, const GemmTask* tasks, int ntasks,
 hipError_t dev_alloc(qax_problem* p, void** ptr, size_t bytes);
 void dev_release(qax_problem* p, void* ptr);
 void dev_drop_spare(qax_problem* p);
+// Workspace of launch_pair_sum; ensure_pair_plan first (it may allocate, so not
+// inside a stream capture).
+hipError_t ensure_pair_plan(qax_problem* p, int prec, int nrhs);
 size_t pair_work_bytes(const qax_problem* p, int prec, int nrhs);
 hipError_t launch_pair_sum(qax_problem* p, int prec, const double* mu, double* out, int nrhs,
                            double* partial, bool accumulate);
@@ -332,6 +361,12 @@ hipError_t release_sym_plan(qax_problem* p, int pi);
 int sym_default_s(const qax_problem* p, int cu_count);
 // launch choices the kernels support (LDS within 64 KB)
 bool pair_config_ok(int prec, int tpb, int nrc);
+// pairmm.hip
+hipError_t ensure_mm_plan(qax_problem* p, int cu_count);
+void free_mm_plan(qax_problem* p);
+size_t mm_work_bytes(const qax_problem* p, int prec, int nrhs);
+hipError_t launch_pair_mmf(qax_problem* p, const double* mu, int nrhs, double* work);
+
 int nearfield_slots(int64_t M, int cu_count);
 hipError_t launch_nearfield(qax_problem* p, const double* mu, int nrhs, const double* pts, int64_t M,
                             int problem, int slots, double* partial, double* u);

@@ -1,0 +1,782 @@
+// Inter-body pair sum with several right-hand sides on the matrix cores: the
+// kernel matrix K_ij of a tile of targets and a chunk of sources is evaluated
+// in registers (the per-pair arithmetic of pairsum.hip) and multiplied with
+// the densities at once,
+//   w_i[r] = sum_j K_ij mu_j[r],  K_ij = (1/4 pi)(ik r - 1) e^{ikr} / r^3
+//                                        (aw_j . (y_j - x_i))   (double layer),
+// so each pair's distance and phase serve every right-hand side and the
+// complex products run on MFMA.  Needs k > 0 in every problem.
+//
+// Chunks of MM_C = 32 consecutive sources and tiles of 16 consecutive targets
+// never straddle bodies or problems (a body has 16 n_panels n_theta nodes and
+// n_theta is even), so the exclusion of pairs on one body is uniform over a
+// wavefront and a chunk.
+#include <algorithm>
+#include <vector>
+
+#include "fastmath.h"
+#include "internal.h"
+
+namespace qax {
+
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// ---------------------------------------------------------------- FP32 path
+// Every FP32 factor x enters the FP16 matrix products as h + l, h = x rounded
+// to FP16 and l = x - h rounded to FP16 (22 to 23 significant bits while x is
+// above 2^-3 in size), and x y = h h' + h l' + l h' in FP32 (the dropped l l'
+// is below 2^-22 of the product, of random sign).  Powers of two keep the
+// factors in range: K is scaled per source body by S_b so that the largest
+// entry that a target at least rho_b = R_b / 2 off the body's bounding ball
+// (radius R_b) can have is below 2^14, mu by 1 / S_b and, per problem and
+// right-hand side, by sigma so that its largest entry is below 2^15.
+__device__ __forceinline__ void split2(float x0, float x1, uint32_t& h, uint32_t& l) {
+  f32x2 r = {x0, x1};
+  h = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, f16x2));
+  // x - h from the packed halves, one mixed-precision fma each
+  asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r[0]) : "v"(h), "v"(x0));
+  asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r[1]) : "v"(h), "v"(x1));
+  l = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, f16x2));
+}
+
+// Scale S_b of a body and the distance from its centre below which a target
+// is near: |K| k^3 / 4 pi <= |aw| / (k^2 r) (sqrt(1 + 1 / (k r)^2) + eta / k) / (4 pi / k^3)
+// (single layer: |aw| / (k^3 r)).
+struct MmBody {
+  float S, near2;   // near: |D|^2 below this
+};
+
+__global__ __launch_bounds__(256) void mm_body_kernel(const BodyDev* __restrict__ bodies,
+                                                      const float4* __restrict__ loc32,
+                                                      const float4* __restrict__ aw32, int form,
+                                                      MmBody* __restrict__ mb) {
+  const BodyDev& B = bodies[blockIdx.x];
+  float r2 = 0.0f, w2 = 0.0f;
+  for (int i = threadIdx.x; i < B.n; i += 256) {
+    const float4 a = aw32[B.off + i];
+    r2 = fmaxf(r2, loc32[B.off + i].w);
+    w2 = fmaxf(w2, a.x * a.x + a.y * a.y + a.z * a.z);
+  }
+  __shared__ float s0[256], s1[256];
+  s0[threadIdx.x] = r2;
+  s1[threadIdx.x] = w2;
+  __syncthreads();
+  for (int h = 128; h > 0; h >>= 1) {
+    if (threadIdx.x < h) {
+      s0[threadIdx.x] = fmaxf(s0[threadIdx.x], s0[threadIdx.x + h]);
+      s1[threadIdx.x] = fmaxf(s1[threadIdx.x], s1[threadIdx.x + h]);
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    const double R = 1.0001 * sqrt((double)s0[0]), W = 1.0001 * sqrt((double)s1[0]), k = B.k;
+    const double rho = 0.5 * R, q = 1.0 / (k * rho);
+    const double lim = W / (k * k * rho) *
+                       (form == 2 ? B.eta / k : sqrt(1.0 + q * q) + (form == 1 ? B.eta / k : 0.0));
+    int e = 0;
+    (void)frexp(lim, &e);
+    mb[blockIdx.x].S = (float)ldexp(1.0, max(-120, min(120, 14 - e)));
+    mb[blockIdx.x].near2 = (float)(1.0001 * (R + rho) * (R + rho));
+  }
+}
+
+// Source records: float4 pairs (y', c |y'|^2), S (aw / 2 c, aw . y') with y'
+// the offset from the body centre and c = k^2 / 2 pi (as the reciprocal FP32
+// kernel stages them), and S eta |aw| / k^2.
+__global__ void mm_records_kernel(const BodyDev* __restrict__ bodies, const int32_t* __restrict__ node_body,
+                                  const float4* __restrict__ loc32, const float4* __restrict__ aw32,
+                                  const float* __restrict__ ew32, const MmBody* __restrict__ mb, int64_t N,
+                                  float4* __restrict__ rec, float* __restrict__ ewk) {
+  const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (n >= N) return;
+  const int b = node_body[n];
+  const double k = bodies[b].k;
+  const double c = k * k / TWO_PI;
+  const float4 y = loc32[n], a = aw32[n];
+  const float S = mb[b].S;
+  const float hw = (float)(0.5 / c) * S;
+  rec[2 * n] = make_float4(y.x, y.y, y.z, (float)c * y.w);
+  rec[2 * n + 1] = make_float4(a.x * hw, a.y * hw, a.z * hw, a.w * S);
+  ewk[n] = ew32[n] * (float)(1.0 / (k * k)) * S;
+}
+
+__global__ void mm_zero_kernel(uint64_t* __restrict__ p, int n) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) p[i] = 0;
+}
+
+// Largest |Re|, |Im| of mu / S_b per problem and right-hand side, as the bits
+// of a non-negative double (which order like the values; NaN above infinity).
+// Workgroup: 256 consecutive nodes (of any problems) x 8 right-hand sides.
+__global__ __launch_bounds__(256) void mm_colmax_kernel(const double2* __restrict__ mu, int64_t N, int nrhs,
+                                                        const BodyDev* __restrict__ bodies,
+                                                        const int32_t* __restrict__ node_body,
+                                                        const MmBody* __restrict__ mb,
+                                                        unsigned long long* __restrict__ colmax) {
+  const int r = blockIdx.y * 8 + (threadIdx.x & 7);
+  const int64_t n0 = (int64_t)blockIdx.x * 256 + (threadIdx.x >> 3) * 8;
+  if (r >= nrhs || n0 >= N) return;
+  // eight consecutive nodes of one body (node counts are multiples of 32)
+  const int b = node_body[n0];
+  unsigned long long m = 0;
+  for (int s = 0; s < 8; ++s) {
+    const double2 v = mu[(n0 + s) * nrhs + r];
+    const unsigned long long x = __double_as_longlong(fabs(v.x)), y = __double_as_longlong(fabs(v.y));
+    m = max(m, max(x, y));
+  }
+  const double is = 1.0 / (double)mb[b].S;
+  m = __double_as_longlong(fabs(__longlong_as_double(m)) * is);
+  unsigned long long* dst = colmax + (int64_t)bodies[b].problem * nrhs + r;
+  if (m > *(volatile unsigned long long*)dst) atomicMax(dst, m);
+}
+
+// sigma of a column from its largest value (1 when that is zero or not finite)
+__device__ __forceinline__ double mm_sigma(unsigned long long bits) {
+  const double m = __longlong_as_double(bits);
+  if (!(m > 0.0) || !(m < 1.0e300)) return 1.0;
+  int e = 0;
+  (void)frexp(m, &e);
+  return ldexp(1.0, min(15 - e, 1000));
+}
+
+// Densities scaled, split and laid out as the B operands of the 32x32x16
+// products, a group of right-hand sides r0 ... at a time: per half chunk of 16
+// sources four fragments of 64 16-byte values, h, l of B1 and of B2.  A tile of 32
+// right-hand sides (wide): B1 = Re mu, B2 = Im mu, one column each; a tile of
+// 16: B1 = [Re mu | Im mu], B2 = [-Im mu | Re mu], 16 columns each.  Lane l of
+// a fragment holds column l % 32 and the sources 8 (l / 32) ... + 7.
+__global__ __launch_bounds__(256) void mm_pack_kernel(const double2* __restrict__ mu, int64_t halves, int nrhs,
+                                                      int r0, int wide, int tiles,
+                                                      const BodyDev* __restrict__ bodies,
+                                                      const int32_t* __restrict__ node_body,
+                                                      const MmBody* __restrict__ mb,
+                                                      const unsigned long long* __restrict__ colmax,
+                                                      u32x4* __restrict__ out) {
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int lane = (int)(t & 63);
+  const int64_t hc = t >> 6;
+  if (hc >= halves) return;
+  const int col = lane & 31;
+  const int tile = blockIdx.y;
+  const bool second = !wide && col >= 16;
+  const int r = r0 + tile * 32 + (wide ? col : (col & 15));
+  const double2* v = mu + (hc * 16 + (lane >> 5) * 8) * nrhs + r;
+  const int body = node_body[hc * 16];
+  const double sc = r < nrhs ? mm_sigma(colmax[(int64_t)bodies[body].problem * nrhs + r]) / (double)mb[body].S : 0.0;
+  float a[8], b[8];
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    const double2 m = r < nrhs ? v[(int64_t)s * nrhs] : make_double2(0.0, 0.0);
+    const float re = (float)(m.x * sc), im = (float)(m.y * sc);
+    a[s] = second ? im : re;
+    b[s] = wide ? im : (second ? re : -im);
+  }
+  u32x4 fa[2], fb[2];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    uint32_t x, y;
+    split2(a[2 * s], a[2 * s + 1], x, y);
+    fa[0][s] = x; fa[1][s] = y;
+    split2(b[2 * s], b[2 * s + 1], x, y);
+    fb[0][s] = x; fb[1][s] = y;
+  }
+  u32x4* o = out + (tiles == 2 ? (hc >> 1) * 4 + tile * 2 + (hc & 1) : hc) * 4 * 64 + lane;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    o[q * 64] = fa[q];
+    o[(2 + q) * 64] = fb[q];
+  }
+}
+
+struct MmTarget {   // per target and source body (see the reciprocal FP32 kernel)
+  float mx, my, mz, d2s, dns, ph0;
+};
+
+// The target at (x, y, z) against body B; returns whether it is near.
+__device__ __forceinline__ bool mm_target(const BodyDev& B, const MmBody& M, double x, double y, double z, double k,
+                                          MmTarget& G) {
+  const double c2 = 2.0 * k * k / TWO_PI;
+  const double Dx = B.cen[0] - x, Dy = B.cen[1] - y, Dz = B.cen[2] - z;
+  const double D2 = fma(Dx, Dx, fma(Dy, Dy, Dz * Dz));
+  const double Dn = sqrt(D2);
+  double ph = k * Dn / TWO_PI;
+  ph -= floor(ph);
+  G.mx = (float)(c2 * Dx);
+  G.my = (float)(c2 * Dy);
+  G.mz = (float)(c2 * Dz);
+  G.d2s = (float)(k * k * D2);
+  G.dns = (float)(k * Dn);
+  G.ph0 = (float)ph;
+  return !(D2 >= (double)M.near2);
+}
+
+// K (in units of k^3 / 4 pi, scaled by the records' S) of a target and the
+// source with records Y, W, E.
+template <int FORM>
+__device__ __forceinline__ void mm_eval(const float4 Y, const float4 W, float E, const MmTarget& T, float& kr,
+                                        float& ki) {
+  const float num = fmaf(Y.x, T.mx, fmaf(Y.y, T.my, fmaf(Y.z, T.mz, Y.w)));
+  const float r2s = fmaf((float)TWO_PI, num, T.d2s);
+  const float irs = __builtin_amdgcn_rsqf(r2s);
+  const float ph = fmaf(num, __builtin_amdgcn_rcpf(fmaf(r2s, irs, T.dns)), T.ph0);
+  const float sn = __builtin_amdgcn_sinf(ph);
+  const float cs = __builtin_amdgcn_cosf(ph);
+  if constexpr (FORM == 2) {
+    const float g = E * irs;
+    kr = cs * g;
+    ki = sn * g;
+  } else {
+    const float d = fmaf(W.x, T.mx, fmaf(W.y, T.my, fmaf(W.z, T.mz, W.w)));
+    const float di = d * (irs * irs);
+    kr = -(fmaf(cs, irs, sn) * di);
+    ki = fmaf(-sn, irs, cs) * di;
+    if constexpr (FORM == 1) {
+      const float g = E * irs;
+      kr = fmaf(g, sn, kr);
+      ki = fmaf(-g, cs, ki);
+    }
+  }
+}
+
+// The A operands (h, l of Re K, h, l of Im K) of the lane's target and eight
+// sources with records at R and E.  With `near` set, entries beyond the bound
+// of S_b scale the whole half chunk down; returns the power of two that undoes
+// that (1 otherwise; entries that are not finite stay so).
+template <int FORM>
+__device__ __forceinline__ float mm_operands(const float4* R, const float* E, const MmTarget& G, bool near,
+                                             u32x4* f) {
+  float kr[8], ki[8], undo = 1.0f;
+#pragma unroll
+  for (int s = 0; s < 8; ++s) mm_eval<FORM>(R[2 * s], R[2 * s + 1], E[FORM ? s : 0], G, kr[s], ki[s]);
+  if (near) {
+    float m = 0.0f;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) m = fmaxf(m, fmaxf(fabsf(kr[s]), fabsf(ki[s])));
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    if (m >= 32768.0f && m < 3.0e38f) {
+      int e = 0;
+      (void)frexpf(m, &e);
+      undo = ldexpf(1.0f, e - 14);
+      const float g = ldexpf(1.0f, 14 - e);
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        kr[s] *= g;
+        ki[s] *= g;
+      }
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    uint32_t x, y;
+    split2(kr[2 * s], kr[2 * s + 1], x, y);
+    f[0][s] = x; f[1][s] = y;
+    split2(ki[2 * s], ki[2 * s + 1], x, y);
+    f[2][s] = x; f[3][s] = y;
+  }
+  return undo;
+}
+
+__device__ __forceinline__ f32x16 mm_mma(u32x4 a, u32x4 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0,
+                                                0, 0);
+}
+
+// c += (a0 + a1)(b0 + b1) without a1 b1
+__device__ __forceinline__ f32x16 mm_mma3(const u32x4* a, const u32x4* b, f32x16 c) {
+  c = mm_mma(a[1], b[0], c);
+  c = mm_mma(a[0], b[1], c);
+  return mm_mma(a[0], b[0], c);
+}
+
+// The products of one half chunk (f: A operands, B operands at fb): a tile of
+// 32 right-hand sides accumulates Re and Im apart, one of 16 [Re | Im].
+template <int WIDE>
+__device__ __forceinline__ void mm_products(u32x4* f, const u32x4* fb, f32x16* acc) {
+  u32x4 b[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) b[q] = fb[q * 64];
+  acc[0] = mm_mma3(f, b, acc[0]);
+  if constexpr (WIDE) {
+    acc[1] = mm_mma3(f, b + 2, acc[1]);
+    acc[1] = mm_mma3(f + 2, b, acc[1]);
+    f[2] ^= 0x80008000u;
+    f[3] ^= 0x80008000u;
+  }
+  acc[0] = mm_mma3(f + 2, b + 2, acc[0]);
+}
+
+// FP32 sums of at most eight chunks (256 sources), added up in FP64
+template <int NA>
+struct MmSums {
+  f32x16 acc[NA];
+  double sum[NA][16];
+  int n;
+  __device__ __forceinline__ void clear() {
+    n = 0;
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        acc[a][e] = 0.0f;
+        sum[a][e] = 0.0;
+      }
+  }
+  __device__ __forceinline__ void flush(double f) {
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        sum[a][e] = fma((double)acc[a][e], f, sum[a][e]);
+        acc[a][e] = 0.0f;
+      }
+  }
+  __device__ __forceinline__ void end_chunk() {
+    if (++n == 8) {
+      n = 0;
+      flush(1.0);
+    }
+  }
+};
+
+// No right-hand side of [r0, r1) is active in a lockstep solve: zeros for the
+// nt targets from t0 on.
+__device__ __forceinline__ bool mm_inactive(const int32_t* __restrict__ seg_active, int problem, int nrhs, int r0,
+                                            int r1, int64_t t0, int nt, double2* __restrict__ dst) {
+  if (!seg_active) return false;
+  bool any = false;
+  for (int r = r0; r < r1; ++r) any = any || seg_active[problem * nrhs + r] != 0;
+  if (any) return false;
+  const int nr = r1 - r0;
+  for (int e = threadIdx.x; e < nt * nr; e += 256) dst[(t0 + e / nr) * nrhs + r0 + e % nr] = make_double2(0.0, 0.0);
+  return true;
+}
+
+// The source chunks of a task: the body that holds every target is passed
+// over; body and the end of its chunks follow the chunk number.
+struct MmWalk {
+  int own0 = 0, own1 = 0;   // chunks passed over
+  int body = -1, end = 0;
+  __device__ __forceinline__ MmWalk(const MmTask& T, const BodyDev* __restrict__ bodies) {
+    if (T.body >= 0) {
+      own0 = (int)(bodies[T.body].off / MM_C);
+      own1 = own0 + bodies[T.body].n / MM_C;
+    }
+  }
+  __device__ __forceinline__ int next(int c) const { return c >= own0 && c < own1 ? own1 : c; }
+  __device__ __forceinline__ void start(int c, const BodyDev* __restrict__ bodies,
+                                        const int32_t* __restrict__ node_body) {
+    body = node_body[(int64_t)c * MM_C];
+    end = (int)((bodies[body].off + bodies[body].n) / MM_C);
+  }
+  __device__ __forceinline__ void to(int c, const BodyDev* __restrict__ bodies) {
+    while (c >= end) end += bodies[++body].n / MM_C;
+  }
+};
+
+// Up to 32 (WIDE) or 16 right-hand sides from r0 on.  A workgroup takes 128
+// targets, 32 per wavefront; the chunk's records and packed densities pass
+// through LDS (double-buffered, the next chunk loaded meanwhile); lane l
+// evaluates K for target l % 32 and the sources 8 (l / 32) ... + 7 of each
+// half chunk, which is the A operand's layout, so K never leaves registers.
+// Bound by vector issue (per pair 4 transcendentals at 8.3 cycles, 15 FP32 and
+// 4 conversion instructions at 2.5 to 4.4, about 92 cycles per 64 pairs; 6 or
+// 12 matrix instructions of 32 cycles per 512 pairs, which overlap little).
+// 100 bodies of 2048 nodes (4.2e10 pairs): 16 right-hand sides 114.6 -> 36.4 ms,
+// 32 202.6 -> 46.4 ms against the per-target kernel; register caps of 4 and 3
+// wavefronts per SIMD are 4 % faster than 3 and 2.  Bfloat16 in three parts (six
+// products, nine vector instructions more per pair) took 51 and 73 ms; moving
+// the products of one half chunk between the evaluations of the next gave nothing.
+template <int WIDE, int FORM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ? 3 : 4))) void pair_mmf_kernel(
+    const MmTask* __restrict__ tasks, const BodyDev* __restrict__ bodies, const int32_t* __restrict__ node_body,
+    const double* __restrict__ pos, int64_t N, const MmBody* __restrict__ mb, const u32x4* __restrict__ rec,
+    const float* __restrict__ ewk, const u32x4* __restrict__ pack,
+    const unsigned long long* __restrict__ colmax, int nrhs, int r0, const int32_t* __restrict__ seg_active,
+    double2* __restrict__ partial) {
+  constexpr int NV = 8 * 64;                     // packed 16-byte values per chunk
+  constexpr int NA = 1 + WIDE;
+  const MmTask T = tasks[blockIdx.x];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int col = lane & 31, half = lane >> 5;
+  double2* dst = partial + (int64_t)T.slot * N * nrhs;
+  if (mm_inactive(seg_active, T.problem, nrhs, r0, min(nrhs, r0 + 16 * NA), T.t0, T.nt, dst)) return;
+  const int64_t tile0 = T.t0 + wave * 32;
+  const bool live = wave * 32 < T.nt;
+  __shared__ u32x4 sB[2][NV];
+  __shared__ u32x4 sR[2][64];
+  __shared__ float sE[2][FORM ? 32 : 1];
+  const double k = T.k;
+  const int mybody = live ? node_body[tile0] : -1;
+  const int64_t ti = live ? tile0 + col : T.t0;
+  const double xi = pos[ti], yi = pos[N + ti], zi = pos[2 * N + ti];
+
+  MmSums<NA> S;
+  S.clear();
+  MmTarget G;
+  bool near = false;
+  int cur = -1, buf = 0;
+  MmWalk W(T, bodies);
+  u32x4 pre[2], prec;
+  float pew = 0.0f;
+  auto fetch = [&](int c) {
+    const u32x4* p = pack + (int64_t)c * NV + tid;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) pre[q] = p[q * 256];
+    if (wave == 0) {
+      prec = rec[(int64_t)c * 64 + lane];
+      if (FORM) pew = ewk[(int64_t)c * MM_C + col];
+    }
+  };
+  int c = W.next(T.c0);
+  if (c < T.c1) {
+    fetch(c);
+    W.start(c, bodies, node_body);
+  }
+  while (c < T.c1) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) sB[buf][tid + q * 256] = pre[q];
+    if (wave == 0) {
+      sR[buf][lane] = prec;
+      if (FORM) sE[buf][col] = pew;
+    }
+    __syncthreads();
+    const int cn = W.next(c + 1);
+    if (cn < T.c1) fetch(cn);
+    W.to(c, bodies);
+    if (live && W.body != mybody) {
+      if (W.body != cur) {
+        cur = W.body;
+        near = __any(mm_target(bodies[cur], mb[cur], xi, yi, zi, k, G));
+      }
+#pragma unroll
+      for (int hc = 0; hc < 2; ++hc) {
+        u32x4 f[4];
+        const float undo = mm_operands<FORM>((const float4*)&sR[buf][(hc * 16 + half * 8) * 2],
+                                             &sE[buf][FORM ? hc * 16 + half * 8 : 0], G, near, f);
+        if (undo != 1.0f) S.flush(1.0);
+        mm_products<WIDE>(f, &sB[buf][hc * 4 * 64 + lane], S.acc);
+        if (undo != 1.0f) S.flush((double)undo);
+      }
+      S.end_chunk();
+    }
+    buf ^= 1;
+    c = cn;
+  }
+  S.flush(1.0);
+  if (!live) return;
+  // element e of the lane: column l % 32, row 8 (e / 4) + 4 (l / 32) + e % 4
+  const int r = r0 + (WIDE ? col : (col & 15));
+  const double sc = r < nrhs ? k * k * k / FOUR_PI / mm_sigma(colmax[(int64_t)T.problem * nrhs + r]) : 0.0;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int64_t i = tile0 + 8 * (e >> 2) + 4 * half + (e & 3);
+    const double im = WIDE ? S.sum[NA - 1][e] : __shfl_down(S.sum[0][e], 16);
+    if ((WIDE || col < 16) && r < nrhs) dst[i * nrhs + r] = make_double2(S.sum[0][e] * sc, im * sc);
+  }
+}
+
+// 33 to 64 right-hand sides from r0 on: two wavefronts share a tile of 32
+// targets, each with 32 right-hand sides.  Each evaluates one half chunk of K
+// for both (the operands pass through LDS) and multiplies the previous chunk,
+// so every entry of K is evaluated once for all 64: 82 ms on the 100 bodies
+// above, against 95 ms for two passes of the kernel above and 394 ms for the
+// per-target kernel.
+template <int FORM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void pair_mmf64_kernel(
+    const MmTask* __restrict__ tasks, const BodyDev* __restrict__ bodies, const int32_t* __restrict__ node_body,
+    const double* __restrict__ pos, int64_t N, const MmBody* __restrict__ mb, const u32x4* __restrict__ rec,
+    const float* __restrict__ ewk, const u32x4* __restrict__ pack,
+    const unsigned long long* __restrict__ colmax, int nrhs, int r0, const int32_t* __restrict__ seg_active,
+    double2* __restrict__ partial) {
+  constexpr int NV = 16 * 64;                    // packed 16-byte values per chunk
+  const MmTask T = tasks[blockIdx.x >> 1];
+  const int sub = (blockIdx.x & 1) * 64;         // this workgroup's half of the task's targets
+  const int nt = min(64, T.nt - sub);
+  if (nt <= 0) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tile = wave >> 1, hw = wave & 1;     // the wavefront's tile; its half chunk and right-hand sides
+  const int col = lane & 31, half = lane >> 5;
+  double2* dst = partial + (int64_t)T.slot * N * nrhs;
+  if (mm_inactive(seg_active, T.problem, nrhs, r0, min(nrhs, r0 + 64), T.t0 + sub, nt, dst)) return;
+  const int64_t tile0 = T.t0 + sub + tile * 32;
+  const bool live = tile * 32 < nt;
+  __shared__ u32x4 sB[2][NV];
+  __shared__ u32x4 sA[2][2][2][4 * 64];          // buffer, tile, half chunk
+  __shared__ u32x4 sR[2][64];
+  __shared__ float sE[2][FORM ? 32 : 1];
+  __shared__ float sU[2][2][2];                  // what undoes the half chunk's scaling
+  const double k = T.k;
+  const int mybody = live ? node_body[tile0] : -1;
+  const int64_t ti = live ? tile0 + col : T.t0;
+  const double xi = pos[ti], yi = pos[N + ti], zi = pos[2 * N + ti];
+
+  MmSums<2> S;
+  S.clear();
+  MmTarget G;
+  bool near = false;
+  int cur = -1;
+  MmWalk W(T, bodies);
+  u32x4 preB[4], preR;
+  float preE = 0.0f;
+  auto fetch_b = [&](int c) {
+    if (c >= T.c1) return;
+    const u32x4* p = pack + (int64_t)c * NV + tid;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) preB[q] = p[q * 256];
+  };
+  auto fetch_r = [&](int c) {
+    if (c >= T.c1 || wave != 0) return;
+    preR = rec[(int64_t)c * 64 + lane];
+    if (FORM) preE = ewk[(int64_t)c * MM_C + col];
+  };
+  auto store_b = [&](int buf) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sB[buf][tid + q * 256] = preB[q];
+  };
+  auto store_r = [&](int buf) {
+    if (wave != 0) return;
+    sR[buf][lane] = preR;
+    if (FORM) sE[buf][col] = preE;
+  };
+  // whether the tile meets the chunk W is at (G and near set for it)
+  auto meets = [&]() {
+    if (!live || W.body == mybody) return false;
+    if (W.body != cur) {
+      cur = W.body;
+      near = __any(mm_target(bodies[cur], mb[cur], xi, yi, zi, k, G));
+    }
+    return true;
+  };
+  // K of the wavefront's half chunk, from record buffer rb to operand buffer ab
+  auto evaluate = [&](int rb, int ab, bool scaled) {
+    u32x4 f[4];
+    const float undo = mm_operands<FORM>((const float4*)&sR[rb][(hw * 16 + half * 8) * 2],
+                                         &sE[rb][FORM ? hw * 16 + half * 8 : 0], G, scaled, f);
+    if (scaled && lane == 0) sU[ab][tile][hw] = undo;
+    u32x4* o = &sA[ab][tile][hw][lane];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) o[q * 64] = f[q];
+  };
+  auto multiply = [&](int ab, int hc) {
+    u32x4 f[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) f[q] = sA[ab][tile][hc][q * 64 + lane];
+    mm_products<1>(f, &sB[ab][(hw * 2 + hc) * 4 * 64 + lane], S.acc);
+  };
+
+  // in step i, after its barrier: chunk i is multiplied, chunk i + 1 evaluated,
+  // and the densities of i + 1 and the records of i + 2 stored into the buffers
+  // that step i - 1 was the last to read
+  int c0 = W.next(T.c0), c1 = W.next(c0 + 1), c2 = W.next(c1 + 1);
+  bool use = false, scaled = false;   // of chunk i
+  if (c0 < T.c1) {
+    fetch_b(c0);
+    fetch_r(c0);
+    store_b(0);
+    store_r(0);
+    fetch_r(c1);
+    if (c1 < T.c1) store_r(1);
+    fetch_b(c1);
+    fetch_r(c2);
+    __syncthreads();
+    W.start(c0, bodies, node_body);
+    use = meets();
+    scaled = near;
+    if (use) evaluate(0, 0, scaled);
+  }
+  for (int i = 0; c0 < T.c1; ++i) {
+    __syncthreads();
+    const int p0 = i & 1, p1 = p0 ^ 1;
+    if (c1 < T.c1) store_b(p1);
+    if (c2 < T.c1) store_r(p0);
+    const int c3 = W.next(c2 + 1);
+    fetch_b(c2);
+    fetch_r(c3);
+    bool use1 = false;
+    if (c1 < T.c1) {
+      W.to(c1, bodies);
+      use1 = meets();
+    }
+    if (use && use1 && !scaled && !near) {
+      // no branch between the two products and the evaluation: 5 % faster
+      multiply(p0, 0);
+      evaluate(p1, p1, false);
+      multiply(p0, 1);
+    } else {
+      if (use1) evaluate(p1, p1, near);
+      if (use) {
+#pragma unroll 1
+        for (int hc = 0; hc < 2; ++hc) {
+          const float undo = scaled ? sU[p0][tile][hc] : 1.0f;
+          if (undo != 1.0f) S.flush(1.0);
+          multiply(p0, hc);
+          if (undo != 1.0f) S.flush((double)undo);
+        }
+      }
+    }
+    S.end_chunk();
+    use = use1;
+    scaled = near;
+    c0 = c1;
+    c1 = c2;
+    c2 = c3;
+  }
+  S.flush(1.0);
+  const int r = r0 + hw * 32 + col;
+  if (!live || r >= nrhs) return;
+  const double sc = k * k * k / FOUR_PI / mm_sigma(colmax[(int64_t)T.problem * nrhs + r]);
+  // element e of the lane: column l % 32, row 8 (e / 4) + 4 (l / 32) + e % 4
+#pragma unroll
+  for (int e = 0; e < 16; ++e)
+    dst[(tile0 + 8 * (e >> 2) + 4 * half + (e & 3)) * nrhs + r] =
+        make_double2(S.sum[0][e] * sc, S.sum[1][e] * sc);
+}
+
+// ---------------------------------------------------------------- plan and launch
+static size_t align256(size_t b) { return (b + 255) / 256 * 256; }
+
+// Target blocks of MM_T nodes of one problem, each against `slots` ranges of
+// the problem's source chunks, sorted by decreasing cost: at least 24
+// workgroups per compute unit (about eight rounds of those the chip holds; with
+// four rounds the last one cost 6 % on the 100 bodies above, with more nothing
+// was gained), at least eight chunks each (the sums' FP64 step).
+static void plan_mm(qax_problem* p, int cu_count, std::vector<MmTask>& tasks) {
+  auto& M = p->mm;
+  int64_t tblocks = 0, cmax = 0;
+  for (int pr = 0; pr < p->n_problems; ++pr) {
+    const int64_t n = p->off[p->prob_body0[pr + 1]] - p->off[p->prob_body0[pr]];
+    tblocks += (n + MM_T - 1) / MM_T;
+    cmax = std::max(cmax, n / MM_C);
+  }
+  int64_t slots = (24LL * cu_count + tblocks - 1) / std::max<int64_t>(tblocks, 1);
+  slots = std::max<int64_t>(1, std::min<int64_t>({slots, 32, cmax / 8}));
+  M.slots = (int)slots;
+  tasks.clear();
+  for (int pr = 0; pr < p->n_problems; ++pr) {
+    const int b0 = (int)p->prob_body0[pr], b1 = (int)p->prob_body0[pr + 1];
+    const int64_t n0 = p->off[b0], n1 = p->off[b1];
+    const int64_t c0 = n0 / MM_C, nc = (n1 - n0) / MM_C;
+    int lo = b0;
+    for (int64_t t0 = n0; t0 < n1; t0 += MM_T) {
+      const int nt = (int)std::min<int64_t>(MM_T, n1 - t0);
+      while (lo + 1 < b1 && p->off[lo + 1] <= t0) ++lo;
+      const bool one = p->off[lo + 1] >= t0 + nt;
+      for (int s = 0; s < slots; ++s) {
+        MmTask T;
+        T.t0 = t0;
+        T.nt = nt;
+        T.c0 = (int32_t)(c0 + nc * s / slots);
+        T.c1 = (int32_t)(c0 + nc * (s + 1) / slots);
+        T.slot = s;
+        T.body = one ? lo : -1;
+        T.problem = pr;
+        T.k = p->k[pr];
+        tasks.push_back(T);
+      }
+    }
+  }
+  std::stable_sort(tasks.begin(), tasks.end(), [](const MmTask& a, const MmTask& b) {
+    return (int64_t)a.nt * (a.c1 - a.c0) > (int64_t)b.nt * (b.c1 - b.c0);
+  });
+}
+
+// The task table, and the bodies' scales and source records of the FP32 path
+// (functions of the geometry and the formulation), made on first use after a
+// build (not inside a capture).
+hipError_t ensure_mm_plan(qax_problem* p, int cu_count) {
+  auto& M = p->mm;
+  if (M.d_tasks) return hipSuccess;
+  std::vector<MmTask> tasks;
+  plan_mm(p, cu_count, tasks);
+  const size_t bt = align256(sizeof(MmTask) * tasks.size()), bb = align256(sizeof(MmBody) * p->n_bodies),
+               br = align256((size_t)p->N * 32);
+  char* m = nullptr;
+  hipError_t e = dev_alloc(p, (void**)&m, bt + bb + br + (size_t)p->N * 4);
+  if (e != hipSuccess) return e;
+  MmBody* mb = (MmBody*)(m + bt);
+  float4* rec = (float4*)(m + bt + bb);
+  float* ewk = (float*)(m + bt + bb + br);
+  e = hipMemcpyAsync(m, tasks.data(), sizeof(MmTask) * tasks.size(), hipMemcpyHostToDevice, p->stream);
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(mm_body_kernel, dim3((unsigned)p->n_bodies), dim3(256), 0, p->stream, p->d_bodies,
+                       (const float4*)p->d_loc32, (const float4*)p->d_aw32, p->form(), mb);
+    hipLaunchKernelGGL(mm_records_kernel, dim3((unsigned)((p->N + 255) / 256)), dim3(256), 0, p->stream, p->d_bodies,
+                       p->d_node_body, (const float4*)p->d_loc32, (const float4*)p->d_aw32, p->d_ew32, mb, p->N, rec,
+                       ewk);
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
+  if (e != hipSuccess) {
+    dev_release(p, m);
+    return e;
+  }
+  M.d_tasks = (MmTask*)m;
+  M.d_bodies = mb;
+  M.d_rec = rec;
+  M.d_ewk = ewk;
+  M.n_tasks = (int)tasks.size();
+  ++p->generation;
+  return hipSuccess;
+}
+
+void free_mm_plan(qax_problem* p) {
+  dev_release(p, p->mm.d_tasks);
+  p->mm.d_tasks = nullptr;
+  p->mm.n_tasks = 0;
+}
+
+static size_t mm_pack_values(const qax_problem* p, int nrhs) {
+  return (size_t)(p->N / MM_C) * (nrhs > 32 ? 16 : 8) * 64;
+}
+
+size_t mm_work_bytes(const qax_problem* p, int prec, int nrhs) {
+  size_t b = align256((size_t)p->mm.slots * p->N * nrhs * 16);
+  if (prec != QAX_FP64)
+    b += align256((size_t)p->n_problems * nrhs * 8) + mm_pack_values(p, nrhs) * sizeof(u32x4);
+  return b;
+}
+
+// Partial sums of the FP32 pair sum (slots x N x nrhs at `work`).
+hipError_t launch_pair_mmf(qax_problem* p, const double* mu, int nrhs, double* work) {
+  char* m = (char*)work;
+  auto take = [&](size_t bytes) {
+    char* q = m;
+    m += align256(bytes);
+    return q;
+  };
+  double2* partial = (double2*)take((size_t)p->mm.slots * p->N * nrhs * 16);
+  const MmBody* mb = (const MmBody*)p->mm.d_bodies;
+  unsigned long long* colmax = (unsigned long long*)take((size_t)p->n_problems * nrhs * 8);
+  u32x4* pack = (u32x4*)m;
+  const int form = p->form();
+  const hipStream_t s = p->stream;
+  const int ncol = p->n_problems * nrhs;
+  const int64_t halves = p->N / 16;
+  hipLaunchKernelGGL(mm_zero_kernel, dim3((unsigned)((ncol + 255) / 256)), dim3(256), 0, s, (uint64_t*)colmax, ncol);
+  hipLaunchKernelGGL(mm_colmax_kernel, dim3((unsigned)((p->N + 255) / 256), (unsigned)((nrhs + 7) / 8)), dim3(256), 0,
+                     s, (const double2*)mu, p->N, nrhs, p->d_bodies, p->d_node_body, mb, colmax);
+  for (int r0 = 0; r0 < nrhs; r0 += 64) {
+    const int left = nrhs - r0, wide = left > 16, tiles = left > 32 ? 2 : 1;
+    hipLaunchKernelGGL(mm_pack_kernel, dim3((unsigned)((halves * 64 + 255) / 256), (unsigned)tiles), dim3(256), 0, s,
+                       (const double2*)mu, halves, nrhs, r0, wide, tiles, p->d_bodies, p->d_node_body, mb, colmax,
+                       pack);
+    auto go = [&](auto kern) {
+      hipLaunchKernelGGL(kern, dim3((unsigned)(p->mm.n_tasks * tiles)), dim3(256), 0, s, p->mm.d_tasks, p->d_bodies,
+                         p->d_node_body, p->d_pos, p->N, mb, (const u32x4*)p->mm.d_rec, p->mm.d_ewk, pack, colmax, nrhs, r0,
+                         p->seg_active, partial);
+    };
+    if (tiles == 2) go(form == 1 ? pair_mmf64_kernel<1> : form == 2 ? pair_mmf64_kernel<2> : pair_mmf64_kernel<0>);
+    else if (wide) go(form == 1 ? pair_mmf_kernel<1, 1> : form == 2 ? pair_mmf_kernel<1, 2> : pair_mmf_kernel<1, 0>);
+    else go(form == 1 ? pair_mmf_kernel<0, 1> : form == 2 ? pair_mmf_kernel<0, 2> : pair_mmf_kernel<0, 0>);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+}  // namespace qax

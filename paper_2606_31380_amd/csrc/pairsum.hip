@@ -6,6 +6,9 @@
 //                                          (aw_j . (y_j - x_i)) mu_j,
 //   r = |y_j - x_i|,  aw_j = n_j |J_j| (pi/N) omega_j.
 //
+// Several right-hand sides go through the matrix cores (pairmm.hip) where the
+// wavenumbers allow it; the kernels here take the rest.
+//
 // A tiled N-body kernel on the vector ALUs: source tiles are staged in LDS,
 // every thread owns one target.  Work is cut into tasks (target block x range
 // of source bodies) listed in a table sorted by cost, so that uneven bodies and
@@ -1470,11 +1473,31 @@ static void launch_any(qax_problem* p, bool f64, int tpb, int nrc, const double*
   }
 }
 
+// The matrix-core kernels (pairmm.hip) take every pair sum with several
+// right-hand sides whose wavenumbers allow their scaling by k (k in
+// [1e-6, 1e6]; FP32 powers of k r overflow beyond): two right-hand sides take
+// 33 ms against the per-target kernel's 42 ms on 100 bodies of 2048 nodes in
+// FP32, and the ratio grows with their number.
+static bool use_mm(const qax_problem* p, int prec, int nrhs) {
+  if (prec == QAX_FP64 || nrhs < 2) return false;
+  for (double k : p->k)
+    if (!(k >= 1e-6 && k <= 1e6)) return false;
+  return true;
+}
+
+hipError_t ensure_pair_plan(qax_problem* p, int prec, int nrhs) {
+  if (!use_mm(p, prec, nrhs) || p->mm.d_tasks) return hipSuccess;
+  int cus = 0;
+  hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device);
+  return e == hipSuccess ? ensure_mm_plan(p, std::max(cus, 1)) : e;
+}
+
 // partial: slots x N x nrhs complex128 workspace; out = pair sum, or
 // out += pair sum when accumulate is set.  The workgroup size is the one the
 // task table was planned with; right-hand sides per pass from the tuning
 // (clamped to a supported configuration).
 size_t pair_work_bytes(const qax_problem* p, int prec, int nrhs) {
+  if (use_mm(p, prec, nrhs)) return std::max(mm_work_bytes(p, prec, nrhs), lattice_work_bytes(p, nrhs));
   const int slots = prec == QAX_FP64 ? p->slots64 : p->slots32;
   size_t b = std::max((size_t)slots * p->N * nrhs * 16, lattice_work_bytes(p, nrhs));
   if (nrhs == 1 && p->sym.ok)
@@ -1551,6 +1574,17 @@ hipError_t launch_pair_sum(qax_problem* p, int prec, const double* mu, double* o
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
+  }
+  if (use_mm(p, prec, nrhs)) {
+    if (!p->mm.d_tasks) return hipErrorInvalidConfiguration;
+    timing_begin(p, kind);
+    hipError_t e = launch_pair_mmf(p, mu, nrhs, partial);
+    timing_end(p, kind);
+    if (e != hipSuccess) return e;
+    const int64_t count = p->N * nrhs;
+    hipLaunchKernelGGL(reduce_slots_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, p->stream,
+                       (const double2*)partial, p->mm.slots, count, (double2*)out, accumulate ? 1 : 0);
+    return hipGetLastError();
   }
   const int tpb = p->tune.pair_tpb[pi];
   int nrc = nrhs == 1 ? 1 : p->tune.pair_nrc[pi][nrhs_class(nrhs)];
