@@ -245,9 +245,9 @@ qax_status qax_solve_dense(qax_problem* p, const double* dirs, int32_t nrhs, voi
  * far-field pattern, in its double-layer form):
  * u_inf_p(xhat) = (1/4 pi) sum_{j in p} (-i k_p xhat.n_j) e^{-i k_p xhat.y_j}
  * mu_j |J_j| w_j (combined field: plus -i eta |J_j| w_j e^{...}; single layer:
- * |J_j| w_j e^{...} mu_j alone).  xhat: host, n_dirs x 3 (finite; a direction
- * whose exact negation is also listed shares its phase evaluation, with the
- * same results).  d_mu: N x nrhs; d_u_inf: n_problems x n_dirs x nrhs
+ * |J_j| w_j e^{...} mu_j alone).  xhat: host, n_dirs x 3 (finite; where an
+ * eighth of the directions or more are pairs of a direction and its exact
+ * negation, those share one phase evaluation, with the same results).  d_mu: N x nrhs; d_u_inf: n_problems x n_dirs x nrhs
  * complex128 (problem, then direction, then right-hand side). */
 qax_status qax_farfield(qax_problem* p, const void* d_mu, int32_t nrhs,
                         const double* xhat, int32_t n_dirs, void* d_u_inf);
@@ -376,9 +376,10 @@ qax_status qax_timing(const qax_problem* p, int32_t kernel, int64_t* launches, d
  *    side of the square of block pairs one workgroup evaluates (1, 2, 4, 8),
  *    which sets the launch's workgroup count and the size of its partial
  *    sums (about 2 N (N / 256) / s complex values, cut into launches of at
- *    most 960 MB each).  With one right-hand side and the reciprocal kernel
- *    serving every such pair sum, the per-target kernel's choices above are
- *    not timed.
+ *    most 960 MB each).  Where the reciprocal kernel serves every pair sum
+ *    with one right-hand side and the matrix-core sums (wavenumbers in
+ *    [1e-6, 1e6]) those with several, the per-target kernel's choices above
+ *    are not timed.
  * Every candidate is timed on this problem's own data (HIP events, the
  * fastest of a few launches after a warm-up) and the fastest is kept for the
  * handle until the next qax_autotune.  Results do not depend on the choices

@@ -680,10 +680,11 @@ extern "C" qax_status qax_farfield(qax_problem* p, const void* d_mu, int32_t nrh
   for (int i = 0; i < 3 * n_dirs; ++i)
     if (!is_finite(xhat[i])) return fail(p, QAX_ERR_ARG, "qax_farfield: non-finite direction");
   QCHECK(hipSetDevice(p->device), "hipSetDevice");
-  // items: each direction, paired with a later one that is its exact
-  // negation (bitwise, open-addressing table over the 24-byte keys)
+  // items: pairs of a direction and its exact negation (bitwise; each
+  // direction looks for an unpaired earlier one in an open-addressing table over the
+  // 24-byte keys), then the directions left over
   std::vector<int2> items;
-  items.reserve(n_dirs);
+  int n_pairs = 0;
   {
     const uint64_t* bits = (const uint64_t*)xhat;
     auto hash = [&](uint64_t a, uint64_t b, uint64_t c) {
@@ -694,32 +695,42 @@ extern "C" qax_status qax_farfield(qax_problem* p, const void* d_mu, int32_t nrh
     };
     size_t cap = 1;
     while (cap < 2 * (size_t)n_dirs) cap <<= 1;
-    std::vector<int32_t> table(cap, -1);
+    std::vector<int32_t> table(cap, -1), partner(n_dirs, -1);
+    const uint64_t sg = 0x8000000000000000ULL;
     for (int i = 0; i < n_dirs; ++i) {
+      const uint64_t a = bits[3 * i] ^ sg, b = bits[3 * i + 1] ^ sg, c = bits[3 * i + 2] ^ sg;
+      int found = -1;
+      for (size_t h = hash(a, b, c) & (cap - 1); table[h] >= 0; h = (h + 1) & (cap - 1)) {
+        const int q = table[h];
+        if (partner[q] < 0 && bits[3 * q] == a && bits[3 * q + 1] == b && bits[3 * q + 2] == c) {
+          found = q;
+          break;
+        }
+      }
+      if (found >= 0) {
+        partner[found] = i;
+        partner[i] = found;
+        ++n_pairs;
+        continue;
+      }
       size_t h = hash(bits[3 * i], bits[3 * i + 1], bits[3 * i + 2]) & (cap - 1);
       while (table[h] >= 0) h = (h + 1) & (cap - 1);
       table[h] = i;
     }
-    const uint64_t sg = 0x8000000000000000ULL;
-    std::vector<char> used(n_dirs, 0);
-    for (int i = 0; i < n_dirs; ++i) {
-      if (used[i]) continue;
-      used[i] = 1;
-      const uint64_t a = bits[3 * i] ^ sg, b = bits[3 * i + 1] ^ sg, c = bits[3 * i + 2] ^ sg;
-      int partner = -1;
-      for (size_t h = hash(a, b, c) & (cap - 1); table[h] >= 0; h = (h + 1) & (cap - 1)) {
-        const int q = table[h];
-        if (!used[q] && bits[3 * q] == a && bits[3 * q + 1] == b && bits[3 * q + 2] == c) {
-          partner = q;
-          break;
-        }
-      }
-      if (partner >= 0) used[partner] = 1;
-      items.push_back(make_int2(i, partner));
+    // a few pairs are not worth a launch of their own (50 of them among 40,000
+    // directions took 108 us for their share of 6 us)
+    if (n_pairs < n_dirs / 8) {
+      n_pairs = 0;
+      std::fill(partner.begin(), partner.end(), -1);
     }
+    items.resize((size_t)n_dirs - n_pairs);
+    size_t q = 0, r = n_pairs;
+    for (int i = 0; i < n_dirs; ++i)
+      if (partner[i] > i) items[q++] = make_int2(i, partner[i]);
+      else if (partner[i] < 0) items[r++] = make_int2(i, -1);
   }
   const int nitems = (int)items.size();
-  const int slots = farfield_slots((int64_t)nitems * p->n_problems, cu_count(p->device));
+  const int slots = mm_slots(p, nitems, 0, p->n_problems, cu_count(p->device));
   const int np = p->n_problems;
   const size_t up = (size_t)n_dirs * 24 + (size_t)nitems * sizeof(int2);
   QBUF(dx, double, "xhat", up);
@@ -736,7 +747,7 @@ extern "C" qax_status qax_farfield(qax_problem* p, const void* d_mu, int32_t nrh
   std::memcpy(p->h_stage, xhat, (size_t)n_dirs * 24);
   std::memcpy((char*)p->h_stage + (size_t)n_dirs * 24, items.data(), (size_t)nitems * sizeof(int2));
   QCHECK(hipMemcpyAsync(dx, p->h_stage, up, hipMemcpyHostToDevice, p->stream), "copy directions");
-  QCHECK(launch_farfield(p, (const double*)d_mu, nrhs, dx, n_dirs, ditems, nitems, p->d_pinfo, slots, part,
+  QCHECK(launch_farfield(p, (const double*)d_mu, nrhs, dx, n_dirs, ditems, n_pairs, nitems - n_pairs, slots, part,
                          (double*)d_u_inf),
          "farfield");
   return sync(p, "qax_farfield");
@@ -757,7 +768,7 @@ extern "C" qax_status qax_nearfield(qax_problem* p, const void* d_mu, int32_t nr
       soa[(size_t)c * n_pts + i] = v;
     }
   QCHECK(hipSetDevice(p->device), "hipSetDevice");
-  const int slots = nearfield_slots(n_pts, cu_count(p->device));
+  const int slots = nearfield_slots(p, n_pts, problem, cu_count(p->device));
   QBUF(dp, double, "nf_points", soa.size() * 8);
   QBUF(part, double, "nf_partial", (size_t)slots * n_pts * nrhs * 16);
   QCHECK(hipMemcpyAsync(dp, soa.data(), soa.size() * 8, hipMemcpyHostToDevice, p->stream), "copy points");
@@ -1293,13 +1304,15 @@ extern "C" qax_status qax_autotune(qax_problem* p, int32_t nrhs_max, const char*
     };
     double best = 1e300;
     int btpb = t.pair_tpb[pi], bmult = t.pair_mult[pi];
-    // one right-hand side with the reciprocal kernel serving every such pair
-    // sum: the per-target kernel's choices are never used, nothing to time
-    const bool recip_only = nrhs_max == 1 && p->sym.ok && p->form() != 2;
+    // several right-hand sides go to the matrix-core sums, one to the
+    // reciprocal kernel, where these serve the problem: the per-target
+    // kernel's choices are then never used, nothing to time
+    const bool several = nrhs_max > 1 && !pair_uses_mm(p, nrhs_max);
+    const bool recip_only = !several && p->sym.ok && p->form() != 2;
     if (recip_only) {
       btpb = defaults.pair_tpb[pi];
       bmult = defaults.pair_mult[pi];
-    } else if (nrhs_max == 1) {
+    } else if (!several) {
       // workgroup size and source-chunk schedule for one right-hand side
       for (int tpb : {128, 256, 512}) {
         for (int mult : {4, 8, 16}) {
@@ -1394,7 +1407,7 @@ extern "C" qax_status qax_autotune(qax_problem* p, int32_t nrhs_max, const char*
     }
     // right-hand sides per pass for the other classes that nrhs_max reaches
     for (int c = 0; c < 4; ++c) {
-      if (nrhs_max < lo[c] || (nrhs_max > 1 && c == qax::nrhs_class(nrhs_max))) continue;
+      if (!several || nrhs_max < lo[c] || c == qax::nrhs_class(nrhs_max)) continue;
       const int nrhs = std::min(nrhs_max, rep[c]);
       double bc = 1e300;
       int bn = t.pair_nrc[pi][c];

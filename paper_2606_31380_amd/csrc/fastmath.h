@@ -106,6 +106,25 @@ __device__ __forceinline__ void sincos_tab512(double u, const double2* tab, doub
   *cp = fma(T.y, Cm1, fma(-T.x, S, T.y));
 }
 
+// 512 / 2 pi and what its double leaves of it
+constexpr double U512 = 512.0 / 6.283185307179586476925;
+constexpr double U512_LOW = -5.037741228846716e-15;
+
+// sin and cos of 2 pi (x (u + ul)) / 512 from the same table, x u not rounded:
+// the remainder against its nearest integer is one fma, the part ul (far below
+// u) another.
+__device__ __forceinline__ void sincos_tab512_scaled(double x, double u, double ul, const double2* tab, double* sp,
+                                                     double* cp) {
+  const double m = rint(x * u);
+  const double g = fma(x, ul, fma(x, u, -m));
+  const double2 T = tab[(int)m & 511];
+  const double g2 = g * g;
+  const double S = g * fma(fma(g2, 2.3193606829202922e-12, -3.080196845561248e-07), g2, 0.01227184630308513);
+  const double Cm1 = g2 * fma(g2, 9.44992556799382e-10, -7.529910584327208e-05);
+  *sp = fma(T.x, Cm1, fma(T.y, S, T.x));
+  *cp = fma(T.y, Cm1, fma(-T.x, S, T.y));
+}
+
 // The table for sincos_tab512: (sin, cos)(2 pi i / 512) in tab[i], filled by
 // the `nthreads` threads of a workgroup (a barrier must follow before use).
 __device__ __forceinline__ void fill_tab512(double2* tab, int tid, int nthreads) {

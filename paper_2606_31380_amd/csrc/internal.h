@@ -347,6 +347,7 @@ void dev_release(qax_problem* p, void* ptr);
 void dev_drop_spare(qax_problem* p);
 // Workspace of launch_pair_sum; ensure_pair_plan first (it may allocate, so not
 // inside a stream capture).
+bool pair_uses_mm(const qax_problem* p, int nrhs);   // several right-hand sides on the matrix cores
 hipError_t ensure_pair_plan(qax_problem* p, int prec, int nrhs);
 size_t pair_work_bytes(const qax_problem* p, int prec, int nrhs);
 hipError_t launch_pair_sum(qax_problem* p, int prec, const double* mu, double* out, int nrhs,
@@ -365,9 +366,17 @@ bool pair_config_ok(int prec, int tpb, int nrc);
 hipError_t ensure_mm_plan(qax_problem* p, int cu_count);
 void free_mm_plan(qax_problem* p);
 size_t mm_work_bytes(const qax_problem* p, int prec, int nrhs);
+int mm_slots(const qax_problem* p, int64_t count, int prob0, int nprob, int cu_count);
+hipError_t launch_mm_near(qax_problem* p, const double* mu, int nrhs, const double* pts, int64_t M, int problem,
+                          int slots, double* partial);
+hipError_t launch_mm_far(qax_problem* p, const double* mu, int nrhs, const double* xhat, int64_t M, const int2* items,
+                         int64_t n_pairs, int64_t n_single, int slots, double* partial);
+// k in the range of the kernels that scale positions by it
+inline bool mm_k_ok(double k) { return k >= 1e-6 && k <= 1e6; }
+hipError_t launch_pair_mmd(qax_problem* p, const double* mu, int nrhs, double* work);
 hipError_t launch_pair_mmf(qax_problem* p, const double* mu, int nrhs, double* work);
 
-int nearfield_slots(int64_t M, int cu_count);
+int nearfield_slots(const qax_problem* p, int64_t M, int problem, int cu_count);
 hipError_t launch_nearfield(qax_problem* p, const double* mu, int nrhs, const double* pts, int64_t M,
                             int problem, int slots, double* partial, double* u);
 hipError_t ensure_gemm_tasks(qax_problem* p);
@@ -393,7 +402,6 @@ hipError_t launch_modal_modes(hipStream_t s, int n, const double* r, const doubl
 
 // krylov.hip
 hipError_t launch_rhs(qax_problem* p, const double* dirs_dev, int nrhs, double* out);
-int farfield_slots(int64_t M, int cu_count);
 // block GMRES products over N x p blocks (p <= 64, node-major, columns
 // fastest; vstride: doubles between consecutive blocks):
 // out[i][b][a] = sum_n conj(V_i[n][b]) W[n][a] for i < nb (partial:
@@ -409,7 +417,7 @@ hipError_t launch_block_update(hipStream_t s, const double* V, int64_t vstride, 
 // (current), taken once per device
 hipError_t noalloc_init(int device);
 hipError_t launch_farfield(qax_problem* p, const double* mu, int nrhs, const double* xhat_dev,
-                           int ndir, const int2* items_dev, int nitems, const int64_t* pinfo_dev,
-                           int slots, double* partial, double* out);
+                           int ndir, const int2* items_dev, int n_pairs, int n_single, int slots,
+                           double* partial, double* out);
 
 }  // namespace qax

@@ -49,119 +49,14 @@ __global__ void reduce_slots_kernel(const double2* __restrict__ partial, int slo
 
 // u_inf[p][dir][r] = (1/4pi) sum_{n in problem p} (-i k_p xhat.aw_n)
 // e^{-i k_p xhat.y_n} mu[n][r] (combined field: plus -i eta |aw_n| e^{...};
-// single layer: |aw_n| e^{...} alone).  One item per thread: a direction, or a
-// direction and its exact negation (the phase negated: one sin/cos for
-// both); node tiles staged in LDS and read by broadcast, the problem's node
-// range cut into `slots` chunks (blockIdx.y) whose partial sums are added in a
-// fixed order afterwards; blockIdx.z = problem * nrhs + right-hand side.
-// pinfo: the problems' first nodes (n_problems + 1 int64) then their k.
-// The phase is taken in 512ths of a revolution for sincos_tab512 (table in
-// LDS per workgroup); PAIRS: the list holds negated pairs (else the second
-// direction's sums are not formed).
-template <int TPB, bool PAIRS>
-__global__ __launch_bounds__(TPB) void farfield_kernel(
-    const double* __restrict__ xhat, const int2* __restrict__ items, int64_t M, int64_t Mi,
-    const double* __restrict__ pos, const double* __restrict__ aw, const double* __restrict__ ew,
-    int form, int64_t N, const int64_t* __restrict__ pinfo, int nprob, int slots,
-    const double2* __restrict__ mu, int nrhs, double2* __restrict__ partial) {
-  const int tid = threadIdx.x;
-  const int64_t t = (int64_t)blockIdx.x * TPB + tid;
-  const bool active = t < Mi;
-  // direction i and, when the list holds its exact negation, that one (i2):
-  // its phase is the negated phase, so sin flips sign and cos is unchanged
-  // items == nullptr: one item per direction, no pairs
-  const int2 it = active ? (items ? items[t] : make_int2((int)t, -1)) : make_int2(0, -1);
-  const int64_t i = it.x, i2 = it.y;
-  const double pair = i2 >= 0 ? 1.0 : 0.0;
-  const int r = blockIdx.z % nrhs, pr = blockIdx.z / nrhs;
-  const int64_t pn0 = pinfo[pr], pn = pinfo[pr + 1] - pn0;
-  const double k = __longlong_as_double(pinfo[nprob + 1 + pr]);
-  const double hx = active ? xhat[3 * i] : 0.0, hy = active ? xhat[3 * i + 1] : 0.0,
-               hz = active ? xhat[3 * i + 2] : 0.0;
-  // phase -k x.y / 2 pi in 512ths of a revolution and k x, per direction
-  const double kr = -k * (512.0 / TWO_PI);
-  const double px = kr * hx, py = kr * hy, pz = kr * hz;
-  const double qx = k * hx, qy = k * hy, qz = k * hz;
-  const int64_t c0 = pn0 + pn * blockIdx.y / slots, c1 = pn0 + pn * (blockIdx.y + 1) / slots;
-  __shared__ double sx[TPB], sy[TPB], sz[TPB], sax[TPB], say[TPB], saz[TPB], sew[TPB];
-  __shared__ double2 smu[TPB];
-  __shared__ double2 sTab[512];
-  fill_tab512(sTab, tid, TPB);   // ordered by the first tile's barrier
-  double ar = 0.0, ai = 0.0, br = 0.0, bi = 0.0;
-  for (int64_t base = c0; base < c1; base += TPB) {
-    const int cnt = (int)min((int64_t)TPB, c1 - base);
-    __syncthreads();
-    if (tid < cnt) {
-      const int64_t j = base + tid;
-      sx[tid] = pos[j]; sy[tid] = pos[N + j]; sz[tid] = pos[2 * N + j];
-      sax[tid] = aw[j]; say[tid] = aw[N + j]; saz[tid] = aw[2 * N + j];
-      sew[tid] = form ? ew[j] : 0.0;
-      smu[tid] = mu[j * nrhs + r];
-    }
-    __syncthreads();
-    if (form == 2) {
-      for (int jj = 0; jj < cnt; ++jj) {
-        double s, c;
-        sincos_tab512(fma(px, sx[jj], fma(py, sy[jj], pz * sz[jj])), sTab, &s, &c);
-        const double fr = sew[jj] * c, fi = sew[jj] * s;
-        const double2 m = smu[jj];
-        ar = fma(fr, m.x, fma(-fi, m.y, ar));
-        ai = fma(fr, m.y, fma(fi, m.x, ai));
-        if constexpr (PAIRS) {
-          // -x: fr, -fi
-          br = fma(fr, m.x, fma(fi, m.y, br));
-          bi = fma(fr, m.y, fma(-fi, m.x, bi));
-        }
-      }
-    } else {
-      for (int jj = 0; jj < cnt; ++jj) {
-        double s, c;
-        sincos_tab512(fma(px, sx[jj], fma(py, sy[jj], pz * sz[jj])), sTab, &s, &c);
-        // (-i k nd)(c + i s) = k nd s - i k nd c; combined field adds
-        // (-i eta |aw|)(c + i s) = eta |aw| s - i eta |aw| c (ew = 0 otherwise)
-        const double d = fma(qx, sax[jj], fma(qy, say[jj], qz * saz[jj]));
-        const double a = d + sew[jj];
-        const double fr = a * s, fi = -a * c;
-        const double2 m = smu[jj];
-        ar = fma(fr, m.x, fma(-fi, m.y, ar));
-        ai = fma(fr, m.y, fma(fi, m.x, ai));
-        if constexpr (PAIRS) {
-          // -x: k nd -> -k nd, s -> -s: (eta |aw| - d)(-s) - i (eta |aw| - d) c
-          const double a2 = sew[jj] - d;
-          const double gr = -a2 * s, gi = -a2 * c;
-          br = fma(gr, m.x, fma(-gi, m.y, br));
-          bi = fma(gr, m.y, fma(gi, m.x, bi));
-        }
-      }
-    }
-  }
-  if (active) {
-    const int64_t base = ((int64_t)blockIdx.y * nprob + pr) * M;
-    partial[(base + i) * nrhs + r] = make_double2(ar * INV_FOUR_PI_K, ai * INV_FOUR_PI_K);
-    if (pair > 0.0)
-      partial[(base + i2) * nrhs + r] = make_double2(br * INV_FOUR_PI_K, bi * INV_FOUR_PI_K);
-  }
-}
-
-int farfield_slots(int64_t M, int cu_count) {
-  const int64_t blocks = (M + 255) / 256;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(64, (8LL * cu_count + blocks - 1) / blocks));
-}
-
-// out[problem][dir][r] (directions xhat_dev, 3 doubles each; pinfo_dev as
-// the kernel's pinfo; items_dev may be null: no pairs); partial:
-// farfield_slots x n_problems x ndir x nrhs complex128.
+// single layer: |aw_n| e^{...} alone): the direction sums of pairmm.hip, then
+// their slots added in a fixed order.  out[problem][dir][r] (directions
+// xhat_dev, 3 doubles each; items as launch_mm_far's); partial: slots x
+// n_problems x ndir x nrhs complex128.
 hipError_t launch_farfield(qax_problem* p, const double* mu, int nrhs, const double* xhat_dev,
-                           int ndir, const int2* items_dev, int nitems, const int64_t* pinfo_dev,
-                           int slots, double* partial, double* out) {
-  dim3 grid((unsigned)((nitems + 255) / 256), (unsigned)slots, (unsigned)(nrhs * p->n_problems));
-  // items pair a direction with its negation only when there are fewer
-  // items than directions
-  auto kern = nitems < ndir ? farfield_kernel<256, true> : farfield_kernel<256, false>;
-  hipLaunchKernelGGL(kern, grid, dim3(256), 0, p->stream, xhat_dev, items_dev,
-                     (int64_t)ndir, (int64_t)nitems, p->d_pos, p->d_aw, p->d_ew, p->form(), p->N,
-                     pinfo_dev, p->n_problems, slots, (const double2*)mu, nrhs, (double2*)partial);
-  hipError_t e = hipGetLastError();
+                           int ndir, const int2* items_dev, int n_pairs, int n_single, int slots,
+                           double* partial, double* out) {
+  hipError_t e = launch_mm_far(p, mu, nrhs, xhat_dev, ndir, items_dev, n_pairs, n_single, slots, partial);
   if (e != hipSuccess) return e;
   const int64_t count = (int64_t)p->n_problems * ndir * nrhs;
   hipLaunchKernelGGL(reduce_slots_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0,
@@ -659,9 +554,9 @@ extern "C" qax_status qax_farfield_noalloc(qax_problem* p, const void* d_mu, int
                 "(at most 4194304 complex values)");
   hipError_t e = hipSetDevice(p->device);
   if (e != hipSuccess) return hip_check(p, e, "hipSetDevice");
-  int slots = farfield_slots((int64_t)n_dirs * p->n_problems, g_noalloc_cus[p->device]);
+  int slots = mm_slots(p, n_dirs, 0, p->n_problems, g_noalloc_cus[p->device]);
   slots = (int)std::min<size_t>((size_t)slots, FF_NOALLOC_BYTES / per_slot);
-  e = launch_farfield(p, (const double*)d_mu, nrhs, d_xhat, n_dirs, nullptr, n_dirs, p->d_pinfo, slots,
+  e = launch_farfield(p, (const double*)d_mu, nrhs, d_xhat, n_dirs, nullptr, 0, n_dirs, slots,
                       (double*)g_noalloc_ptr[p->device], (double*)d_u_inf);
   return e == hipSuccess ? QAX_OK : hip_check(p, e, "qax_farfield_noalloc");
 }

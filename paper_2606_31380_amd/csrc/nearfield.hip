@@ -81,19 +81,29 @@ __global__ __launch_bounds__(TPB) void nearfield_kernel(
 }
 
 // partial: slots x M x nrhs complex128 (nearfield_slots); u = sum over slots.
-int nearfield_slots(int64_t M, int cu_count) {
+// The matrix-core sums (pairmm.hip) where the wavenumber allows their scaling
+// by k: one evaluation of the kernel for all right-hand sides and the table's
+// sine and cosine (28,800 nodes x 5000 points, 8 right-hand sides: 2.97 -> 0.42
+// ms a call); the kernel above for k = 0 and beyond that range.
+int nearfield_slots(const qax_problem* p, int64_t M, int problem, int cu_count) {
+  if (mm_k_ok(p->k[problem])) return mm_slots(p, M, problem, 1, cu_count);
   const int64_t blocks = (M + 255) / 256;
   return (int)std::max<int64_t>(1, std::min<int64_t>(64, (8LL * cu_count + blocks - 1) / blocks));
 }
 
 hipError_t launch_nearfield(qax_problem* p, const double* mu, int nrhs, const double* pts, int64_t M,
                             int problem, int slots, double* partial, double* u) {
-  const int64_t s0 = p->off[p->prob_body0[problem]], s1 = p->off[p->prob_body0[problem + 1]];
-  dim3 grid((unsigned)((M + 255) / 256), (unsigned)slots, (unsigned)nrhs);
-  hipLaunchKernelGGL((nearfield_kernel<256>), grid, dim3(256), 0, p->stream, pts, M, p->d_pos,
-                     p->d_aw, p->d_ew, p->form(), p->N, s0, s1,
-                     slots, p->k[problem], (const double2*)mu, nrhs, (double2*)partial);
-  hipError_t e = hipGetLastError();
+  hipError_t e = hipSuccess;
+  if (mm_k_ok(p->k[problem])) {
+    e = launch_mm_near(p, mu, nrhs, pts, M, problem, slots, partial);
+  } else {
+    const int64_t s0 = p->off[p->prob_body0[problem]], s1 = p->off[p->prob_body0[problem + 1]];
+    dim3 grid((unsigned)((M + 255) / 256), (unsigned)slots, (unsigned)nrhs);
+    hipLaunchKernelGGL((nearfield_kernel<256>), grid, dim3(256), 0, p->stream, pts, M, p->d_pos,
+                       p->d_aw, p->d_ew, p->form(), p->N, s0, s1,
+                       slots, p->k[problem], (const double2*)mu, nrhs, (double2*)partial);
+    e = hipGetLastError();
+  }
   if (e != hipSuccess) return e;
   const int64_t count = M * nrhs;
   hipLaunchKernelGGL(reduce_slots_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0,

@@ -637,6 +637,287 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
         make_double2(S.sum[0][e] * sc, S.sum[1][e] * sc);
 }
 
+// ---------------------------------------------------------------- FP64 path
+// The same scheme on v_mfma_f64_16x16x4f64, for pair sums (tasks given; the
+// targets' own body is left out), for evaluation points off the surfaces and
+// for far-field directions (tasks null: 128 targets x one of gridDim.y ranges
+// of a problem's sources x problem).  Lane l evaluates K for targets l % 16 of
+// two tiles and source l / 16 of each step of four, which is the A operand's
+// layout; a tile of 8 right-hand sides has columns [Re mu | Im mu] against
+// Re K and [-Im mu | Re mu] against Im K.
+// Pair sums and points: with t = 1 / (k r), K = k e^{ikr} (i - t) aw.(y - x) / r^2 / 4 pi
+// (combined field: minus i eta |aw| e^{ikr} / r; single layer: |aw| e^{ikr} / r),
+// the sine and cosine from a table of k sin, k cos.  Directions xhat: K = (-i k xhat.aw) e^{-i k xhat.y}
+// (combined field: plus -i eta |aw| e^{...}; single layer: |aw| e^{...}) / 4 pi.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+enum { MM_DOUBLE = 0, MM_COMBINED = 1, MM_SINGLE = 2, MM_FAR = 3 };   // far field: MM_FAR + formulation
+
+struct MmTargets {        // coordinate c of target i: x[i step + c stride]
+  const double* x;
+  int64_t step, stride;
+  int64_t count;          // targets
+  const int2* items;      // far field: paired directions (item: direction, its exact negation), or null
+  int64_t n_items;        // items, or targets without a list
+  const int64_t* pinfo;   // first node of every problem, the end of the last, then their k (as bits)
+  int32_t nprob, prob0;   // problems in pinfo, first problem evaluated (gridDim.z of them)
+};
+
+// VEC: up to VEC right-hand sides by vector fmas instead (each lane adds up its
+// targets over every fourth source, the four sums are added at the end).
+// PAIRS (far field): the lane's two targets are a direction and its negation,
+// with one sine and cosine for both.
+// Bound by FP64 issue: about 40 instructions a pair for K (4.4 cycles each, 200
+// per 64 pairs with the table reads), 145 cycles of matrix time per tile of 8
+// right-hand sides, or 25 of vector time each.  40 bodies of 2048 nodes (6.5e9
+// pairs), against the per-target kernel: 2 right-hand sides 17.4 -> 11.0 ms,
+// 4 17.8 -> 13.4 (14.2 on the matrix cores), 8 21.4 -> 14.2, 16 41.8 -> 20.2, 32 81.3 -> 32.3.
+// Far field of 57,600 nodes in 40,000 directions 3.1 -> 2.4 ms (28.7 vector
+// instructions a pair, the vector ALUs 90 % busy at the 1.84 GHz that FP64 work
+// leaves; before, nine LDS reads a pair for one direction per lane).
+template <int NT, int VEC, int FORM, bool PAIRS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT > 2 ? 2 : 3))) void mm_sum_kernel(
+    const MmTask* __restrict__ tasks, MmTargets P, const BodyDev* __restrict__ bodies,
+    const int32_t* __restrict__ node_body, const double* __restrict__ pos, const double* __restrict__ aw,
+    const double* __restrict__ ew, int64_t N, const double2* __restrict__ mu, int nrhs, int r0,
+    const int32_t* __restrict__ seg_active, double2* __restrict__ partial) {
+  constexpr bool FAR = FORM >= MM_FAR;
+  constexpr bool EW = FORM % 3 != MM_DOUBLE;     // the single-layer weights enter
+  constexpr int NM = VEC ? 1 : NT;               // groups of 8 right-hand sides staged
+  constexpr int PER = PAIRS ? 16 : 32;           // items per wavefront
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int col = lane & 15, kq = lane >> 4;
+  MmTask T;
+  int64_t slot = 0;
+  if (tasks) {
+    T = tasks[blockIdx.x];
+    slot = T.slot;
+  } else {
+    const int pr = P.prob0 + blockIdx.z;
+    const int32_t q0 = (int32_t)(P.pinfo[pr] / MM_C), q1 = (int32_t)(P.pinfo[pr + 1] / MM_C);
+    T.t0 = (int64_t)blockIdx.x * (4 * PER);
+    T.nt = (int32_t)min((int64_t)(4 * PER), P.n_items - T.t0);
+    T.c0 = q0 + (int32_t)((int64_t)(q1 - q0) * blockIdx.y / gridDim.y);
+    T.c1 = q0 + (int32_t)((int64_t)(q1 - q0) * (blockIdx.y + 1) / gridDim.y);
+    T.body = -1;
+    T.problem = pr;
+    T.k = __longlong_as_double(P.pinfo[P.nprob + 1 + pr]);
+    slot = (int64_t)blockIdx.y * gridDim.z + blockIdx.z;
+  }
+  double2* dst = partial + slot * P.count * nrhs;
+  if (mm_inactive(seg_active, T.problem, nrhs, r0, min(nrhs, r0 + 8 * NM), T.t0, T.nt, dst)) return;
+  const double k = T.k;
+  const int64_t item0 = T.t0 + wave * PER;
+  const bool live = wave * PER < T.nt;
+  const int mybody = tasks && live ? node_body[item0] : -1;
+  // target of the tile's row q (16 rows), and whether there is one
+  auto target = [&](int t, int q, int64_t* i) {
+    const int64_t m = item0 + (PAIRS ? q : 16 * t + q);
+    const bool ok = m < P.n_items;
+    *i = ok ? m : P.n_items - 1;
+    if (FAR && P.items) *i = PAIRS && t ? P.items[*i].y : P.items[*i].x;
+    return ok;
+  };
+  double tx[2], ty[2], tz[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    int64_t i;
+    (void)target(t, col, &i);
+    tx[t] = P.x[i * P.step];
+    ty[t] = P.x[i * P.step + P.stride];
+    tz[t] = P.x[i * P.step + 2 * P.stride];
+  }
+  __shared__ double2 sQ[2][3][MM_C];             // (x, y), (z, awx), (awy, awz)
+  __shared__ double sE[2][EW ? MM_C : 1];        // ew (ew / k)
+  __shared__ double2 sM[2][NM][MM_C][8];
+  __shared__ double2 sTab[512];
+  for (int i = tid; i < 512; i += 256) {         // ordered by the first chunk's barrier
+    double s, c;
+    sincos_2pi(i * (1.0 / 512.0), &s, &c);
+    sTab[i] = FAR ? make_double2(s, c) : make_double2(k * s, k * c);
+  }
+
+  f64x4 acc[2][NT ? NT : 1];
+  double vr[2][VEC ? VEC : 1], vi[2][VEC ? VEC : 1];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+#pragma unroll
+    for (int n = 0; n < NT; ++n) acc[t][n] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int r = 0; r < VEC; ++r) vr[t][r] = vi[t][r] = 0.0;
+  }
+  const double u512 = U512;                      // phases in 512ths of a revolution
+  const double ku = (FAR ? -k : k) * u512;       // far field: the phase -k xhat.y
+  // what ku leaves of k 512 / 2 pi (without it every phase is off by the same
+  // 2^-54 of itself, which does not average out over the sources)
+  const double kul = fma(k, u512, -ku) + k * U512_LOW;
+  const double ik = FAR ? 0.0 : 1.0 / k;
+  double X[2], Y[2], Z[2];                       // far field: k xhat, and ku xhat in tx, ty, tz
+  if (FAR) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      X[t] = k * tx[t];
+      Y[t] = k * ty[t];
+      Z[t] = k * tz[t];
+      tx[t] *= ku;
+      ty[t] *= ku;
+      tz[t] *= ku;
+    }
+  }
+  int buf = 0;
+  MmWalk W(T, bodies);
+  double2 preM[NM];
+  double2 preQ[3];
+  double preE = 0.0;
+  // thread tid loads right-hand side tid % 8 of source tid / 8; threads 0-31 also the records
+  auto fetch = [&](int c) {
+    const int64_t j = (int64_t)c * MM_C + (tid >> 3);
+#pragma unroll
+    for (int n = 0; n < NM; ++n) {
+      const int r = r0 + 8 * n + (tid & 7);
+      preM[n] = r < nrhs ? mu[j * nrhs + r] : make_double2(0.0, 0.0);
+    }
+    if (tid < MM_C) {
+      const int64_t i = (int64_t)c * MM_C + tid;
+      preQ[0] = make_double2(pos[i], pos[N + i]);
+      preQ[1] = make_double2(pos[2 * N + i], aw[i]);
+      preQ[2] = make_double2(aw[N + i], aw[2 * N + i]);
+      if (EW) preE = FAR ? ew[i] : ew[i] / k;
+    }
+  };
+  int c = W.next(T.c0);
+  if (c < T.c1) {
+    fetch(c);
+    if (tasks) W.start(c, bodies, node_body);
+  }
+  const uint32_t flip = col < 8 ? 0x80000000u : 0u;   // sign of the second operand's columns
+  while (c < T.c1) {
+    if (tasks) W.to(c, bodies);
+#pragma unroll
+    for (int n = 0; n < NM; ++n) sM[buf][n][tid >> 3][tid & 7] = preM[n];
+    if (tid < MM_C) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) sQ[buf][q][tid] = preQ[q];
+      if (EW) sE[buf][tid] = preE;
+    }
+    __syncthreads();
+    const int cn = W.next(c + 1);
+    if (cn < T.c1) fetch(cn);
+    if (live && (!tasks || W.body != mybody)) {
+#pragma unroll 2
+      for (int st = 0; st < MM_C / 4; ++st) {
+        const int j = 4 * st + kq;
+        const double2 q0 = sQ[buf][0][j], q1 = sQ[buf][1][j], q2 = sQ[buf][2][j];
+        const double e = EW ? sE[buf][j] : 0.0;
+        double kr[2], ki[2], sn = 0.0, cs = 0.0, d = 0.0;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          if constexpr (FAR) {
+            // the negated direction: d and the sine change sign
+            if (PAIRS && t) {
+              sn = -sn;
+              d = -d;
+            } else {
+              sincos_tab512(fma(tx[t], q0.x, fma(ty[t], q0.y, tz[t] * q1.x)), sTab, &sn, &cs);
+              d = fma(X[t], q1.y, fma(Y[t], q2.x, Z[t] * q2.y));
+            }
+            if constexpr (FORM == MM_FAR + MM_SINGLE) {
+              kr[t] = e * cs;
+              ki[t] = e * sn;
+            } else {
+              const double a = EW ? d + e : d;
+              kr[t] = a * sn;
+              ki[t] = -(a * cs);
+            }
+          } else {
+            const double dx = q0.x - tx[t], dy = q0.y - ty[t], dz = q1.x - tz[t];
+            const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
+            const double ir = rsqrt_pos(r2);
+            sincos_tab512_scaled(r2 * ir, ku, kul, sTab, &sn, &cs);
+            if constexpr (FORM == MM_SINGLE) {
+              const double g = e * ir;
+              kr[t] = cs * g;
+              ki[t] = sn * g;
+            } else {
+              d = fma(q1.y, dx, fma(q2.x, dy, q2.y * dz)) * (ir * ir);
+              const double it = ir * ik;
+              kr[t] = -(fma(cs, it, sn) * d);
+              ki[t] = fma(-sn, it, cs) * d;
+              if constexpr (FORM == MM_COMBINED) {
+                const double g = e * ir;
+                kr[t] = fma(g, sn, kr[t]);
+                ki[t] = fma(-g, cs, ki[t]);
+              }
+            }
+          }
+        }
+        if constexpr (VEC != 0) {
+#pragma unroll
+          for (int r = 0; r < VEC; ++r) {
+            const double2 m = sM[buf][0][j][r];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+              vr[t][r] = fma(kr[t], m.x, fma(-ki[t], m.y, vr[t][r]));
+              vi[t][r] = fma(kr[t], m.y, fma(ki[t], m.x, vi[t][r]));
+            }
+          }
+        } else {
+          double b1[NT ? NT : 1], b2[NT ? NT : 1];
+#pragma unroll
+          for (int n = 0; n < NT; ++n) {
+            const double* m = (const double*)&sM[buf][n][j][col & 7];
+            b1[n] = m[col >> 3];
+            const double x = m[1 - (col >> 3)];
+            b2[n] = __hiloint2double(__double2hiint(x) ^ flip, __double2loint(x));
+          }
+#pragma unroll
+          for (int n = 0; n < NT; ++n)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+              acc[t][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(kr[t], b1[n], acc[t][n], 0, 0, 0);
+#pragma unroll
+          for (int n = 0; n < NT; ++n)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+              acc[t][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(ki[t], b2[n], acc[t][n], 0, 0, 0);
+        }
+      }
+    }
+    buf ^= 1;
+    c = cn;
+  }
+  if (!live) return;
+  const double sc = 1.0 / FOUR_PI;
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    int64_t i;
+    if constexpr (VEC != 0) {
+      const bool ok = target(t, col, &i) && kq == 0;
+#pragma unroll
+      for (int r = 0; r < VEC; ++r) {
+        double re = vr[t][r], im = vi[t][r];
+        re += __shfl_xor(re, 16);
+        im += __shfl_xor(im, 16);
+        re += __shfl_xor(re, 32);
+        im += __shfl_xor(im, 32);
+        if (ok && r0 + r < nrhs) dst[i * nrhs + r0 + r] = make_double2(re * sc, im * sc);
+      }
+    } else {
+      // element e of the lane: column l % 16, row l / 16 + 4 e of the tile
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool ok = target(t, kq + 4 * e, &i) && col < 8;
+#pragma unroll
+        for (int n = 0; n < NT; ++n) {
+          const double re = acc[t][n][e], im = __shfl_down(re, 8);
+          const int r = r0 + 8 * n + col;
+          if (ok && r < nrhs) dst[i * nrhs + r] = make_double2(re * sc, im * sc);
+        }
+      }
+    }
+  }
+}
+
 // ---------------------------------------------------------------- plan and launch
 static size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
@@ -777,6 +1058,86 @@ hipError_t launch_pair_mmf(qax_problem* p, const double* mu, int nrhs, double* w
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+template <int V>
+using I = std::integral_constant<int, V>;
+
+// FP64 sums over the pair-sum tasks or other targets, right-hand sides 32 at a time.
+template <int FORM, bool PAIRS>
+static hipError_t launch_mm_sum(qax_problem* p, const MmTask* tasks, const MmTargets& P, dim3 grid, const double* mu,
+                                int nrhs, double* partial) {
+  for (int r0 = 0; r0 < nrhs; r0 += 32) {
+    auto go = [&](auto nt, auto vec) {
+      hipLaunchKernelGGL((mm_sum_kernel<decltype(nt)::value, decltype(vec)::value, FORM, PAIRS>), grid, dim3(256), 0,
+                         p->stream, tasks, P, p->d_bodies, p->d_node_body, p->d_pos, p->d_aw, p->d_ew, p->N,
+                         (const double2*)mu, nrhs, r0, p->seg_active, (double2*)partial);
+    };
+    const int left = nrhs - r0;
+    if (left == 1) go(I<0>{}, I<1>{});
+    else if (left == 2) go(I<0>{}, I<2>{});
+    else if (left <= 4) go(I<0>{}, I<4>{});
+    else if (left <= 8) go(I<1>{}, I<0>{});
+    else if (left <= 16) go(I<2>{}, I<0>{});
+    else if (left <= 24) go(I<3>{}, I<0>{});
+    else go(I<4>{}, I<0>{});
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+template <int BASE, bool PAIRS>
+static hipError_t launch_mm_forms(qax_problem* p, const MmTask* tasks, const MmTargets& P, dim3 grid,
+                                  const double* mu, int nrhs, double* partial) {
+  switch (p->form()) {
+    case 1: return launch_mm_sum<BASE + MM_COMBINED, PAIRS>(p, tasks, P, grid, mu, nrhs, partial);
+    case 2: return launch_mm_sum<BASE + MM_SINGLE, PAIRS>(p, tasks, P, grid, mu, nrhs, partial);
+    default: return launch_mm_sum<BASE + MM_DOUBLE, PAIRS>(p, tasks, P, grid, mu, nrhs, partial);
+  }
+}
+
+// Partial sums of the FP64 pair sum (slots x N x nrhs at `work`).
+hipError_t launch_pair_mmd(qax_problem* p, const double* mu, int nrhs, double* work) {
+  const MmTargets P = {p->d_pos, 1, p->N, p->N, nullptr, p->N, nullptr, 0, 0};
+  return launch_mm_forms<MM_DOUBLE, false>(p, p->mm.d_tasks, P, dim3((unsigned)p->mm.n_tasks), mu, nrhs, work);
+}
+
+// Ranges of the sources for `count` targets of `nprob` problems from prob0 on:
+// 24 workgroups per compute unit as for the pair sums, at least two chunks each.
+int mm_slots(const qax_problem* p, int64_t count, int prob0, int nprob, int cu_count) {
+  int64_t cmax = 1;
+  for (int pr = prob0; pr < prob0 + nprob; ++pr)
+    cmax = std::max(cmax, (p->off[p->prob_body0[pr + 1]] - p->off[p->prob_body0[pr]]) / MM_C);
+  const int64_t blocks = (count + MM_T - 1) / MM_T * nprob;
+  return (int)std::max<int64_t>(1, std::min<int64_t>({64, cmax / 2, (24LL * cu_count + blocks - 1) / blocks}));
+}
+
+// Near field of one problem at M points (SoA); partial: slots x M x nrhs.
+hipError_t launch_mm_near(qax_problem* p, const double* mu, int nrhs, const double* pts, int64_t M, int problem,
+                          int slots, double* partial) {
+  const MmTargets P = {pts, 1, M, M, nullptr, M, p->d_pinfo, p->n_problems, problem};
+  return launch_mm_forms<MM_DOUBLE, false>(p, nullptr, P, dim3((unsigned)((M + MM_T - 1) / MM_T), (unsigned)slots), mu,
+                                           nrhs, partial);
+}
+
+// Far field of every problem in M directions (AoS); partial: slots x problems x
+// M x nrhs.  items: first the n_pairs pairs of a direction and its exact
+// negation, then the n_single other directions; null: all M directions.
+hipError_t launch_mm_far(qax_problem* p, const double* mu, int nrhs, const double* xhat, int64_t M, const int2* items,
+                         int64_t n_pairs, int64_t n_single, int slots, double* partial) {
+  MmTargets P = {xhat, 3, 1, M, items, n_pairs, p->d_pinfo, p->n_problems, 0};
+  auto grid = [&](int64_t n, int per) {
+    return dim3((unsigned)((n + per - 1) / per), (unsigned)slots, (unsigned)p->n_problems);
+  };
+  hipError_t e = hipSuccess;
+  if (items && n_pairs)
+    e = launch_mm_forms<MM_FAR, true>(p, nullptr, P, grid(n_pairs, MM_T / 2), mu, nrhs, partial);
+  P.items = items ? items + n_pairs : nullptr;
+  P.n_items = items ? n_single : M;
+  if (e == hipSuccess && P.n_items)
+    e = launch_mm_forms<MM_FAR, false>(p, nullptr, P, grid(P.n_items, MM_T), mu, nrhs, partial);
+  return e;
 }
 
 }  // namespace qax

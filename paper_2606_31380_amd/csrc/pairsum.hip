@@ -1477,16 +1477,17 @@ static void launch_any(qax_problem* p, bool f64, int tpb, int nrc, const double*
 // right-hand sides whose wavenumbers allow their scaling by k (k in
 // [1e-6, 1e6]; FP32 powers of k r overflow beyond): two right-hand sides take
 // 33 ms against the per-target kernel's 42 ms on 100 bodies of 2048 nodes in
-// FP32, and the ratio grows with their number.
-static bool use_mm(const qax_problem* p, int prec, int nrhs) {
-  if (prec == QAX_FP64 || nrhs < 2) return false;
+// FP32 (FP64, 40 bodies: 10.3 against 17.4 ms), and the ratio grows with their
+// number.
+bool pair_uses_mm(const qax_problem* p, int nrhs) {
+  if (nrhs < 2) return false;
   for (double k : p->k)
-    if (!(k >= 1e-6 && k <= 1e6)) return false;
+    if (!mm_k_ok(k)) return false;
   return true;
 }
 
 hipError_t ensure_pair_plan(qax_problem* p, int prec, int nrhs) {
-  if (!use_mm(p, prec, nrhs) || p->mm.d_tasks) return hipSuccess;
+  if (!pair_uses_mm(p, nrhs) || p->mm.d_tasks) return hipSuccess;
   int cus = 0;
   hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device);
   return e == hipSuccess ? ensure_mm_plan(p, std::max(cus, 1)) : e;
@@ -1497,7 +1498,7 @@ hipError_t ensure_pair_plan(qax_problem* p, int prec, int nrhs) {
 // task table was planned with; right-hand sides per pass from the tuning
 // (clamped to a supported configuration).
 size_t pair_work_bytes(const qax_problem* p, int prec, int nrhs) {
-  if (use_mm(p, prec, nrhs)) return std::max(mm_work_bytes(p, prec, nrhs), lattice_work_bytes(p, nrhs));
+  if (pair_uses_mm(p, nrhs)) return std::max(mm_work_bytes(p, prec, nrhs), lattice_work_bytes(p, nrhs));
   const int slots = prec == QAX_FP64 ? p->slots64 : p->slots32;
   size_t b = std::max((size_t)slots * p->N * nrhs * 16, lattice_work_bytes(p, nrhs));
   if (nrhs == 1 && p->sym.ok)
@@ -1575,10 +1576,10 @@ hipError_t launch_pair_sum(qax_problem* p, int prec, const double* mu, double* o
     }
     return hipSuccess;
   }
-  if (use_mm(p, prec, nrhs)) {
+  if (pair_uses_mm(p, nrhs)) {
     if (!p->mm.d_tasks) return hipErrorInvalidConfiguration;
     timing_begin(p, kind);
-    hipError_t e = launch_pair_mmf(p, mu, nrhs, partial);
+    hipError_t e = f64 ? launch_pair_mmd(p, mu, nrhs, partial) : launch_pair_mmf(p, mu, nrhs, partial);
     timing_end(p, kind);
     if (e != hipSuccess) return e;
     const int64_t count = p->N * nrhs;

@@ -10,6 +10,8 @@ Bounds.  FP32: the phase carries FP32 rounding of the distance difference
 2-norm and 4e-6 of the largest entry.  Near targets: r^2 is formed against
 |D|^2, so its relative error is (D / r)^2 2^-24, 36 x 6e-8 at D = 0.6 and
 r = 0.1, up to 2.5 of which enters 1 / r^2 and the factor (i - 1 / kr): 6e-6.
+FP64: 1e-12 of the norm and of the largest entry (coordinates of size 20 in
+phases k r of size 100 and sums of a few thousand terms, each 2^-53).
 """
 import numpy as np
 import pytest
@@ -75,6 +77,8 @@ def test_every_tile_of_right_hand_sides(form):
     with qax.Problem(s, formulation=FORMS[form]) as P:
         for nrhs in (2, 16, 17, 32, 33, 64, 65, 70):
             close(run(P, qax.QAX_MIXED, mu[:, :nrhs]), want[:, :nrhs], 2e-6, 4e-6)
+        for nrhs in (2, 3, 4, 5, 8, 9, 16, 17, 24, 25, 32, 33, 70):
+            close(run(P, qax.QAX_FP64, mu[:, :nrhs]), want[:, :nrhs], 1e-12, 1e-12)
 
 
 @pytest.mark.parametrize("nrhs", [3, 20, 40])
@@ -88,6 +92,7 @@ def test_near_targets(nrhs):
     want = oracle_sum(s, mu, "double")
     with qax.Problem(s) as P:
         close(run(P, qax.QAX_MIXED, mu), want, 6e-6, 6e-6)
+        close(run(P, qax.QAX_FP64, mu), want, 1e-12, 1e-12)
 
 
 @pytest.mark.parametrize("nrhs", [5, 30, 50])
@@ -119,3 +124,56 @@ def test_small_wavenumber_falls_back():
         mu = densities(t.n_unknowns(), 4)
         with qax.Problem(t) as P:
             close(run(P, qax.QAX_MIXED, mu), oracle_sum(t, mu, "double"), 2e-6, 4e-6)
+            close(run(P, qax.QAX_FP64, mu), oracle_sum(t, mu, "double"), 1e-12, 1e-12)
+
+
+def field_reference(s, x, mu, problem, form, far):
+    """Near field at x, or far field in directions x, of one problem in plain numpy."""
+    d = geo.discretize(s)
+    m = d.problem == problem
+    k, y, aw, v = float(s.k[problem]), d.pos[m], d.aw[m], mu[m]
+    w = np.linalg.norm(aw, axis=1)
+    if far:
+        e = np.exp(-1j * k * (x @ y.T))
+        f = w if form == "single" else -1j * k * (x @ aw.T) - (1j * k * w if form == "combined" else 0.0)
+        return (e * f) @ v / (4 * np.pi)
+    dx = y[None] - x[:, None]
+    r = np.sqrt((dx * dx).sum(-1))
+    e = np.exp(1j * k * r) / (4 * np.pi * r)
+    f = w if form == "single" else (1j * k / r - 1 / r ** 2) * np.einsum("ijc,jc->ij", dx, aw)
+    if form == "combined":
+        f = f - 1j * k * w
+    return (e * f) @ v
+
+
+@pytest.mark.parametrize("form", sorted(FORMS))
+@pytest.mark.parametrize("points", [1, 31, 65, 200])
+def test_fields_every_tile(form, points):
+    # odd numbers of targets (partial tiles, clamped rows), tiles of
+    # right-hand sides; the far field with no, some and only paired directions
+    s = scenario()
+    mu = densities(s.n_unknowns(), 33)
+    rng = np.random.default_rng(points)
+    near = rng.uniform(-9.0, 9.0, (points, 3)) + np.array([0.0, 0.0, 25.0])
+    dirs = rng.standard_normal((points, 3))
+    dirs /= np.linalg.norm(dirs, axis=1)[:, None]
+    with qax.Problem(s, formulation=FORMS[form]) as P:
+        for nrhs in (1, 2, 4, 7, 9, 33):
+            v = torch.from_numpy(np.ascontiguousarray(mu[:, :nrhs].ravel())).to(DEV)
+            for p in range(2):
+                u = torch.zeros(points * nrhs, dtype=torch.complex128, device=DEV)
+                qax.qax_nearfield(P.h, v, near, u, nrhs, problem=p)
+                close(u.cpu().numpy().reshape(points, nrhs),
+                      field_reference(s, near, mu[:, :nrhs], p, form, False), 1e-12, 1e-12)
+            for x in (dirs, np.concatenate([dirs, -dirs[::2]]), np.concatenate([-dirs, dirs, dirs])):
+                n = x.shape[0]
+                u = torch.zeros(2 * n * nrhs, dtype=torch.complex128, device=DEV)
+                qax.qax_farfield(P.h, v, x, u, nrhs)
+                got = u.cpu().numpy().reshape(2, n, nrhs)
+                un = torch.zeros_like(u)
+                qax.qax_farfield_noalloc(P.h, v, torch.from_numpy(x).to(DEV), un, nrhs)
+                gn = un.cpu().numpy().reshape(2, n, nrhs)
+                for p in range(2):
+                    want = field_reference(s, x, mu[:, :nrhs], p, form, True)
+                    close(got[p], want, 1e-12, 1e-12)
+                    close(gn[p], want, 1e-12, 1e-12)
