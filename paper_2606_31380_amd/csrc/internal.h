@@ -71,7 +71,8 @@ struct PairTask {
 // super-task is a square of up to SYM_SMAX x SYM_SMAX block pairs (I, J),
 // I <= J, of one problem, evaluated by one workgroup.  Its target-side sums go
 // to ni slots from part[toff], its source-side sums to nj slots from
-// part[soff] (SYM_T complex128 values per slot).
+// part[soff] (SYM_T complex128 values per slot).  Where the block pairs are few,
+// each is split by its sources [c0, c1) into parts with a target slot each.
 constexpr int SYM_T = 256;
 constexpr int SYM_SMAX = 8;
 // largest workspace of one launch of the reciprocal kernels, complex128
@@ -87,6 +88,7 @@ struct SymSuper {
   int32_t i0, ni, j0, nj;  // block rows [i0, i0 + ni) x columns [j0, j0 + nj)
   int32_t diag;            // rows == columns: block pairs with J >= I only
   int32_t problem;
+  int32_t c0, c1;          // sources [c0, c1) of each column block (a part of a split pair of blocks)
   double k;
   uint64_t skip;           // bit ii * SYM_SMAX + jj: both blocks inside one body
   int64_t toff, soff;      // first target / source slot

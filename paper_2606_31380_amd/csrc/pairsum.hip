@@ -37,6 +37,7 @@ namespace qax {
 
 constexpr double INV_FOUR_PI = 0.0795774715459476678844;
 
+
 // Lockstep solves pass seg_active[problem * nrhs + r] (0 once that GMRES
 // segment has converged in the current cycle; its basis vectors are then
 // zero).  A task none of whose right-hand sides is active writes zeros to its
@@ -465,9 +466,14 @@ template <typename S2>
 __device__ __forceinline__ bool sym_inactive(const SymSuper& T, const int32_t* __restrict__ seg_active,
                                              S2* __restrict__ part) {
   if (!seg_active || seg_active[T.problem] != 0) return false;
-  for (int e = threadIdx.x; e < (T.ni + T.nj) * SYM_T; e += blockDim.x) {
+  for (int e = threadIdx.x; e < T.ni * SYM_T; e += blockDim.x) {
     part[T.toff + e].x = 0;
     part[T.toff + e].y = 0;
+  }
+  for (int e = threadIdx.x; e < T.nj * SYM_T; e += blockDim.x) {
+    if (e % SYM_T < T.c0 || e % SYM_T >= T.c1) continue;   // (another part's)
+    part[T.soff + e].x = 0;
+    part[T.soff + e].y = 0;
   }
   return true;
 }
@@ -554,6 +560,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(5))) void p
     for (int jj = 0; jj < T.nj; ++jj) {
       if (!((rowmask >> jj) & 1u)) continue;
       const SymBlock BJ = blocks[T.j0 + jj];
+      const int cend = min(BJ.n, T.c1);
       const bool dtask = (T.j0 + jj) == I;    // diagonal block: target direction only
       const bool first_src = !dtask && !((touched >> jj) & 1u);
       if (!dtask) touched |= 1u << jj;
@@ -561,11 +568,11 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(5))) void p
       float mx[2], my[2], mz[2], bq[2], d2s[2], dns[2], ph0[2], mre[2], mie[2];
       bool msk[2];
       int cur_b = -1;
-      for (int cs = 0; cs < BJ.n;) {
+      for (int cs = T.c0; cs < cend;) {
         const int64_t node = BJ.n0 + cs;
         const int b = node_body[node];
         const BodyDev& BB = bodies[b];
-        const int cl = (int)min((int64_t)min(64, BJ.n - cs), BB.off + BB.n - node);
+        const int cl = (int)min((int64_t)min(64, cend - cs), BB.off + BB.n - node);
         if (b != cur_b) {
           cur_b = b;
 #pragma unroll
@@ -795,17 +802,18 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) void p
     for (int jj = 0; jj < T.nj; ++jj) {
       if (!((rowmask >> jj) & 1u)) continue;
       const SymBlock BJ = blocks[T.j0 + jj];
+      const int cend = min(BJ.n, T.c1);
       const bool dtask = (T.j0 + jj) == I;
       const bool first_src = !dtask && !((touched >> jj) & 1u);
       if (!dtask) touched |= 1u << jj;
       double Dx[2], Dy[2], Dz[2], d2[2], bq[2], mre[2], mie[2];
       bool msk[2];
       int cur_b = -1;
-      for (int cs = 0; cs < BJ.n;) {
+      for (int cs = T.c0; cs < cend;) {
         const int64_t node = BJ.n0 + cs;
         const int b = node_body[node];
         const BodyDev& BB = bodies[b];
-        const int cl = (int)min((int64_t)min(64, BJ.n - cs), BB.off + BB.n - node);
+        const int cl = (int)min((int64_t)min(64, cend - cs), BB.off + BB.n - node);
         if (b != cur_b) {
           cur_b = b;
 #pragma unroll
@@ -1068,7 +1076,7 @@ static void plan_sym_blocks(qax_problem* p) {
 // Super-tasks of s x s block pairs, sorted by decreasing cost, cut into
 // launches whose slots fit `cap` complex values; per launch and block, the
 // slots that hold sums of the block's nodes (in super-task order).
-static void plan_sym_supers(qax_problem* p, int pi, int s, int64_t cap) {
+static void plan_sym_supers(qax_problem* p, int pi, int s, int64_t cap, int cu_count) {
   auto& S = p->sym;
   auto& P = S.plan[pi];
   P.supers.clear();
@@ -1105,6 +1113,8 @@ static void plan_sym_supers(qax_problem* p, int pi, int s, int64_t cap) {
           }
         if (!visits) continue;
         T.toff = T.soff = 0;
+        T.c0 = 0;
+        T.c1 = SYM_T;
         P.supers.push_back(T);
         cost.push_back(c);
       }
@@ -1138,14 +1148,41 @@ static void plan_sym_supers(qax_problem* p, int pi, int s, int64_t cap) {
   sorted.reserve(ord.size());
   for (int64_t i : ord) sorted.push_back(P.supers[i]);
   P.supers.swap(sorted);
-  // launches and slot offsets
+  // Few block pairs leave the chip idle (one takes 77 us in FP64 and 45 in
+  // FP32, whatever their number): below eight workgroups per compute unit each
+  // pair is split into 2, 4 or 8 parts by its sources, which write a target slot
+  // each and share the source slot.  Calls at N = 1600: 92.7 -> 30.2 us (FP32 63 -> 26);
+  // N = 5568: 101.6 -> 64.1 (66.4 -> 46.3); N = 11,936: 212 -> 182 (121 -> 106);
+  // N = 23,712 (4371 pairs): 625 -> 625 with 2 parts, 727 with 8, so not split.
+  int parts = 1;
+  if (s == 1)
+    while (parts < 8 && (int64_t)P.supers.size() * parts < 8LL * cu_count) parts *= 2;
+  if (parts > 1) {
+    std::vector<SymSuper> split;
+    for (const SymSuper& T : P.supers)
+      for (int q = 0; q < parts; ++q) {
+        SymSuper U = T;
+        U.c0 = SYM_T / parts * q;
+        U.c1 = SYM_T / parts * (q + 1);
+        if (U.c0 < S.blocks[T.j0].n) split.push_back(U);
+      }
+    P.supers.swap(split);
+  }
+  // launches and slot offsets (the parts of a pair stay in one launch)
   P.launch_super.assign(1, 0);
   P.max_slots = 0;
   int64_t used = 0;
   for (size_t i = 0; i < P.supers.size(); ++i) {
     SymSuper& T = P.supers[i];
+    if (T.c0 > 0) {          // a later part: its own target slot only
+      T.toff = used;
+      T.soff = P.supers[i - 1].soff;
+      used += SYM_T;
+      P.max_slots = std::max(P.max_slots, used);
+      continue;
+    }
     const int64_t need = (int64_t)(T.ni + T.nj) * SYM_T;
-    if (used > 0 && used + need > cap) {
+    if (used > 0 && used + need + (parts - 1) * SYM_T > cap) {
       P.launch_super.push_back((int64_t)i);
       used = 0;
     }
@@ -1175,7 +1212,7 @@ static void plan_sym_supers(qax_problem* p, int pi, int s, int64_t cap) {
           for (int jj = T.diag ? ii : 0; jj < T.nj; ++jj) {
             if ((T.skip >> (ii * SYM_SMAX + jj)) & 1ull) continue;
             row = true;
-            if (T.i0 + ii != T.j0 + jj) colseen |= 1u << jj;
+            if (T.i0 + ii != T.j0 + jj && T.c0 == 0) colseen |= 1u << jj;
           }
           if (row) {
             if (pass == 0) ++fill[T.i0 + ii];
@@ -1277,7 +1314,11 @@ static hipError_t upload_sym_plan(qax_problem* p, int pi) {
 }
 
 // Default super-task size: the largest of 8, 4, 2, 1 that still gives every
-// compute unit 16 super-tasks.
+// compute unit 64 super-tasks, about six rounds of the workgroups it holds: the
+// last, partly filled round costs more than the larger squares save (with 16
+// per compute unit N = 57,984 took 1524 us in FP32 and 3203 in FP64 against
+// 1423 and 3114, N = 233,024 23.6 and 49.1 ms against 22.2 and 46.8; with 128
+// 21.8 and 47.2).
 int sym_default_s(const qax_problem* p, int cu_count) {
   const auto& S = p->sym;
   for (int s : {8, 4, 2}) {
@@ -1286,7 +1327,7 @@ int sym_default_s(const qax_problem* p, int cu_count) {
       const int64_t r = (S.prob_blk0[pr + 1] - S.prob_blk0[pr] + s - 1) / s;
       n += r * (r + 1) / 2;
     }
-    if (n >= 16LL * cu_count) return s;
+    if (n >= 64LL * cu_count) return s;
   }
   return 1;
 }
@@ -1307,7 +1348,7 @@ hipError_t plan_sym(qax_problem* p, int pi, int s, int cu_count) {
   if (e != hipSuccess) return e;
   ++p->generation;   // captured solver steps hold the old launch sizes
   // the FP32 slots are complex64: twice as many fit the same workspace
-  plan_sym_supers(p, pi, s, SYM_SLOT_CAP * (pi == 1 ? 2 : 1));
+  plan_sym_supers(p, pi, s, SYM_SLOT_CAP * (pi == 1 ? 2 : 1), cu_count);
   return upload_sym_plan(p, pi);
 }
 
