@@ -599,10 +599,10 @@ static qax_status check_vec_call(qax_problem* p, const void* a, const void* b, i
 }
 
 static qax_status pair_sum_into(qax_problem* p, int prec, const double* mu, double* out, int nrhs,
-                                bool accumulate) {
+                                const double* base) {
   QCHECK(ensure_pair_plan(p, prec, nrhs), "pair-sum plan");
   QBUF(partial, double, "pair_partial", pair_work_bytes(p, prec, nrhs));
-  QCHECK(launch_pair_sum(p, prec, mu, out, nrhs, partial, accumulate), "pair_sum");
+  QCHECK(launch_pair_sum(p, prec, mu, out, nrhs, partial, base), "pair_sum");
   return QAX_OK;
 }
 
@@ -613,7 +613,7 @@ extern "C" qax_status qax_pair_sum(qax_problem* p, qax_prec prec, const void* d_
   if (st != QAX_OK) return st;
   if (prec != QAX_FP64 && prec != QAX_MIXED) return fail(p, QAX_ERR_ARG, "bad precision");
   QCHECK(hipSetDevice(p->device), "hipSetDevice");
-  st = pair_sum_into(p, prec, (const double*)d_mu, (double*)d_out, nrhs, false);
+  st = pair_sum_into(p, prec, (const double*)d_mu, (double*)d_out, nrhs, nullptr);
   if (st != QAX_OK) return st;
   return sync(p, "qax_pair_sum");
 }
@@ -635,7 +635,7 @@ extern "C" qax_status qax_block_apply(qax_problem* p, int32_t inverse, qax_prec 
 
 static qax_status apply_full(qax_problem* p, int prec, const double* mu, double* out, int nrhs) {
   QCHECK(launch_block_apply(p, 0, QAX_FP64, mu, out, nrhs, false), "block_apply");
-  return pair_sum_into(p, prec, mu, out, nrhs, true);
+  return pair_sum_into(p, prec, mu, out, nrhs, out);
 }
 
 extern "C" qax_status qax_apply(qax_problem* p, qax_prec prec, const void* d_mu, void* d_out,
@@ -840,7 +840,10 @@ static qax_status setup_krylov(qax_problem* p, int nrhs, int mmax, Krylov& K) {
   K.N = p->N;
   K.nrhs = nrhs;
   K.nprob = p->n_problems;
-  const int64_t chunk_nodes = std::max<int64_t>(64, 8192 / nrhs);
+  // about 512 workgroups per basis vector, at least 512 entries each (8192
+  // entries a workgroup left 17 us per dot product at N = 45,000, most of the
+  // chip idle)
+  const int64_t chunk_nodes = (std::max<int64_t>(512, std::min<int64_t>(8192, p->N * nrhs / 512)) + nrhs - 1) / nrhs;
   std::vector<Chunk> ch;
   std::vector<int32_t> pc0(p->n_problems + 1, 0);
   for (int pr = 0; pr < p->n_problems; ++pr) {
@@ -988,13 +991,12 @@ static qax_status solve_core(qax_problem* p, qax_prec prec, const double* dirs, 
     hipError_t e = launch_block_apply(p, 1, inner_prec, Vj, t, nrhs, false);
     if (exact_op) {
       if (e == hipSuccess) e = launch_block_apply(p, 0, QAX_MIXED, t, w, nrhs, false);
-      if (e == hipSuccess) e = launch_pair_sum(p, inner_prec, t, w, nrhs, ppart, true);
+      if (e == hipSuccess) e = launch_pair_sum(p, inner_prec, t, w, nrhs, ppart, w);
     } else {
-      if (e == hipSuccess) e = launch_pair_sum(p, inner_prec, t, w, nrhs, ppart, false);
+      if (e == hipSuccess) e = launch_pair_sum(p, inner_prec, t, w, nrhs, ppart, Vj);
     }
     p->seg_active = nullptr;
     if (e != hipSuccess) return e;
-    if (!exact_op) K.axpby(1.0, w, 1.0, Vj, w);
     K.dots(V, vs, j + 1, w, h1);
     K.orth(V, vs, j + 1, h1, w);
     K.dots(V, vs, j + 1, w, h2);
@@ -1296,7 +1298,7 @@ extern "C" qax_status qax_autotune(qax_problem* p, int32_t nrhs_max, const char*
       qax_status s = QAX_OK;
       double* part = (double*)dbuf(p, "pair_partial", pair_work_bytes(p, prec, nrhs), &s);
       if (!part) return hipErrorOutOfMemory;
-      return launch_pair_sum(p, prec, mu, out, nrhs, part, false);
+      return launch_pair_sum(p, prec, mu, out, nrhs, part, nullptr);
     };
     const int lo[4] = {2, 5, 9, 17}, rep[4] = {4, 8, 16, 64};
     auto nrc_ok = [&](int tpb, int nrc, int c, int nrhs) {
@@ -1760,8 +1762,7 @@ static qax_status solve_block(qax_problem* p, qax_prec prec, const double* dirs,
     for (int j = 0; j < m && total_its < maxit; ++j) {
       double* Vj = V + (size_t)j * vs;
       QCHECK(launch_block_apply(p, 1, inner_prec, Vj, T, P, false), "block apply");
-      QCHECK(launch_pair_sum(p, inner_prec, T, W, P, ppart, false), "pair sum");
-      K.axpby(1.0, W, 1.0, Vj, W);
+      QCHECK(launch_pair_sum(p, inner_prec, T, W, P, ppart, Vj), "pair sum");
       // block Gram-Schmidt twice against V_0 .. V_j
       hblk.assign((size_t)(j + 2) * P * P, 0.0);
       for (int pass = 0; pass < 2; ++pass) {

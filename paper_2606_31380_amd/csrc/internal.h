@@ -353,7 +353,7 @@ bool pair_uses_mm(const qax_problem* p, int nrhs);   // several right-hand sides
 hipError_t ensure_pair_plan(qax_problem* p, int prec, int nrhs);
 size_t pair_work_bytes(const qax_problem* p, int prec, int nrhs);
 hipError_t launch_pair_sum(qax_problem* p, int prec, const double* mu, double* out, int nrhs,
-                           double* partial, bool accumulate);
+                           double* partial, const double* base);
 void plan_pair_sum(qax_problem* p, int prec, int cu_count);
 // plan_pair_sum + device copy of the task table (synchronous).
 hipError_t upload_pair_plan(qax_problem* p, int prec, int cu_count);

@@ -45,7 +45,7 @@ hipError_t launch_rhs(qax_problem* p, const double* dirs_dev, int nrhs, double* 
 
 // out[e] = sum_s partial[s][e] (fixed order), from the pair-sum translation unit
 __global__ void reduce_slots_kernel(const double2* __restrict__ partial, int slots, int64_t count,
-                                    double2* __restrict__ out, int accumulate);
+                                    const double2* base, double2* out);
 
 // u_inf[p][dir][r] = (1/4pi) sum_{n in problem p} (-i k_p xhat.aw_n)
 // e^{-i k_p xhat.y_n} mu[n][r] (combined field: plus -i eta |aw_n| e^{...};
@@ -60,14 +60,15 @@ hipError_t launch_farfield(qax_problem* p, const double* mu, int nrhs, const dou
   if (e != hipSuccess) return e;
   const int64_t count = (int64_t)p->n_problems * ndir * nrhs;
   hipLaunchKernelGGL(reduce_slots_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0,
-                     p->stream, (const double2*)partial, slots, count, (double2*)out, 0);
+                     p->stream, (const double2*)partial, slots, count, (const double2*)nullptr, (double2*)out);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- segmented dots
 // partial[i][chunk][r] = sum_{n in chunk} conj(V_i[n][r]) w[n][r]
 // The block has U*nrhs threads (U = 256/nrhs rounded down); thread t handles
-// right-hand side t % nrhs.
+// right-hand side t % nrhs.  Latency-bound: N = 45,000, about nine vectors, 16.8 -> 4.7 us
+// with small chunks and the halving sum (before, one thread added the U sums).
 __global__ __launch_bounds__(256) void mdot_kernel(const double2* __restrict__ V, int64_t vstride,
                                                    const double2* __restrict__ w, int nrhs,
                                                    const Chunk* __restrict__ chunks,
@@ -91,31 +92,38 @@ __global__ __launch_bounds__(256) void mdot_kernel(const double2* __restrict__ V
   sr[t] = ar;
   si[t] = ai;
   __syncthreads();
-  if (t < nrhs) {
-    double xr = 0.0, xi = 0.0;
-    for (int q = 0; q < U; ++q) {
-      xr += sr[t + q * nrhs];
-      xi += si[t + q * nrhs];
+  // the U sums of each right-hand side, halved until one is left
+  for (int left = U; left > 1;) {
+    const int h = (left + 1) >> 1;
+    if (u < left - h) {
+      sr[t] += sr[t + h * nrhs];
+      si[t] += si[t + h * nrhs];
     }
-    partial[((int64_t)i * nchunks + blockIdx.x) * nrhs + t] = make_double2(xr, xi);
+    left = h;
+    __syncthreads();
   }
+  if (u == 0) partial[((int64_t)i * nchunks + blockIdx.x) * nrhs + r] = make_double2(sr[t], si[t]);
 }
 
-// h[i][problem][r] = sum over the chunks of the problem (in order).
-__global__ void mdot_reduce_kernel(const double2* __restrict__ partial, int nchunks, int nrhs,
-                                   const int32_t* __restrict__ prob_chunk0, int nprob,
-                                   double2* __restrict__ h) {
-  const int i = blockIdx.y;
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= nprob * nrhs) return;
+// h[i][problem][r] = sum over the chunks of the problem, one wavefront per
+// sum: each lane its share in order, then the lanes pairwise.
+__global__ __launch_bounds__(64) void mdot_reduce_kernel(const double2* __restrict__ partial, int nchunks, int nrhs,
+                                                         const int32_t* __restrict__ prob_chunk0, int nprob,
+                                                         double2* __restrict__ h) {
+  const int i = blockIdx.y, e = blockIdx.x, lane = threadIdx.x;
   const int pr = e / nrhs, r = e % nrhs;
   double xr = 0.0, xi = 0.0;
-  for (int c = prob_chunk0[pr]; c < prob_chunk0[pr + 1]; ++c) {
+  for (int c = prob_chunk0[pr] + lane; c < prob_chunk0[pr + 1]; c += 64) {
     const double2 v = partial[((int64_t)i * nchunks + c) * nrhs + r];
     xr += v.x;
     xi += v.y;
   }
-  h[(int64_t)i * nprob * nrhs + e] = make_double2(xr, xi);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    xr += __shfl_xor(xr, o);
+    xi += __shfl_xor(xi, o);
+  }
+  if (lane == 0) h[(int64_t)i * nprob * nrhs + e] = make_double2(xr, xi);
 }
 
 // w[n][r] -= sum_{i<m} V_i[n][r] h[i][problem(n)][r]
@@ -292,8 +300,7 @@ void Krylov::dots(const double* V, int64_t vstride, int m, const double* w, doub
   const int nthr = (256 / nrhs) * nrhs;
   hipLaunchKernelGGL(mdot_kernel, dim3(nchunks, m), dim3(nthr), 0, stream, (const double2*)V,
                      vstride / 2, (const double2*)w, nrhs, d_chunks, (double2*)d_partial, nchunks);
-  hipLaunchKernelGGL(mdot_reduce_kernel, dim3(blocks_for((int64_t)nprob * nrhs), m), dim3(256), 0,
-                     stream, (const double2*)d_partial, nchunks, nrhs, d_prob_chunk0, nprob,
+  hipLaunchKernelGGL(mdot_reduce_kernel, dim3((unsigned)(nprob * nrhs), m), dim3(64), 0, stream, (const double2*)d_partial, nchunks, nrhs, d_prob_chunk0, nprob,
                      (double2*)h);
 }
 

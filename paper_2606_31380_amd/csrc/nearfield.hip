@@ -15,7 +15,7 @@ constexpr double INV_FOUR_PI_NF = 0.0795774715459476678844;
 
 // out[e] = sum_s partial[s][e] (fixed order), from the pair-sum translation unit
 __global__ void reduce_slots_kernel(const double2* __restrict__ partial, int slots, int64_t count,
-                                    double2* __restrict__ out, int accumulate);
+                                    const double2* base, double2* out);
 
 // ---------------------------------------------------------------- near field
 // u(x) = 1/(4 pi) sum_{j in problem} (ik r - 1) e^{ikr} / r^3 (aw_j . (y_j - x)) mu_j
@@ -107,7 +107,7 @@ hipError_t launch_nearfield(qax_problem* p, const double* mu, int nrhs, const do
   if (e != hipSuccess) return e;
   const int64_t count = M * nrhs;
   hipLaunchKernelGGL(reduce_slots_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0,
-                     p->stream, (const double2*)partial, slots, count, (double2*)u, 0);
+                     p->stream, (const double2*)partial, slots, count, (const double2*)nullptr, (double2*)u);
   return hipGetLastError();
 }
 

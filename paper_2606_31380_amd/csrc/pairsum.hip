@@ -381,12 +381,12 @@ __global__ __launch_bounds__(TPB) void pair_sum_f32_kernel(
   }
 }
 
-// out[e] = (accumulate ? out[e] : 0) + sum_s partial[s][e], fixed order.
+// out[e] = (base ? base[e] : 0) + sum_s partial[s][e], fixed order (base may be out).
 __global__ void reduce_slots_kernel(const double2* __restrict__ partial, int slots, int64_t count,
-                                    double2* __restrict__ out, int accumulate) {
+                                    const double2* base, double2* out) {
   int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= count) return;
-  double2 acc = accumulate ? out[e] : make_double2(0.0, 0.0);
+  double2 acc = base ? base[e] : make_double2(0.0, 0.0);
   for (int s = 0; s < slots; ++s) {
     const double2 v = partial[(int64_t)s * count + e];
     acc.x += v.x;
@@ -965,11 +965,11 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(4))) void p
 // out[n] (+)= the slots of n's block in this launch.  A workgroup takes 64
 // consecutive nodes; wavefront w adds the list entries w, w + 4, ... of each
 // node, and the four sums are added in wavefront order (a fixed order).
-// mode 0: out = sum, 1: out += sum.
+// out = (base ? base : 0) + the sums; base may be out.
 __global__ __launch_bounds__(256) void reduce_sym_kernel(
     const double2* __restrict__ part, const int32_t* __restrict__ node_block,
     const SymBlock* __restrict__ blocks, const int64_t* __restrict__ lptr,
-    const int64_t* __restrict__ list, int64_t N, double2* __restrict__ out, int mode) {
+    const int64_t* __restrict__ list, int64_t N, const double2* base, double2* out) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t n = (int64_t)blockIdx.x * 64 + lane;
   __shared__ double2 red[4][64];
@@ -989,8 +989,8 @@ __global__ __launch_bounds__(256) void reduce_sym_kernel(
   }
   red[w][lane] = acc;
   __syncthreads();
-  if (w == 0 && n < N && (mode == 0 || e1 > e0)) {
-    double2 o = mode ? out[n] : make_double2(0.0, 0.0);
+  if (w == 0 && n < N && (base != out || e1 > e0)) {
+    double2 o = base ? base[n] : make_double2(0.0, 0.0);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       o.x += red[q][lane].x;
@@ -1006,7 +1006,7 @@ __global__ __launch_bounds__(256) void reduce_sym_kernel(
 __global__ __launch_bounds__(256) void reduce_sym32_kernel(
     const float4* __restrict__ part, const int32_t* __restrict__ node_block,
     const SymBlock* __restrict__ blocks, const int64_t* __restrict__ lptr,
-    const int64_t* __restrict__ list, int64_t N, double2* __restrict__ out, int mode) {
+    const int64_t* __restrict__ list, int64_t N, const double2* base, double2* out) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t n = (int64_t)blockIdx.x * 128 + 2 * lane;
   __shared__ double4 red[4][64];
@@ -1028,9 +1028,9 @@ __global__ __launch_bounds__(256) void reduce_sym32_kernel(
   }
   red[w][lane] = acc;
   __syncthreads();
-  if (w == 0 && n < N && (mode == 0 || e1 > e0)) {
-    double2 o0 = mode ? out[n] : make_double2(0.0, 0.0);
-    double2 o1 = mode ? out[n + 1] : make_double2(0.0, 0.0);
+  if (w == 0 && n < N && (base != out || e1 > e0)) {
+    double2 o0 = base ? base[n] : make_double2(0.0, 0.0);
+    double2 o1 = base ? base[n + 1] : make_double2(0.0, 0.0);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       o0.x += red[q][lane].x;
@@ -1149,14 +1149,15 @@ static void plan_sym_supers(qax_problem* p, int pi, int s, int64_t cap, int cu_c
   for (int64_t i : ord) sorted.push_back(P.supers[i]);
   P.supers.swap(sorted);
   // Few block pairs leave the chip idle (one takes 77 us in FP64 and 45 in
-  // FP32, whatever their number): below eight workgroups per compute unit each
-  // pair is split into 2, 4 or 8 parts by its sources, which write a target slot
+  // FP32, whatever their number): below 16 workgroups per compute unit each pair
+  // is split into 2, 4 or 8 parts by its sources, which write a target slot
   // each and share the source slot.  Calls at N = 1600: 92.7 -> 30.2 us (FP32 63 -> 26);
-  // N = 5568: 101.6 -> 64.1 (66.4 -> 46.3); N = 11,936: 212 -> 182 (121 -> 106);
-  // N = 23,712 (4371 pairs): 625 -> 625 with 2 parts, 727 with 8, so not split.
+  // N = 5568: 101.6 -> 64.1 (66.4 -> 46.3); N = 11,936: 212 -> 180 (121 -> 111);
+  // six problems with 2990 pairs in all: 323 -> 282; N = 23,712 (4371 pairs):
+  // 625 -> 625 with 2 parts, 727 with 8, so not split.
   int parts = 1;
   if (s == 1)
-    while (parts < 8 && (int64_t)P.supers.size() * parts < 8LL * cu_count) parts *= 2;
+    while (parts < 8 && (int64_t)P.supers.size() * parts < 16LL * cu_count) parts *= 2;
   if (parts > 1) {
     std::vector<SymSuper> split;
     for (const SymSuper& T : P.supers)
@@ -1534,8 +1535,8 @@ hipError_t ensure_pair_plan(qax_problem* p, int prec, int nrhs) {
   return e == hipSuccess ? ensure_mm_plan(p, std::max(cus, 1)) : e;
 }
 
-// partial: slots x N x nrhs complex128 workspace; out = pair sum, or
-// out += pair sum when accumulate is set.  The workgroup size is the one the
+// partial: slots x N x nrhs complex128 workspace; out = pair sum, plus base
+// unless that is null (base may be out).  The workgroup size is the one the
 // task table was planned with; right-hand sides per pass from the tuning
 // (clamped to a supported configuration).
 size_t pair_work_bytes(const qax_problem* p, int prec, int nrhs) {
@@ -1553,12 +1554,16 @@ static bool use_sym(const qax_problem* p, int prec, int nrhs) {
 }
 
 hipError_t launch_pair_sum(qax_problem* p, int prec, const double* mu, double* out, int nrhs,
-                           double* partial, bool accumulate) {
+                           double* partial, const double* base) {
   if (p->lat.active) {
     // regular array of identical bodies: block-Toeplitz apply
     const int kind = prec == QAX_FP64 ? QAX_K_PAIRSUM_FP64 : QAX_K_PAIRSUM_FP32;
+    hipError_t e = hipSuccess;
+    if (base && base != out)
+      e = hipMemcpyAsync(out, base, (size_t)p->N * nrhs * 16, hipMemcpyDeviceToDevice, p->stream);
+    if (e != hipSuccess) return e;
     timing_begin(p, kind);
-    hipError_t e = launch_lattice_apply(p, prec, mu, out, nrhs, partial, accumulate);
+    e = launch_lattice_apply(p, prec, mu, out, nrhs, partial, base != nullptr);
     timing_end(p, kind);
     return e;
   }
@@ -1603,15 +1608,15 @@ hipError_t launch_pair_sum(qax_problem* p, int prec, const double* mu, double* o
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
       }
-      const int mode = l == 0 ? (accumulate ? 1 : 0) : 1;
+      const double2* from = l == 0 ? (const double2*)base : (const double2*)out;
       if (f64)
         hipLaunchKernelGGL(reduce_sym_kernel, rgrid, dim3(256), 0, p->stream, (const double2*)part,
                            S.d_node_block, S.d_blocks, P.d_lptr + (size_t)l * (nblk + 1), P.d_list, p->N,
-                           (double2*)out, mode);
+                           from, (double2*)out);
       else
         hipLaunchKernelGGL(reduce_sym32_kernel, dim3((unsigned)((p->N + 127) / 128)), dim3(256), 0, p->stream,
                            (const float4*)partial, S.d_node_block, S.d_blocks, P.d_lptr + (size_t)l * (nblk + 1),
-                           P.d_list, p->N, (double2*)out, mode);
+                           P.d_list, p->N, from, (double2*)out);
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
@@ -1625,7 +1630,7 @@ hipError_t launch_pair_sum(qax_problem* p, int prec, const double* mu, double* o
     if (e != hipSuccess) return e;
     const int64_t count = p->N * nrhs;
     hipLaunchKernelGGL(reduce_slots_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, p->stream,
-                       (const double2*)partial, p->mm.slots, count, (double2*)out, accumulate ? 1 : 0);
+                       (const double2*)partial, p->mm.slots, count, (const double2*)base, (double2*)out);
     return hipGetLastError();
   }
   const int tpb = p->tune.pair_tpb[pi];
@@ -1644,8 +1649,7 @@ hipError_t launch_pair_sum(qax_problem* p, int prec, const double* mu, double* o
   const int slots = prec == QAX_FP64 ? p->slots64 : p->slots32;
   const int64_t count = p->N * nrhs;
   hipLaunchKernelGGL(reduce_slots_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0,
-                     p->stream, (const double2*)partial, slots, count, (double2*)out,
-                     accumulate ? 1 : 0);
+                     p->stream, (const double2*)partial, slots, count, (const double2*)base, (double2*)out);
   return hipGetLastError();
 }
 
