@@ -239,9 +239,10 @@ def rooflines(ktimes, scen, P, factor_fp64, steps, applies):
     g = np.where(npan >= 2, 48.0, 64.0)
     self_flop = float(np.sum(rows_frac * nb * ((2 * g + g * adj) * per_node + (1 + adj) * per_item)))
     # inversion: 8 m^3 per matrix of order m inverted; a trailing update of
-    # the 128 columns at k0 is 8 m (m - w) w, w = min(128, m - k0), and the
-    # dispatches are one per 128 columns of the largest matrix of each batch
-    # (symmetric reduced blocks, other blocks)
+    # the p columns at k0 (p = 64 in FP64, on the diagonal; 128 in FP32) is
+    # 8 m (m - w) w, w = min(p, m - k0), and the dispatches are one per p
+    # columns of the largest matrix of each batch (symmetric reduced blocks,
+    # other blocks)
     half = npan * 16 / 2
     orders, batches = [], [[], []]
     for i in range(len(nb)):
@@ -249,13 +250,14 @@ def rooflines(ktimes, scen, P, factor_fp64, steps, applies):
         orders += ms
         batches[0 if sym[i] else 1] += ms
     orders = np.array(orders)
+    panel = 64 if factor_fp64 else 128
     inv_flop = float(np.sum(8.0 * orders ** 3))
     upd_tot = 0.0
     for m in orders:
-        for k0 in np.arange(0, m, 128):
-            w = min(128.0, m - k0)
+        for k0 in np.arange(0, m, panel):
+            w = min(float(panel), m - k0)
             upd_tot += 8.0 * m * (m - w) * w
-    upd_disp = sum(int(np.ceil(max(b) / 128)) for b in batches if b)
+    upd_disp = sum(int(np.ceil(max(b) / panel)) for b in batches if b)
     upd_flop = float(upd_tot / max(upd_disp, 1))
     # the FP32 block apply is the preconditioner's: when every body is
     # mirror-symmetric it reads the four reduced inverses of each body

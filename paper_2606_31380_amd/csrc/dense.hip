@@ -10,7 +10,8 @@
 // input slice comes from L2.  FP32 storage is accumulated in FP64.
 //
 // Inversion: blocked Gauss-Jordan elimination with partial pivoting, in place,
-// batched over matrices of different orders (see gj_invert).
+// batched over matrices of different orders (see gj_invert); the self blocks
+// first by elimination on the diagonal (see gjd_invert).
 #include <hip/hip_runtime.h>
 
 #include "fastmath.h"
@@ -1193,6 +1194,331 @@ static void gj_factor_panel(hipStream_t s, typename Cx<T>::V* pool, const MatDes
   launch_half_update<T>(s, pool, d_mats, batch, nmax, c0 + h, h, c0, Wn, rows_blocks);
 }
 
+// ---------------------------------------------------------------- elimination on the diagonal
+// Gauss-Jordan elimination in FP64 whose pivots stay on the diagonal, by
+// panels of GJD columns, for matrices that need no interchanges: the self
+// blocks 1/2 I + D (- i eta S).  Per panel two launches: G = [-A_ip D^-1;
+// D^-1] with the inverse D^-1 of the panel's diagonal block (the panel rows
+// copied to W meanwhile), then A <- (panel rows ? 0 : A) + G W, where the
+// workgroups of the next diagonal block go on to invert it.  The recursive
+// panels above take 62 launches per 64 columns, their leaves one workgroup per
+// matrix, column by column down the whole matrix.  108 reduced blocks of
+// orders 528 and 496: 6.1 -> 3.3 ms; two blocks of order 2304: 25 -> 5.1 ms
+// (41-48 TFLOP/s in the updates, bound by the matrix cores, by whole tiles
+// over the chip's places and by the load and store around 64 columns' work).
+//
+// bad[0], bad[1] are set where elimination on the diagonal may lose digits:
+// a multiplier beyond 4 within a diagonal block, a 2 x 2 pivot block whose
+// determinant cancels (a diagonal product beyond 8 times it), an entry of G
+// beyond 8, or anything not finite; the caller then inverts again with
+// interchanges.  Over spheroids, peanuts, quasi-ellipsoids, conches and spirals
+// at k = 0.5 to 20 the largest entry of G is 0.03 to 9 for 1/2 I + D on
+// resolved bodies and 0.05 to 0.4 with - i eta S, the inverses agreeing with
+// LAPACK's to 3e-15; a sphere at k = 20 on 16 azimuths (G to 23) and the
+// single layer (G to 2000) take the interchanges.
+constexpr int GJD = 64;
+
+// The inverse of the block [k0, k0 + 64) x [k0, k0 + 64) of a matrix (padded
+// with the identity) to D, Gauss-Jordan in registers by pivot blocks of 2 x 2:
+// thread (ty, tx) of 16 x 16 holds rows ty + 16 r and columns tx + 16 c;
+// the two pivot rows and columns exchanged through LDS (lds: 2 x 4 x 64) per step.
+__device__ __forceinline__ void gjd_diag(const double2* A, int n, int k0, double2* __restrict__ D,
+                                         double2 (*lds)[4][GJD], int* __restrict__ bad) {
+  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+  auto mul = [](double2 u, double2 v) {
+    return make_double2(fma(u.x, v.x, -u.y * v.y), fma(u.x, v.y, u.y * v.x));
+  };
+  auto mac = [](double2 s, double2 u, double2 v) {
+    return make_double2(fma(u.x, v.x, fma(-u.y, v.y, s.x)), fma(u.x, v.y, fma(u.y, v.x, s.y)));
+  };
+  auto neg = [](double2 u) { return make_double2(-u.x, -u.y); };
+  auto norm = [](double2 u) { return fma(u.x, u.x, u.y * u.y); };
+  double2 x[4][4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int i = k0 + ty + 16 * r, j = k0 + tx + 16 * c;
+      const double2 v = A[(int64_t)min(i, n - 1) * n + min(j, n - 1)];
+      x[r][c] = i < n && j < n ? v : make_double2(i == j ? 1.0 : 0.0, 0.0);
+    }
+  bool fail = false;
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+#pragma unroll 1
+    for (int t = 0; t < 16; t += 2) {
+      double2 (*row)[GJD] = lds[t / 2 & 1], (*col)[GJD] = row + 2;
+      const bool own_r = (ty & ~1) == t, own_c = (tx & ~1) == t;
+      if (own_r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) row[ty & 1][tx + 16 * c] = x[g][c];
+      if (own_c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) col[tx & 1][ty + 16 * r] = x[r][g];
+      __syncthreads();
+      const int k = 16 * g + t;
+      const double2 p00 = row[0][k], p01 = row[0][k + 1], p10 = row[1][k], p11 = row[1][k + 1];
+      const double2 dd = mul(p00, p11), det = mac(dd, neg(p01), p10);
+      const double dn = norm(det), rd = 1.0 / dn;
+      const double2 id = make_double2(det.x * rd, -det.y * rd);
+      const double2 q00 = mul(p11, id), q01 = mul(neg(p01), id), q10 = mul(neg(p10), id), q11 = mul(p00, id);
+      double2 m0[4], m1[4];            // the multipliers of this thread's rows; of a pivot row, Pinv's row
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const double2 f0 = neg(col[0][ty + 16 * r]), f1 = neg(col[1][ty + 16 * r]);
+        m0[r] = mac(mul(f0, q00), f1, q10);
+        m1[r] = mac(mul(f0, q01), f1, q11);
+        if (!(fmax(norm(m0[r]), norm(m1[r])) <= 16.0) && ty + 16 * r > k + 1) fail = true;
+      }
+      if (!(dn > 0.0 && dn < 1e300 && norm(dd) <= 64.0 * dn)) fail = true;
+      if (own_r) {
+        m0[g] = ty & 1 ? q10 : q00;
+        m1[g] = ty & 1 ? q11 : q01;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) x[g][c] = make_double2(0.0, 0.0);
+      }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const double2 r0 = row[0][tx + 16 * c], r1 = row[1][tx + 16 * c];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r][c] = mac(mac(x[r][c], m0[r], r0), m1[r], r1);
+      }
+      if (own_c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r][g] = tx & 1 ? m1[r] : m0[r];
+    }
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) D[(ty + 16 * r) * GJD + tx + 16 * c] = x[r][c];
+  if (fail) atomicOr(bad, 1);
+}
+
+__global__ __launch_bounds__(256) void gjd_first_kernel(const MatDesc* __restrict__ mats,
+                                                        const double2* __restrict__ pool,
+                                                        double2* __restrict__ dinv, int* __restrict__ bad) {
+  __shared__ double2 lds[2][4][GJD];
+  const MatDesc M = mats[blockIdx.x];
+  gjd_diag(pool + M.elem_off, M.n, 0, dinv + (int64_t)blockIdx.x * GJD * GJD, lds, bad);
+}
+
+// Tiles of 64 x 64 complex products on v_mfma_f64_16x16x4f64, as the trailing
+// update below the recursive panels (As, Bs, the operand order).
+// UPDATE 0, grid (2 tiles, batch): the first tiles blocks of a matrix G rows
+// [64 x, 64 x + 64) = panel rows ? D^-1 rows : -A[:, panel] D^-1; the others 64
+// columns of the panel rows copied to W.
+// UPDATE 1, grid tiles^2 batch: tile (it, jt) of A <- (panel rows ? 0 : A) +
+// G W, or G itself in the panel's columns.  The next panel's diagonal tiles
+// come first, and their workgroups go on to invert them while the others run
+// (35 us alone; 5-15 us here).  Each XCD takes one run of tiles, whose G and W
+// stay in its L2 (108 matrices of order ~512: 346 -> 302 us per panel).
+template <int UPDATE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void gjd_tile_kernel(
+    const MatDesc* __restrict__ mats, double2* __restrict__ pool, int k0, double2* __restrict__ G,
+    double2* __restrict__ W, double2* __restrict__ dinv, int nmax, int tiles, int batch, int* __restrict__ bad) {
+  typedef MfmaAcc<double> MA;
+  typedef MA::v4 v4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int z, it, jt;
+  bool next = false;                    // the next panel's diagonal tile
+  if (UPDATE) {
+    if (bad[0]) return;                 // some matrix needs interchanges (not written by this launch)
+    const int d = k0 / GJD + 1 < tiles ? k0 / GJD + 1 : 0;
+    int b = blockIdx.x;
+    const int first = (batch + 7) & ~7, rest = batch * (tiles * tiles - 1), per = (rest + 7) >> 3;
+    if (b < first) {
+      if (b >= batch) return;
+      z = b;
+      it = jt = d;
+      next = d != 0;
+    } else {
+      b -= first;
+      b = (b & 7) * per + (b >> 3);
+      if (b >= rest) return;
+      z = b / (tiles * tiles - 1);
+      b -= z * (tiles * tiles - 1);
+      if (b >= d * tiles + d) ++b;
+      it = b / tiles;
+      jt = b - it * tiles;
+    }
+  } else {
+    z = blockIdx.y;
+    it = blockIdx.x;
+    jt = 0;
+  }
+  const MatDesc M = mats[z];
+  const int n = M.n;
+  if (k0 >= n) return;
+  const int kend = min(k0 + GJD, n), w = kend - k0;
+  double2* A = pool + M.elem_off;
+  double2* Gm = G + (int64_t)z * nmax * GJD;
+  double2* Wm = W + (int64_t)z * nmax * GJD;
+  dinv += (int64_t)z * GJD * GJD;
+  if (!UPDATE && it >= tiles) {
+    const int j = (it - tiles) * 64 + lane;
+    if (j < n)
+#pragma unroll 4
+      for (int q = wave; q < w; q += 4) Wm[(int64_t)q * nmax + j] = A[(int64_t)(k0 + q) * n + j];
+    return;
+  }
+  const int i0 = it * 64, j0 = jt * 64;
+  if (i0 >= n || j0 >= n) return;
+  if (UPDATE ? j0 == k0 : i0 == k0) {   // the panel's columns; G's panel rows
+    for (int e = tid; e < 64 * GJD; e += 256) {
+      const int r = e >> 6, c = e & 63;
+      if (i0 + r >= n) break;
+      if (!UPDATE) Gm[(int64_t)(i0 + r) * GJD + c] = dinv[e];
+      if (UPDATE && c < w) A[(int64_t)(i0 + r) * n + k0 + c] = Gm[(int64_t)(i0 + r) * GJD + c];
+    }
+    return;
+  }
+  const double2* B = UPDATE ? Wm : dinv;
+  const int ldb = UPDATE ? nmax : GJD, jend = UPDATE ? n : GJD;
+  __shared__ __attribute__((aligned(16))) double As[64][33];
+  __shared__ __attribute__((aligned(16))) double Bs[32][136];
+  const int wr = (wave >> 1) * 32, wc = (wave & 1) * 64;
+  // 16-row and 8-column parts of this wavefront that hold entries
+  const int xs = (min(max(n - i0 - wr, 0), 32) + 15) >> 4, ys = (min(max(jend - j0 - (wc >> 1), 0), 32) + 7) >> 3;
+  // loads at indices clamped to the matrix, what lies outside it not stored;
+  // beyond the panel's end (p >= w) zeros
+  v4 acc[2][4];
+  if (UPDATE && i0 != k0) {
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const double* a = (const double*)(A + (int64_t)min(i0 + wr + 16 * x + MA::row(lane, e), n - 1) * n);
+#pragma unroll
+        for (int y = 0; y < 4; ++y) acc[x][y][e] = a[min(2 * j0 + wc + 16 * y + (lane & 15), 2 * n - 1)];
+      }
+  } else {
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int y = 0; y < 4; ++y) acc[x][y] = v4{0.0, 0.0, 0.0, 0.0};
+  }
+  const int pa = tid & 15, pw = tid >> 6;
+  const double2* ga = UPDATE ? Gm : A + k0;
+  const int lda = UPDATE ? GJD : n;
+  const double2* gb = B + min(j0 + lane, jend - 1);
+  double2 ra[4], rw[4];
+  auto load_chunk = [&](int p0) {
+    const int pc = min(p0 + pa, w - 1);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      ra[q] = ga[(int64_t)min(i0 + (tid >> 4) + 16 * q, n - 1) * lda + pc];
+      rw[q] = gb[(int64_t)min(p0 + pw + 4 * q, w - 1) * ldb];
+    }
+    if (p0 + 16 > w) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (p0 + pa >= w) ra[q] = make_double2(0.0, 0.0);
+        if (p0 + pw + 4 * q >= w) rw[q] = make_double2(0.0, 0.0);
+      }
+    }
+  };
+  load_chunk(0);
+  for (int p0 = 0; p0 < w; p0 += 16) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int rr = (tid >> 4) + 16 * q, pb = pw + 4 * q;
+      As[rr][2 * pa] = ra[q].x;
+      As[rr][2 * pa + 1] = ra[q].y;
+      *(double2*)&Bs[2 * pb][2 * lane] = rw[q];
+      *(double2*)&Bs[2 * pb + 1][2 * lane] = make_double2(-rw[q].y, rw[q].x);
+    }
+    __syncthreads();
+    if (p0 + 16 < w) load_chunk(p0 + 16);
+    if (xs == 2 && ys == 4) {
+#pragma unroll
+      for (int kk = 0; kk < 32; kk += 4) {
+        const int kr = kk + (lane >> 4), ci = lane & 15;
+        double af[2], bf[4];
+#pragma unroll
+        for (int x = 0; x < 2; ++x) af[x] = As[wr + 16 * x + ci][kr];
+#pragma unroll
+        for (int y = 0; y < 4; ++y) bf[y] = Bs[kr][wc + 16 * y + ci];
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+          for (int y = 0; y < 4; ++y) acc[x][y] = MA::mma(af[x], bf[y], acc[x][y]);
+      }
+    } else {
+#pragma unroll 1
+      for (int kk = 0; kk < 32; kk += 4) {
+        const int kr = kk + (lane >> 4), ci = lane & 15;
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+          for (int y = 0; y < 4; ++y)
+            if (x < xs && y < ys)
+              acc[x][y] = MA::mma(As[wr + 16 * x + ci][kr], Bs[kr][wc + 16 * y + ci], acc[x][y]);
+      }
+    }
+    __syncthreads();
+  }
+  bool big = false;
+  double* out = UPDATE ? (double*)A : (double*)Gm;
+  const int ldo = UPDATE ? 2 * n : 2 * GJD;
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int i = i0 + wr + 16 * x + MA::row(lane, e);
+      if (i >= n) continue;
+#pragma unroll
+      for (int y = 0; y < 4; ++y) {
+        const int c = 2 * j0 + wc + 16 * y + (lane & 15);
+        const double v = UPDATE ? acc[x][y][e] : -acc[x][y][e];
+        if (!UPDATE && !(fabs(v) <= 8.0)) big = true;
+        if (!UPDATE || c < ldo) out[(int64_t)i * ldo + c] = v;
+      }
+    }
+  if (!UPDATE && big) atomicOr(bad, 1);
+  if (UPDATE && next) {
+    __syncthreads();
+    gjd_diag(A, n, i0, dinv, (double2(*)[4][GJD]) & As[0][0], bad + 1);
+  }
+}
+
+__global__ void gjd_clear_kernel(int* bad) { bad[0] = bad[1] = 0; }
+
+// In-place inversion of `batch` FP64 matrices on the diagonal, work as
+// gj_invert's; *failed: some matrix needs interchanges (the pool then holds
+// no inverse).  Waits for the stream.
+static hipError_t gjd_invert(qax_problem* p, double2* pool, const MatDesc* d_mats, int batch, int nmax,
+                             double* work, bool* failed) {
+  if (nmax > 8192) return hipErrorInvalidValue;
+  const hipStream_t s = p->stream;
+  double2* W = (double2*)work;
+  double2* G = W + (int64_t)GJD * nmax * batch;
+  double2* dinv = G + (int64_t)GJD * nmax * batch;      // in the recursive panels' part of the workspace
+  int* bad = (int*)(dinv + (int64_t)batch * GJD * GJD);
+  const int tiles = (nmax + 63) / 64;
+  hipLaunchKernelGGL(gjd_clear_kernel, dim3(1), dim3(1), 0, s, bad);
+  int h_bad[2] = {0, 0};
+  auto check = [&]() {
+    const hipError_t e = hipMemcpyAsync(h_bad, bad, sizeof(h_bad), hipMemcpyDeviceToHost, s);
+    return e == hipSuccess ? hipStreamSynchronize(s) : e;
+  };
+  hipError_t e = hipSuccess;
+  hipLaunchKernelGGL(gjd_first_kernel, dim3(batch), dim3(256), 0, s, d_mats, pool, dinv, bad);
+  for (int k0 = 0; k0 < nmax && e == hipSuccess; k0 += GJD) {
+    hipLaunchKernelGGL(gjd_tile_kernel<0>, dim3(2 * tiles, batch), dim3(256), 0, s, d_mats, pool, k0, G, W, dinv,
+                       nmax, tiles, batch, bad);
+    // matrices that need interchanges show it early, mostly in the first panel
+    if (k0 / GJD % 8 == 0 && ((e = check()) != hipSuccess || h_bad[0] || h_bad[1])) break;
+    timing_begin(p, QAX_K_INVERT_UPDATE);
+    hipLaunchKernelGGL(gjd_tile_kernel<1>, dim3(((batch + 7) & ~7) + ((batch * (tiles * tiles - 1) + 7) & ~7)), dim3(256), 0, s, d_mats, pool, k0, G, W,
+                       dinv, nmax, tiles, batch, bad);
+    timing_end(p, QAX_K_INVERT_UPDATE);
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess && !h_bad[0] && !h_bad[1]) e = check();
+  *failed = h_bad[0] || h_bad[1];
+  return e;
+}
+
 // In-place inversion of `batch` matrices of complex T (interleaved, pool in
 // units of T) described on the device by `mats` (orders up to nmax, at most
 // 8192), on p->stream.  work: see gj_work_bytes.  With timed set, the trailing
@@ -1222,6 +1548,8 @@ hipError_t gj_invert(qax_problem* p, T* pool, const MatDesc* d_mats, int batch, 
   return hipGetLastError();
 }
 
+// (the elimination on the diagonal lays out W, G, the diagonal inverses and its
+// flag in the same bytes)
 size_t gj_work_bytes(int batch, int nmax) {
   return (size_t)nmax * batch * sizeof(double2) * GJB +
          (((size_t)nmax * batch * sizeof(int32_t)) + 255) / 256 * 256 +
@@ -1594,11 +1922,25 @@ static hipError_t invert_blocks_sym(qax_problem* p, const SymInvPlan& P, char* w
     e = hipMemcpyAsync(d_plain, P.plain.data(), P.plain.size() * sizeof(MatDesc), hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return e;
   timing_begin(p, QAX_K_INVERT);
+  // FP64: on the diagonal, again with interchanges where that fails
+  auto invert = [&](typename Cx<T>::V* mats, const MatDesc* d_md, int batch, int nmax, auto&& fill) {
+    hipError_t ie = fill();
+    if (ie != hipSuccess) return ie;
+    if constexpr (sizeof(T) == 8) {
+      bool failed = false;
+      ie = gjd_invert(p, mats, d_md, batch, nmax, gjw, &failed);
+      if (ie != hipSuccess || !failed) return ie;
+      ie = fill();
+      if (ie != hipSuccess) return ie;
+    }
+    return gj_invert<T>(p, (T*)mats, d_md, batch, nmax, gjw, true);
+  };
   if (!P.red.empty()) {
-    hipLaunchKernelGGL(sym_reduce_kernel<T>, dim3((unsigned)P.rows.size()), dim3(256), 0, s, d_rows,
-                       d_desc, (const double2*)p->d_B, (typename Cx<T>::V*)pool);
-    e = hipGetLastError();
-    if (e == hipSuccess) e = gj_invert<T>(p, pool, d_red, (int)P.red.size(), P.nmax_red, gjw, true);
+    e = invert((typename Cx<T>::V*)pool, d_red, (int)P.red.size(), P.nmax_red, [&]() {
+      hipLaunchKernelGGL(sym_reduce_kernel<T>, dim3((unsigned)P.rows.size()), dim3(256), 0, s, d_rows, d_desc,
+                         (const double2*)p->d_B, (typename Cx<T>::V*)pool);
+      return hipGetLastError();
+    });
     if (e == hipSuccess) {
       hipLaunchKernelGGL(sym_expand_kernel<T>, dim3((unsigned)P.rows.size()), dim3(256), 0, s, d_rows,
                          d_desc, (const typename Cx<T>::V*)pool, inv_pool);
@@ -1606,7 +1948,15 @@ static hipError_t invert_blocks_sym(qax_problem* p, const SymInvPlan& P, char* w
     }
   }
   if (e == hipSuccess && !P.plain.empty())
-    e = gj_invert<T>(p, (T*)inv_pool, d_plain, (int)P.plain.size(), P.nmax_plain, gjw, true);
+    e = invert(inv_pool, d_plain, (int)P.plain.size(), P.nmax_plain, [&]() {
+      hipError_t fe = hipSuccess;
+      if (sizeof(T) == 8)      // (FP32: B rounded into the pool by the caller)
+        for (const MatDesc& m : P.plain)
+          if (fe == hipSuccess)
+            fe = hipMemcpyAsync(inv_pool + m.elem_off, (const double2*)p->d_B + m.elem_off, (size_t)m.n * m.n * 16,
+                                hipMemcpyDeviceToDevice, s);
+      return fe;
+    });
   timing_end(p, QAX_K_INVERT);
   return e;
 }
@@ -1654,17 +2004,6 @@ hipError_t launch_factor_blocks64(qax_problem* p, double* work) {
 hipError_t launch_invert_blocks64(qax_problem* p, double* work) {
   SymInvPlan P;
   plan_sym_inverse(p, sizeof(double2), P);
-  if (P.red.empty()) {
-    hipError_t e = hipMemcpyAsync(p->d_Binv, p->d_B, (size_t)p->block_elems * 16,
-                                  hipMemcpyDeviceToDevice, p->stream);
-    if (e != hipSuccess) return e;
-  } else {
-    for (const MatDesc& m : P.plain) {
-      hipError_t e = hipMemcpyAsync(p->d_Binv + 2 * m.elem_off, p->d_B + 2 * m.elem_off,
-                                    (size_t)m.n * m.n * 16, hipMemcpyDeviceToDevice, p->stream);
-      if (e != hipSuccess) return e;
-    }
-  }
   return invert_blocks_sym<double>(p, P, (char*)work, (double2*)p->d_Binv);
 }
 

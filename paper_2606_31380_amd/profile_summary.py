@@ -39,7 +39,7 @@ KINDS = {
     "block_apply_f32": (r"qax::(block_gemv_f32_lds_kernel<\d>|sym_seg_gemv_kernel<float, 4>)",
                         "paper_2606_31380_amd/csrc/dense.hip", False),
     "self_assembly": (r"qax::assemble_self_kernel<0>", "paper_2606_31380_amd/csrc/selfblock.hip", False),
-    "invert_update": (r"qax::gjm_update_kernel<double>", "paper_2606_31380_amd/csrc/dense.hip", True),
+    "invert_update": (r"qax::gjd_tile_kernel<1>", "paper_2606_31380_amd/csrc/dense.hip", True),
 }
 
 
