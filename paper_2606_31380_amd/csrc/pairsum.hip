@@ -1085,37 +1085,32 @@ static void plan_sym_supers(qax_problem* p, int pi, int s, int64_t cap, int cu_c
     return S.blk_body_lo[I] == S.blk_body_hi[I] && S.blk_body_lo[J] == S.blk_body_hi[J] &&
            S.blk_body_lo[I] == S.blk_body_lo[J];
   };
+  // squares by their corner and cost; the super-tasks themselves once the
+  // order is known
+  struct Corner { int32_t pr, r0, c0; };
+  std::vector<Corner> corner;
   std::vector<double> cost;
+  size_t cap_s = 0;
+  for (int pr = 0; pr < p->n_problems; ++pr) {
+    const size_t r = (S.prob_blk0[pr + 1] - S.prob_blk0[pr] + s - 1) / s;
+    cap_s += r * (r + 1) / 2;
+  }
+  corner.reserve(cap_s);
+  cost.reserve(cap_s);
   for (int pr = 0; pr < p->n_problems; ++pr) {
     const int g0 = S.prob_blk0[pr], g1 = S.prob_blk0[pr + 1];
     for (int r0 = g0; r0 < g1; r0 += s)
       for (int c0 = r0; c0 < g1; c0 += s) {
-        SymSuper T;
-        T.i0 = r0;
-        T.ni = std::min(s, g1 - r0);
-        T.j0 = c0;
-        T.nj = std::min(s, g1 - c0);
-        T.diag = r0 == c0 ? 1 : 0;
-        T.problem = pr;
-        T.k = p->k[pr];
-        T.skip = 0;
         double c = 0.0;
         int visits = 0;
-        for (int ii = 0; ii < T.ni; ++ii)
-          for (int jj = T.diag ? ii : 0; jj < T.nj; ++jj) {
-            const int I = r0 + ii, J = c0 + jj;
-            if (same_body(I, J)) {
-              T.skip |= 1ull << (ii * SYM_SMAX + jj);
-              continue;
-            }
+        for (int I = r0; I < std::min(r0 + s, g1); ++I)
+          for (int J = r0 == c0 ? I : c0; J < std::min(c0 + s, g1); ++J) {
+            if (same_body(I, J)) continue;
             ++visits;
             c += (double)S.blocks[I].n * S.blocks[J].n;
           }
         if (!visits) continue;
-        T.toff = T.soff = 0;
-        T.c0 = 0;
-        T.c1 = SYM_T;
-        P.supers.push_back(T);
+        corner.push_back(Corner{pr, r0, c0});
         cost.push_back(c);
       }
   }
@@ -1124,16 +1119,20 @@ static void plan_sym_supers(qax_problem* p, int pi, int s, int64_t cap, int cu_c
   // built by buckets of equal cost, which is the stable sort's order
   std::vector<int64_t> ord;
   {
-    std::vector<double> uniq(cost);
+    std::vector<double> uniq;
+    for (size_t i = 0; i < cost.size() && uniq.size() <= 256; ++i)
+      if ((i == 0 || cost[i] != cost[i - 1]) && std::find(uniq.begin(), uniq.end(), cost[i]) == uniq.end())
+        uniq.push_back(cost[i]);
     std::sort(uniq.begin(), uniq.end(), std::greater<double>());
-    uniq.erase(std::unique(uniq.begin(), uniq.end()), uniq.end());
     ord.reserve(cost.size());
     if (uniq.size() <= 256) {
       std::vector<int64_t> cnt(uniq.size() + 1, 0);
       std::vector<int32_t> bucket(cost.size());
       for (size_t i = 0; i < cost.size(); ++i) {
-        bucket[i] = (int32_t)(std::lower_bound(uniq.begin(), uniq.end(), cost[i], std::greater<double>()) -
-                              uniq.begin());
+        bucket[i] = i && cost[i] == cost[i - 1]
+                        ? bucket[i - 1]
+                        : (int32_t)(std::lower_bound(uniq.begin(), uniq.end(), cost[i], std::greater<double>()) -
+                                    uniq.begin());
         ++cnt[bucket[i] + 1];
       }
       for (size_t b = 1; b < cnt.size(); ++b) cnt[b] += cnt[b - 1];
@@ -1144,10 +1143,26 @@ static void plan_sym_supers(qax_problem* p, int pi, int s, int64_t cap, int cu_c
       std::stable_sort(ord.begin(), ord.end(), [&](int64_t a, int64_t b) { return cost[a] > cost[b]; });
     }
   }
-  std::vector<SymSuper> sorted;
-  sorted.reserve(ord.size());
-  for (int64_t i : ord) sorted.push_back(P.supers[i]);
-  P.supers.swap(sorted);
+  P.supers.resize(ord.size());
+  for (size_t q = 0; q < ord.size(); ++q) {
+    const Corner& C = corner[ord[q]];
+    const int g1 = S.prob_blk0[C.pr + 1];
+    SymSuper& T = P.supers[q];
+    T.i0 = C.r0;
+    T.ni = std::min(s, g1 - C.r0);
+    T.j0 = C.c0;
+    T.nj = std::min(s, g1 - C.c0);
+    T.diag = C.r0 == C.c0 ? 1 : 0;
+    T.problem = C.pr;
+    T.k = p->k[C.pr];
+    T.skip = 0;
+    for (int ii = 0; ii < T.ni; ++ii)
+      for (int jj = T.diag ? ii : 0; jj < T.nj; ++jj)
+        if (same_body(C.r0 + ii, C.c0 + jj)) T.skip |= 1ull << (ii * SYM_SMAX + jj);
+    T.toff = T.soff = 0;
+    T.c0 = 0;
+    T.c1 = SYM_T;
+  }
   // Few block pairs leave the chip idle (one takes 77 us in FP64 and 45 in
   // FP32, whatever their number): below 16 workgroups per compute unit each pair
   // is split into 2, 4 or 8 parts by its sources, which write a target slot
