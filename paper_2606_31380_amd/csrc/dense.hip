@@ -1700,12 +1700,16 @@ __global__ __launch_bounds__(256) void sym_reduce_kernel(const SymInvRow* __rest
   }
 }
 
-// B^-1 from the inverses M_c^-1: every pair of images of (o1, o2).
+// B^-1 from the inverses M_c^-1: every pair of images of (o1, o2).  Bound by
+// the writes.  Where given, Binv32 and M32 take B^-1 and M_c^-1 rounded to FP32
+// (with passes of their own over both: 27 blocks of order 2048 in 1.17 ms, here
+// 0.86, 4.7 TB/s).
 template <typename T>
 __global__ __launch_bounds__(256) void sym_expand_kernel(const SymInvRow* __restrict__ rows,
                                                          const SymInvDesc* __restrict__ descs,
                                                          const typename Cx<T>::V* __restrict__ M,
-                                                         typename Cx<T>::V* __restrict__ Binv) {
+                                                         typename Cx<T>::V* __restrict__ Binv,
+                                                         float2* __restrict__ Binv32, float2* __restrict__ M32) {
   typedef typename Cx<T>::V V;
   const SymInvRow R = rows[blockIdx.x];
   const SymInvDesc D = descs[R.blk];
@@ -1715,12 +1719,13 @@ __global__ __launch_bounds__(256) void sym_expand_kernel(const SymInvRow* __rest
   const bool fix1 = j1 == 0 || j1 == N;
   const int64_t r0 = (int64_t)R.o1 * (half * np), r1 = (int64_t)(s1 * nm + j1 - 1) * (half * nm);
   // rows of the images: [a_t][a_h] (a_h = 1 only where R_h moves the orbit)
-  V* rw[2][2];
+  int64_t rw[2][2];
   for (int at = 0; at < 2; ++at)
     for (int ah = 0; ah < 2; ++ah) {
       const int s = at ? ns - 1 - s1 : s1, j = ah ? (nth - j1) % nth : j1;
-      rw[at][ah] = Binv + D.b_off + (int64_t)(s * nth + j) * n;
+      rw[at][ah] = D.b_off + (int64_t)(s * nth + j) * n;
     }
+  auto r32 = [](V v) { return make_float2((float)v.x, (float)v.y); };
   for (int o2 = threadIdx.x; o2 < half * np; o2 += blockDim.x) {
     const int s2 = o2 / np, j2 = o2 % np;
     const bool fix2 = j2 == 0 || j2 == N;
@@ -1730,6 +1735,14 @@ __global__ __launch_bounds__(256) void sym_expand_kernel(const SymInvRow* __rest
       const int64_t c1 = s2 * nm + j2 - 1;
       m1 = M[D.m_off[1] + r1 + c1];
       m3 = M[D.m_off[3] + r1 + c1];
+      if (M32) {
+        M32[D.m_off[1] + r1 + c1] = r32(m1);
+        M32[D.m_off[3] + r1 + c1] = r32(m3);
+      }
+    }
+    if (M32) {
+      M32[D.m_off[0] + r0 + o2] = r32(m0);
+      M32[D.m_off[2] + r0 + o2] = r32(m2);
     }
     const T w = fix2 ? (T)0.5 : (T)0.25;
     // same t image (p_t = +1): m0 + m2 +- (m1 + m3); other: m0 - m2 +- (m1 - m3)
@@ -1745,7 +1758,10 @@ __global__ __launch_bounds__(256) void sym_expand_kernel(const SymInvRow* __rest
           const V a = at == bt ? ap : am, c = at == bt ? cp : cm;
           for (int bh = 0; bh < (fix2 ? 1 : 2); ++bh) {
             const T sg = ah == bh ? (T)1 : (T)-1;
-            rw[at][ah][col[bt] + jj[bh]] = Cx<T>::make(a.x + sg * c.x, a.y + sg * c.y);
+            const V v = Cx<T>::make(a.x + sg * c.x, a.y + sg * c.y);
+            const int64_t at_ = rw[at][ah] + col[bt] + jj[bh];
+            Binv[at_] = v;
+            if (Binv32) Binv32[at_] = r32(v);
           }
         }
   }
@@ -1895,13 +1911,27 @@ static void launch_sym_apply(qax_problem* p, int prec, const double* v, double* 
                      (const double2*)A.d_w, (double2*)out, accumulate ? 1 : 0, p->seg_active);
 }
 
+// f(complex offset, complex elements) over the runs of blocks inverted as they
+// are, adjacent ones together.
+template <typename F>
+static hipError_t plain_runs(const SymInvPlan& P, F f) {
+  hipError_t e = hipSuccess;
+  for (size_t i = 0; i < P.plain.size() && e == hipSuccess;) {
+    const int64_t off = P.plain[i].elem_off;
+    int64_t end = off;
+    for (; i < P.plain.size() && P.plain[i].elem_off == end; ++i) end += (int64_t)P.plain[i].n * P.plain[i].n;
+    e = f(off, end - off);
+  }
+  return e;
+}
+
 // Symmetric blocks: B -> M_c (reduced pool), inverted there, B^-1 (FP64 into
 // d_Binv, FP32 into d_Binv32); the others inverted in place in the inverse
 // pool of their precision.  The inverse pool of a non-symmetric block holds
 // a copy of B (FP64) or B rounded to FP32 on entry.
 template <typename T>
 static hipError_t invert_blocks_sym(qax_problem* p, const SymInvPlan& P, char* work,
-                                    typename Cx<T>::V* inv_pool) {
+                                    typename Cx<T>::V* inv_pool, float2* inv32 = nullptr, float2* red32 = nullptr) {
   const hipStream_t s = p->stream;
   MatDesc* d_red = (MatDesc*)(work + P.off_red);
   MatDesc* d_plain = (MatDesc*)(work + P.off_plain);
@@ -1943,19 +1973,17 @@ static hipError_t invert_blocks_sym(qax_problem* p, const SymInvPlan& P, char* w
     });
     if (e == hipSuccess) {
       hipLaunchKernelGGL(sym_expand_kernel<T>, dim3((unsigned)P.rows.size()), dim3(256), 0, s, d_rows,
-                         d_desc, (const typename Cx<T>::V*)pool, inv_pool);
+                         d_desc, (const typename Cx<T>::V*)pool, inv_pool, inv32, red32);
       e = hipGetLastError();
     }
   }
   if (e == hipSuccess && !P.plain.empty())
     e = invert(inv_pool, d_plain, (int)P.plain.size(), P.nmax_plain, [&]() {
-      hipError_t fe = hipSuccess;
-      if (sizeof(T) == 8)      // (FP32: B rounded into the pool by the caller)
-        for (const MatDesc& m : P.plain)
-          if (fe == hipSuccess)
-            fe = hipMemcpyAsync(inv_pool + m.elem_off, (const double2*)p->d_B + m.elem_off, (size_t)m.n * m.n * 16,
-                                hipMemcpyDeviceToDevice, s);
-      return fe;
+      if (sizeof(T) == 4) return hipSuccess;      // (B rounded into the pool by the caller)
+      return plain_runs(P, [&](int64_t off, int64_t elems) {
+        return hipMemcpyAsync(inv_pool + off, (const double2*)p->d_B + off, (size_t)elems * 16,
+                              hipMemcpyDeviceToDevice, s);
+      });
     });
   timing_end(p, QAX_K_INVERT);
   return e;
@@ -1987,16 +2015,16 @@ hipError_t launch_invert_blocks(qax_problem* p, double* work) {
 // Factorisation in FP64 for both paths: the FP64 inverse (below), then B^-1
 // rounded to FP32 for the mixed path.
 hipError_t launch_factor_blocks64(qax_problem* p, double* work) {
-  hipError_t e = launch_invert_blocks64(p, work);
-  if (e != hipSuccess) return e;
-  if (p->symap.on) {
-    e = launch_convert_f32(p->stream, p->symap.d_Minv, p->symap.d_Minv32, 2 * p->symap.elems);
-    if (e != hipSuccess) return e;
-  }
-  // B^-1 rounded to FP32 (the mixed path's preconditioner); B itself on
-  // first use (ensure_b32)
+  // B itself in FP32 on first use (ensure_b32)
   p->b32_ready = false;
-  return launch_convert_f32(p->stream, p->d_Binv, (float*)p->d_Binv32, 2 * p->block_elems);
+  SymInvPlan P;
+  plan_sym_inverse(p, sizeof(double2), P);
+  hipError_t e = invert_blocks_sym<double>(p, P, (char*)work, (double2*)p->d_Binv, (float2*)p->d_Binv32,
+                                           p->symap.on ? (float2*)p->symap.d_Minv32 : nullptr);
+  if (e != hipSuccess) return e;
+  return plain_runs(P, [&](int64_t off, int64_t elems) {
+    return launch_convert_f32(p->stream, p->d_Binv + 2 * off, p->d_Binv32 + 2 * off, 2 * elems);
+  });
 }
 
 // FP64 inverse: symmetric blocks through their four reduced blocks, the
