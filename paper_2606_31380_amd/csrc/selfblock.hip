@@ -15,8 +15,8 @@
 //    stable, Miller's backward recurrence normalised by Q_{-1/2} = mu K(mu)
 //    otherwise; K and E by the arithmetic-geometric mean), Q' by dleg_recur,
 //    static derivative modes, the smooth factors F = cos k rho + k rho sin k rho
-//    and Hs = (k rho cos k rho - sin k rho)/(4 pi rho^3) sampled on 128 azimuths
-//    and transformed by FFT in LDS, the convolution of F^ with the static modes
+//    and Hs = (k rho cos k rho - sin k rho)/(4 pi rho^3), even in the azimuth, sampled at
+//    64 of 128 midpoints and cosine-transformed in LDS, the convolution of F^ with the static modes
 //    and the shift to the theta frame;
 //  * direct route otherwise: trapezoidal rule on L = 128 or 256 azimuths
 //    (chosen from the decay rate acosh(chi) of the modes so that aliasing stays
@@ -33,7 +33,17 @@
 // about 1e-13.  Geometry near the target uses cancellation-free differences of
 // the generating curve (chi - 1 keeps full relative accuracy).
 //
-// One wavefront (64 lanes) per (target row, panel) work item.
+// One wavefront (64 lanes) per (target row, panel) work item.  Bound by the
+// latency of its LDS round trips and FP64 chains: half of the issue slots are
+// filled with two wavefronts per SIMD, which the LDS (19 KB: the recurrence in
+// batches of QB nodes, the final transform in halves of RH functions) and 256
+// registers (some spilled, outside the node loops) allow; with one (34 KB, 444
+// registers, 32 nodes a batch) the 27-body lattice took 5.76 ms, with two
+// 5.10.  Fewer instructions per node gave the rest: what each node needs
+// computed once by its lane, the even smooth factors on half the azimuths and
+// a transform of half the length, sines and cosines from the twiddle table,
+// the recurrence's normalisation as a factor, static modes stored for both
+// signs: 3.86 ms (a spiral and a conch of 2304 nodes 3.51 -> 2.32).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -50,7 +60,8 @@ constexpr int LM = 128;                       // modal FFT length
 constexpr int NF_CAP = 48;                    // largest convolution half-width
 constexpr int NTH_MAX = 64;                   // largest n_theta
 constexpr int MQ_CAP = NTH_MAX / 2 + 2 + NF_CAP;   // highest Q index kept (82)
-constexpr int QB = 32;                        // nodes per recurrence batch
+constexpr int QB = 11;                        // nodes per recurrence batch
+constexpr int RH = GL_ORDER / 2;              // rows of the final inverse DFT at a time
 constexpr int LD = 256;                       // direct-route azimuthal samples (FFT length)
 // outer Gauss-Legendre order per side of the target: 48 on two or more
 // uniform panels (self-block entries converged to ~1e-14 there), 64 on a
@@ -69,36 +80,38 @@ struct NodeLoc {
 // CF: the single-layer arrays are only sized for the combined-field kernel.
 template <bool CF>
 struct ModalScratch {
-  double2 fa[LM];
-  double2 fb[LM];
+  double2 f[CF ? 3 : 2][LM / 2];   // samples, then transforms: (F, Hs), (Hr, CF: cos k rho),
+                                   // CF: sin(k rho) / (4 pi rho)
   double Fh[LM / 2];
   double Hrh[NTH_MAX / 2 + 2];
   double Hh[NTH_MAX / 2 + 2];
-  double2 AB0[MQ_CAP + 1];      // static modes (dr, dz) of the kernel, n = 0..nmax+nf
+  double2 AB0[NF_CAP + MQ_CAP + 1];   // static modes (dr, dz) of the kernel, n = -nf..nmax+nf,
+                                      // at NF_CAP + n (even in n)
   double2 Am[NTH_MAX / 2 + 2];
   double2 Bm[NTH_MAX / 2 + 2];
   // single layer (combined field only)
-  double2 fc[CF ? LM : 1];               // sin(k rho) / (4 pi rho) samples, then transform
   double Ch[CF ? LM / 2 : 1];            // modes of cos(k rho)
   double Sh[CF ? NTH_MAX / 2 + 2 : 1];   // modes of sin(k rho) / (4 pi rho)
-  double G0[CF ? MQ_CAP + 1 : 1];        // static modes of G
+  double G0[CF ? NF_CAP + MQ_CAP + 1 : 1];        // static modes of G
   double2 Gm[CF ? NTH_MAX / 2 + 2 : 1];  // phi-frame modes of G
 };
 
 template <bool CF>
 struct SelfShared {
-  union {
-    double Q[QB][MQ_CAP + 1];     // toroidal functions of one recurrence batch, node-major
-                                  // (odd row stride: conflict-free rows and columns)
-    double2 acc[GL_ORDER][64];    // accumulated modes (final inverse DFT)
-  };
   double2 tw[LD + LD / 16];     // e^{-2 pi i q / LD} at twi(q) (FFT twiddles, azimuth table)
   double2 tw2n[NTH_MAX];        // e^{i pi m / N}
   int modal_idx[64];
   union {
-    ModalScratch<CF> m;
-    double2 K[CF ? 2 : 1][LD];   // direct-route samples: double layer (, single layer)
-  } u;
+    struct {
+      double Q[QB][MQ_CAP + 1];   // toroidal functions of one recurrence batch, node-major
+                                  // (odd row stride: conflict-free rows and columns)
+      union {
+        ModalScratch<CF> m;
+        double2 K[CF ? 2 : 1][LD];   // direct-route samples: double layer (, single layer)
+      } u;
+    };
+    double2 acc[RH][64];          // accumulated modes (final inverse DFT)
+  };
 };
 
 // ---------------------------------------------------------------- elliptic / Q
@@ -200,9 +213,26 @@ constexpr QRecTables make_qrec() {
 }
 __constant__ QRecTables qrec = make_qrec();
 
-// Q[col][n] = Q_{n-1/2}(chi), n = 0..mq, for the node of each lane with `act`
-// (one batch of nodes, one node per lane).  Starting values Q_{-1/2} = mu K,
-// Q_{1/2} = chi mu K - sqrt(2 (chi + 1)) E (K, E of modulus mu by the AGM).
+// Starting values of the recurrence for the node of each lane: Q_{-1/2} = mu K,
+// Q_{1/2} = chi mu K - sqrt(2 (chi + 1)) E (K, E of modulus mu by the AGM), and
+// acosh(chi).
+struct QStart {
+  double q0, q1, acosh;
+};
+__device__ __forceinline__ QStart toroidal_start(double chi, double chim1) {
+  const double mu = sqrt(2.0 / (chi + 1.0));
+  const double mup = sqrt(chim1 / (chi + 1.0));
+  double K, E;
+  agm_ke(mu, mup, K, E);
+  QStart q;
+  q.q0 = mu * K;
+  q.q1 = chi * mu * K - sqrt(2.0 * (chi + 1.0)) * E;
+  q.acosh = log(chi + sqrt(chim1 * (chi + 1.0)));
+  return q;
+}
+
+// scale * Q[col][n] = Q_{n-1/2}(chi), n = 0..mq, for the node of each lane with
+// `act` (one batch of nodes, one node per lane; returns scale).
 // Where m acosh(chi) stays small the recurrence leg_recur runs forward; else
 // Miller's backward recurrence from one common start index for the batch
 // (20 / acosh(chi) + 10 beyond mq for the slowest-decaying lane, which only
@@ -211,27 +241,17 @@ __constant__ QRecTables qrec = make_qrec();
 // is stored yet), normalised by Q_{-1/2}.  One dependent fma per step: the
 // coefficients come from qrec and the older term's product is formed a step
 // ahead.
-__device__ __forceinline__ void toroidal_q_batch(bool act, double chi, double chim1, int mq,
-                                                 double (*Q)[MQ_CAP + 1], int col) {
-  if (!act) {
-    chi = 2.0;
-    chim1 = 1.0;
-  }
-  const double mu = sqrt(2.0 / (chi + 1.0));
-  const double mup = sqrt(chim1 / (chi + 1.0));
-  double K, E;
-  agm_ke(mu, mup, K, E);
-  const double q0 = mu * K;
-  const double q1 = chi * mu * K - sqrt(2.0 * (chi + 1.0)) * E;
-  const double a = log(chi + sqrt(chim1 * (chi + 1.0)));   // acosh(chi)
-  const bool fwd = act && a * (mq + 1) <= 2.5;
+__device__ __forceinline__ double toroidal_q_batch(bool act, double chi, const QStart& q, int mq,
+                                                   double (*Q)[MQ_CAP + 1], int col) {
+  const bool fwd = act && q.acosh * (mq + 1) <= 2.5;
   const bool bwd = act && !fwd;
+  double scale = 1.0;
   if (__ballot(fwd)) {
     if (fwd) {
-      Q[col][0] = q0;
-      Q[col][1] = q1;
+      Q[col][0] = q.q0;
+      Q[col][1] = q.q1;
     }
-    double qm = q0, qn = q1;
+    double qm = q.q0, qn = q.q1;
     const double2* tf = qrec.f;
 #pragma unroll 4
     for (int n = 1; n < mq; ++n) {
@@ -242,7 +262,7 @@ __device__ __forceinline__ void toroidal_q_batch(bool act, double chi, double ch
       qn = qp;
     }
   }
-  int start = bwd ? mq + (int)ceil(20.0 / a) + 10 : 0;
+  int start = bwd ? mq + (int)ceil(20.0 / q.acosh) + 10 : 0;
   start = __builtin_amdgcn_readfirstlane(min(wave_max_int(start), QREC_MAX));
   if (start > 0) {
     double hi = 0.0, lo = 1e-200;
@@ -267,20 +287,39 @@ __device__ __forceinline__ void toroidal_q_batch(bool act, double chi, double ch
       }
     }
     for (; n > mq; --n) step(tb[n]);
+#pragma unroll 4
     for (; n >= 1; --n) {
       if (bwd) Q[col][n] = lo;
       step(tb[n]);
     }
     if (bwd) {
-      const double scale = q0 / lo;
-      Q[col][0] = q0;
-      for (int m = 1; m <= mq; ++m) Q[col][m] *= scale;
+      Q[col][0] = lo;
+      scale = q.q0 / lo;
     }
   }
+  return scale;
 }
 
 // position of twiddle q in the padded table (see below)
 __device__ __forceinline__ int twi(int q) { return q + (q >> 4); }
+
+// sin and cos of 2 pi t from the twiddle table (tw[twi(q)] = e^{-2 pi i q /
+// LD}): the nearest entry turned by the remainder |g| <= 1/512, whose series
+// end below 1e-19.
+__device__ __forceinline__ void sincos_tw(double t, const double2* tw, double* sp, double* cp) {
+  const double n = rint(t * LD);
+  const double g = fma(n, -1.0 / LD, t);
+  const double2 e = tw[twi((int)n & (LD - 1))];
+  const double g2 = g * g;
+  // sin 2 pi g, cos 2 pi g - 1
+  double s = fma(g2, -76.70585975306139, 81.60524927607506);
+  s = fma(s, g2, -41.34170224039976);
+  s = g * fma(s, g2, 6.283185307179586);
+  double c = fma(g2, -85.45681720669373, 64.9393940226683);
+  c = g2 * fma(c, g2, -19.739208802178716);
+  *cp = e.x + fma(e.x, c, e.y * s);
+  *sp = fma(e.x, s, -fma(e.y, c, e.y));
+}
 
 // ---------------------------------------------------------------- FFT in LDS
 // Forward DFT X_q = sum_l x_l e^{-2 pi i q l / L}, in place, natural order in
@@ -353,6 +392,46 @@ __device__ __forceinline__ void r2_last128(double2* x, int j, const double2* tw)
   x[j + 64] = make_double2(a0.x - a1.x, a0.y - a1.y);
 }
 
+// One radix-4 Stockham pass (as r4_pass) over the NR rows X[l][0..L) at once:
+// NR L / 4 butterflies, NR L / 256 per lane, read before the barrier, written
+// after it.
+template <int L, int Ns, int NR>
+__device__ __forceinline__ void r4_pass_rows(double2 (*X)[64], const double2* tw) {
+  constexpr int NB = L / 4, NBT = NR * NB, PER = NBT >= 64 ? NBT / 64 : 1;
+  const int lane = threadIdx.x;
+  const bool act = NBT >= 64 || lane < NBT;
+  double2 a[PER][4], w[PER][3];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int e = lane + 64 * u, row = e / NB, j = e % NB;
+    if (!act) continue;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[u][i] = X[row][j + i * NB];
+    if (Ns > 1) {
+      constexpr int step = LD / (4 * Ns);
+      const int k = j & (Ns - 1);
+#pragma unroll
+      for (int i = 1; i < 4; ++i) w[u][i - 1] = tw[twi(i * k * step)];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int e = lane + 64 * u, row = e / NB, j = e % NB;
+    if (!act) continue;
+    const int k = j & (Ns - 1);
+    if (Ns > 1) {
+#pragma unroll
+      for (int i = 1; i < 4; ++i) a[u][i] = cmul(a[u][i], w[u][i - 1]);
+    }
+    dft4(a[u][0], a[u][1], a[u][2], a[u][3]);
+    const int o = 4 * (j - k) + k;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) X[row][o + i * Ns] = a[u][i];
+  }
+  __syncthreads();
+}
+
 // Two 128-point transforms at once: lanes 0-31 take xa, lanes 32-63 take xb in
 // the radix-4 passes; every lane finishes one butterfly of each.
 __device__ void fft128x2(double2* xa, double2* xb, const double2* tw) {
@@ -419,75 +498,114 @@ __device__ __forceinline__ double smooth_h(double k, double rho, double irho, do
   return (x * cx - sx) * INV_4PI * irho * irho * irho;
 }
 
+// What the modes of one node need of it, computed once by the node's lane.
+struct ModalNode {
+  double r, rt, c, chim1;
+  double hc;             // 1 / (2 (chi^2 - 1))
+  double a1, a2, b1;     // A = a1 Q' - a2 Q, B = b1 Q' (dleg_recur)
+  double pref;           // G = pref Q (combined field only)
+};
+__device__ __forceinline__ ModalNode modal_node(double r, double rt, double c, double chim1, double rmrt) {
+  ModalNode n;
+  n.r = r;
+  n.rt = rt;
+  n.c = c;
+  n.chim1 = chim1;
+  n.pref = 1.0 / (TWO_PI * sqrt(rt * r));
+  const double ir = 1.0 / r, irt = 1.0 / rt;
+  n.hc = 0.5 / (chim1 * (chim1 + 2.0));
+  n.a1 = n.pref * ((rmrt * (r + rt) - c * c) * 0.5 * irt * ir * ir);
+  n.a2 = n.pref * 0.5 * ir;
+  n.b1 = n.pref * (-c * ir * irt);
+  return n;
+}
+
+// 2 sin^2(phi / 2) at this lane's azimuth phi = 2 pi (lane + 1/2) / LM
+__device__ __forceinline__ double lane_azimuth() {
+  double s, c;
+  sincos_cw((threadIdx.x + 0.5) * (PI / LM), &s, &c);
+  return 2.0 * s * s;
+}
+
 // phi-frame modes m = 0..nmax of A = dr G, B = dz G for one node (all lanes),
-// given its Q column.  Results in M.Am, M.Bm.
+// given its Q column times qs.  Results in M.Am, M.Bm.
+// The smooth factors are even in phi: at the LM midpoints phi = 2 pi (l + 1/2)
+// / LM they take LM / 2 values, one per lane (sh2 from lane_azimuth), and
+// their modes sum_l f cos(m phi) come from a complex transform of half the length over two
+// factors at a time: v_n = z_{2n}, v_{63-n} = z_{2n+1}, V its transform,
+// sum_l z cos(m phi) = e^{-2 pi i m / 256} V_m + e^{2 pi i m / 256} V_{-m}
+// (J. Makhoul, A fast cosine transform in one and two dimensions, 1980).
 // CF: also the modes of G itself (the single layer, Section 3.3 equations
 // conv and I1): cos(k rho) convolved with the static modes of G plus
 // i times the modes of sin(k rho) / (4 pi rho).
 template <bool CF>
-__device__ void modal_modes(double k, double r, double rt, double c, double chim1, double rmrt,
-                            int nmax, const double (*Q)[MQ_CAP + 1], int col, ModalScratch<CF>& M,
+__device__ __forceinline__ void modal_modes(double k, const ModalNode& nd, double qs, double sh2, int nmax,
+                            const double (*Q)[MQ_CAP + 1], int col, ModalScratch<CF>& M,
                             const double2* tw) {
   const int lane = threadIdx.x;
-  const double chi = 1.0 + chim1;
+  const double chim1 = nd.chim1, c = nd.c;
   int nf = 0;
   if (k != 0.0) {
-    const double k2pi = k / TWO_PI;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int l = lane + 64 * h;
-      // sin(phi/2) with phi = 2 pi l / LM from the table e^{-2 pi i q / LD}
-      const double sh = -tw[twi(l * (LD / (2 * LM)))].y;
-      const double rho2 = 2.0 * r * rt * (chim1 + 2.0 * sh * sh);
-      const double irho = rsqrt_pos(rho2);
-      const double rho = rho2 * irho;
-      double sk, ck;
-      sincos_2pi(rho * k2pi, &sk, &ck);
-      const double F = ck + k * rho * sk;
-      const double Hs = smooth_h(k, rho, irho, sk, ck);
-      const double cphi = 1.0 - 2.0 * sh * sh;
-      M.fa[l] = make_double2(F, Hs);
-      M.fb[l] = make_double2(Hs * (r - rt * cphi), CF ? ck : 0.0);
-      if constexpr (CF) {
-        const double x = k * rho;
-        // sin(x) / (4 pi rho) = (k / 4 pi) sin(x) / x
-        const double sx = x < 1e-3 ? 1.0 - x * x * (1.0 / 6.0 - x * x * (1.0 / 120.0)) : sk / x;
-        M.fc[l] = make_double2(k * INV_4PI * sx, 0.0);
-      }
+    const double rho2 = 2.0 * nd.r * nd.rt * (chim1 + sh2);
+    const double irho = rsqrt_pos(rho2);
+    const double rho = rho2 * irho;
+    double sk, ck;
+    sincos_tw(rho * (k / TWO_PI), tw, &sk, &ck);
+    const double F = fma(k * rho, sk, ck);
+    const double Hs = smooth_h(k, rho, irho, sk, ck);
+    const int pos = lane & 1 ? LM / 2 - 1 - (lane >> 1) : lane >> 1;
+    M.f[0][pos] = make_double2(F, Hs);
+    M.f[1][pos] = make_double2(Hs * fma(nd.rt, sh2 - 1.0, nd.r), CF ? ck : 0.0);
+    if constexpr (CF) {
+      const double x = k * rho;
+      // sin(x) / (4 pi rho) = (k / 4 pi) sin(x) / x
+      const double sx = x < 1e-3 ? 1.0 - x * x * (1.0 / 6.0 - x * x * (1.0 / 120.0)) : sk / x;
+      M.f[CF ? 2 : 0][pos] = make_double2(k * INV_4PI * sx, 0.0);
     }
     __syncthreads();
-    fft128x2(M.fa, M.fb, tw);
-    if constexpr (CF) fft128(M.fc, tw);
+    r4_pass_rows<LM / 2, 1, CF ? 3 : 2>(M.f, tw);
+    r4_pass_rows<LM / 2, 4, CF ? 3 : 2>(M.f, tw);
+    r4_pass_rows<LM / 2, 16, CF ? 3 : 2>(M.f, tw);
     const double sc = TWO_PI / LM;
-    M.Fh[lane] = M.fa[lane].x * sc;
-    if constexpr (CF) M.Ch[lane] = M.fb[lane].y * sc;
+    const double2 e = tw[twi(lane)];
+    const int neg = (LM / 2 - lane) & (LM / 2 - 1);
+    auto mode = [&](int row) {       // e V_m + conj(e) V_{-m}
+      const double2 u = M.f[row][lane], v = M.f[row][neg];
+      return make_double2(sc * fma(e.x, u.x + v.x, -e.y * (u.y - v.y)),
+                          sc * fma(e.x, u.y + v.y, e.y * (u.x - v.x)));
+    };
+    const double2 fh = mode(0), hr = mode(1);
+    M.Fh[lane] = fh.x;
+    if constexpr (CF) M.Ch[lane] = hr.y;
     if (lane < nmax + 1) {
-      M.Hh[lane] = M.fa[lane].y * sc;
-      M.Hrh[lane] = M.fb[lane].x * sc;
-      if constexpr (CF) M.Sh[lane] = M.fc[lane].x * sc;
+      M.Hh[lane] = fh.y;
+      M.Hrh[lane] = hr.x;
+      if constexpr (CF) M.Sh[lane] = mode(CF ? 2 : 0).x;
     }
-    const double mag = fabs(M.fa[lane].x * sc);
+    const double mag = fabs(fh.x);
     const double mx = wave_max_nonneg(mag);
     const bool above = mag > 1e-15 * mx;
     const unsigned long long bal = __ballot(above);
     nf = bal ? 63 - __clzll(bal) : 0;
     nf = min(nf + 1, NF_CAP);
     nf = min(nf, MQ_CAP - nmax - 1);
-    __syncthreads();
   }
   // static modes n = 0..nmax+nf
   const int mtot = nmax + nf;
-  const double pref = 1.0 / (TWO_PI * sqrt(rt * r));
-  const double ir = 1.0 / r, irt = 1.0 / rt;
-  const double half_inv_chi2m1 = 0.5 / (chim1 * (chi + 1.0));
-  const double drchi = (rmrt * (r + rt) - c * c) * 0.5 * irt * ir * ir;
-  const double dzchi = -c * ir * irt;
+  double2* AB0 = M.AB0 + NF_CAP;
+  double* G0 = M.G0 + (CF ? NF_CAP : 0);
+  const double chi = 1.0 + chim1, hc = nd.hc * qs, a2 = nd.a2 * qs;
   for (int n = lane; n <= mtot; n += 64) {
     const double qn = Q[col][n];
-    const double qm = n == 0 ? Q[col][1] : Q[col][n - 1];
-    const double qp = (2.0 * n - 1.0) * half_inv_chi2m1 * (chi * qn - qm);
-    M.AB0[n] = make_double2(pref * (drchi * qp - 0.5 * ir * qn), pref * dzchi * qp);
-    if constexpr (CF) M.G0[n] = pref * qn;
+    const double qm = Q[col][n == 0 ? 1 : n - 1];
+    const double qp = (2.0 * n - 1.0) * hc * fma(chi, qn, -qm);
+    const double2 ab = make_double2(fma(nd.a1, qp, -a2 * qn), nd.b1 * qp);
+    AB0[n] = ab;
+    if (n <= nf) AB0[-n] = ab;
+    if constexpr (CF) {
+      G0[n] = nd.pref * qs * qn;
+      if (n <= nf) G0[-n] = nd.pref * qs * qn;
+    }
   }
   __syncthreads();
   if (k != 0.0 && nmax < 32) {
@@ -499,21 +617,21 @@ __device__ void modal_modes(double k, double r, double rt, double c, double chim
     double ar = 0.0, br = 0.0, gr = 0.0;
     if (m <= nmax) {
       if (!hf) {
-        const double2 ab = M.AB0[m];
+        const double2 ab = AB0[m];
         ar = M.Fh[0] * ab.x;
         br = M.Fh[0] * ab.y;
-        if constexpr (CF) gr = M.Ch[0] * M.G0[m];
+        if constexpr (CF) gr = M.Ch[0] * G0[m];
       }
 #pragma unroll 4
       for (int n = n0; n <= n1; ++n) {
         const double f = M.Fh[n];
-        const double2 u = M.AB0[abs(m - n)], v = M.AB0[m + n];
+        const double2 u = AB0[m - n], v = AB0[m + n];
         ar = fma(f, u.x + v.x, ar);
         br = fma(f, u.y + v.y, br);
       }
       if constexpr (CF) {
 #pragma unroll 4
-        for (int n = n0; n <= n1; ++n) gr = fma(M.Ch[n], M.G0[abs(m - n)] + M.G0[m + n], gr);
+        for (int n = n0; n <= n1; ++n) gr = fma(M.Ch[n], G0[m - n] + G0[m + n], gr);
       }
     }
     ar += __shfl_xor(ar, 32);
@@ -525,27 +643,27 @@ __device__ void modal_modes(double k, double r, double rt, double c, double chim
       if constexpr (CF) M.Gm[m] = make_double2(gr * (1.0 / TWO_PI), M.Sh[m]);
     }
   } else if (lane <= nmax) {
-    const double2 ab = M.AB0[lane];
+    const double2 ab = AB0[lane];
     if (k == 0.0) {
       M.Am[lane] = make_double2(ab.x, 0.0);
       M.Bm[lane] = make_double2(ab.y, 0.0);
-      if constexpr (CF) M.Gm[lane] = make_double2(M.G0[lane], 0.0);
+      if constexpr (CF) M.Gm[lane] = make_double2(G0[lane], 0.0);
     } else {
       // F^ is even in n: (F^ * g)_m = F^_0 g_m + sum_{n>=1} F^_n (g_{|m-n|} + g_{m+n})
       double ar = M.Fh[0] * ab.x, br = M.Fh[0] * ab.y;
 #pragma unroll 4
       for (int n = 1; n <= nf; ++n) {
         const double f = M.Fh[n];
-        const double2 u = M.AB0[abs(lane - n)], v = M.AB0[lane + n];
+        const double2 u = AB0[lane - n], v = AB0[lane + n];
         ar = fma(f, u.x + v.x, ar);
         br = fma(f, u.y + v.y, br);
       }
       M.Am[lane] = make_double2(ar * (1.0 / TWO_PI), M.Hrh[lane]);
       M.Bm[lane] = make_double2(br * (1.0 / TWO_PI), -c * M.Hh[lane]);
       if constexpr (CF) {
-        double gr = M.Ch[0] * M.G0[lane];
+        double gr = M.Ch[0] * G0[lane];
 #pragma unroll 4
-        for (int n = 1; n <= nf; ++n) gr = fma(M.Ch[n], M.G0[abs(lane - n)] + M.G0[lane + n], gr);
+        for (int n = 1; n <= nf; ++n) gr = fma(M.Ch[n], G0[lane - n] + G0[lane + n], gr);
         M.Gm[lane] = make_double2(gr * (1.0 / TWO_PI), M.Sh[lane]);
       }
     }
@@ -557,19 +675,25 @@ __device__ void modal_modes(double k, double r, double rt, double c, double chim
 // (even in m), with e^{-i m alpha} = (c0, s0) and e^{i alpha} = (ca, sa):
 //   e^{-i m alpha} (r z' A_m - r r' B_m)
 //   - r/2 (p' - i q') e^{-i(m-1) alpha} B_{m-1} - r/2 (p' + i q') e^{-i(m+1) alpha} B_{m+1}
+// e1 = r z', e2 = r r', fr = r p' / 2, fq = r q' / 2.
+struct SlotNode {
+  double arev;           // alpha in revolutions
+  double ca, sa;         // e^{i alpha}
+  double e1, e2, fr, fq;
+};
 template <bool CF>
-__device__ __forceinline__ double2 theta_mode(int m, double c0, double s0, double ca, double sa,
-                                              const NodeLoc& L, const ModalScratch<CF>& M) {
-  const double r = L.r;
+__device__ __forceinline__ double2 theta_mode(int m, double c0, double s0, const SlotNode& L,
+                                              const ModalScratch<CF>& M) {
+  const double ca = L.ca, sa = L.sa;
   const double c1 = c0 * ca - s0 * sa, s1 = s0 * ca + c0 * sa;   // e^{-i(m-1) alpha}
   const double c2 = c0 * ca + s0 * sa, s2 = s0 * ca - c0 * sa;   // e^{-i(m+1) alpha}
   const double2 A = M.Am[abs(m)], B = M.Bm[abs(m)];
   const double2 Bm1 = M.Bm[abs(m - 1)], Bp1 = M.Bm[abs(m + 1)];
-  const double tr = r * L.dz * A.x - r * L.dr * B.x;
-  const double ti = r * L.dz * A.y - r * L.dr * B.y;
+  const double tr = L.e1 * A.x - L.e2 * B.x;
+  const double ti = L.e1 * A.y - L.e2 * B.y;
   double kr = c0 * tr - s0 * ti;
   double ki = c0 * ti + s0 * tr;
-  const double fr = 0.5 * r * L.dp, fq = 0.5 * r * L.dq;
+  const double fr = L.fr, fq = L.fq;
   {
     const double er = c1 * Bm1.x - s1 * Bm1.y, ei = c1 * Bm1.y + s1 * Bm1.x;
     kr -= fr * er + fq * ei;
@@ -588,22 +712,17 @@ __device__ __forceinline__ double2 theta_mode(int m, double c0, double s0, doubl
 // CF: ks receives the single-layer slot, e^{-i m alpha} G_|m| (the same
 // pairing of -N and N in slot 0).
 template <bool CF>
-__device__ __forceinline__ double2 modal_slot(int N, const NodeLoc& L, const ModalScratch<CF>& M,
-                                              double2& ks) {
+__device__ __forceinline__ double2 modal_slot(int N, const SlotNode& L, const ModalScratch<CF>& M,
+                                              double c0, double s0, double2& ks) {
   const int lane = threadIdx.x;
   double2 out = make_double2(0.0, 0.0);
   ks = make_double2(0.0, 0.0);
-  const double arev = L.alpha * (1.0 / TWO_PI);   // alpha in revolutions
-  double sa, ca;
-  sincos_2pi(arev, &sa, &ca);
   if (lane < 2 * N) {
     const int m = lane - N;
-    double s0, c0;
-    sincos_2pi(-m * arev, &s0, &c0);
-    out = theta_mode(m, c0, s0, ca, sa, L, M);
+    out = theta_mode(m, c0, s0, L, M);
     if constexpr (CF) ks = cmul(make_double2(c0, s0), M.Gm[abs(m)]);
     if (lane == 0) {
-      const double2 o2 = theta_mode(N, c0, -s0, ca, sa, L, M);
+      const double2 o2 = theta_mode(N, c0, -s0, L, M);
       out.x += o2.x;
       out.y += o2.y;
       if constexpr (CF) {
@@ -667,29 +786,6 @@ __device__ NodeLoc node_local(int shape, double a, double c, double kappa, const
   return L;
 }
 
-// The node held by lane `src` (uniform), broadcast to the wavefront.
-__device__ __forceinline__ NodeLoc read_node(const NodeLoc& v, int src) {
-  NodeLoc o;
-  o.r = readlane_f64(v.r, src); o.dr = readlane_f64(v.dr, src); o.dz = readlane_f64(v.dz, src);
-  o.dp = readlane_f64(v.dp, src); o.dq = readlane_f64(v.dq, src); o.rt = readlane_f64(v.rt, src);
-  o.alpha = readlane_f64(v.alpha, src); o.c = readlane_f64(v.c, src);
-  o.chim1 = readlane_f64(v.chim1, src); o.rmrt = readlane_f64(v.rmrt, src);
-  o.z = readlane_f64(v.z, src); o.p = readlane_f64(v.p, src); o.q = readlane_f64(v.q, src);
-  o.w = 0.0;
-  o.s = readlane_f64(v.s, src);
-  return o;
-}
-
-__device__ __forceinline__ NodeLoc shfl_node(const NodeLoc& v, int src) {
-  NodeLoc o;
-  o.r = __shfl(v.r, src); o.dr = __shfl(v.dr, src); o.dz = __shfl(v.dz, src);
-  o.dp = __shfl(v.dp, src); o.dq = __shfl(v.dq, src); o.rt = __shfl(v.rt, src);
-  o.alpha = __shfl(v.alpha, src); o.c = __shfl(v.c, src); o.chim1 = __shfl(v.chim1, src);
-  o.rmrt = __shfl(v.rmrt, src); o.z = __shfl(v.z, src); o.p = __shfl(v.p, src);
-  o.q = __shfl(v.q, src); o.w = __shfl(v.w, src); o.s = __shfl(v.s, src);
-  return o;
-}
-
 // ---------------------------------------------------------------- assembly kernel
 struct OuterRule {
   double x[2][NGO];   // [0]: NGO_UNIFORM nodes (rest unused), [1]: NGO nodes
@@ -701,18 +797,17 @@ struct OuterRule {
 // weighted 1/2 (applied when the slots were stored);
 // e^{i (s - N) j pi / N} = (-1)^j e^{i pi s j / N}.
 template <bool CF>
-__device__ __forceinline__ void slots_to_nodes(const SelfShared<CF>& S, int N,
-                                               double2 (&g)[GL_ORDER]) {
+__device__ __forceinline__ void slots_to_nodes(const SelfShared<CF>& S, int N, double2* g) {
   const int lane = threadIdx.x;
 #pragma unroll
-  for (int l = 0; l < GL_ORDER; ++l) g[l] = make_double2(0.0, 0.0);
+  for (int l = 0; l < RH; ++l) g[l] = make_double2(0.0, 0.0);
   int e = 0;
   for (int sl = 0; sl < 2 * N; ++sl) {
     const double2 t = S.tw2n[e];
     e += lane;
     if (e >= 2 * N) e -= 2 * N;
 #pragma unroll
-    for (int l = 0; l < GL_ORDER; ++l) {
+    for (int l = 0; l < RH; ++l) {
       const double2 v = S.acc[l][sl];
       g[l].x = fma(v.x, t.x, fma(-v.y, t.y, g[l].x));
       g[l].y = fma(v.x, t.y, fma(v.y, t.x, g[l].y));
@@ -720,56 +815,16 @@ __device__ __forceinline__ void slots_to_nodes(const SelfShared<CF>& S, int N,
   }
   const double scale = ((lane & 1) ? -1.0 : 1.0) / (2 * N);
 #pragma unroll
-  for (int l = 0; l < GL_ORDER; ++l) g[l] = make_double2(g[l].x * scale, g[l].y * scale);
+  for (int l = 0; l < RH; ++l) g[l] = make_double2(g[l].x * scale, g[l].y * scale);
 }
 
 template <bool CF>
-__device__ __forceinline__ void store_slots(SelfShared<CF>& S, const double2 (&acc)[GL_ORDER], bool conj) {
+__device__ __forceinline__ void store_slots(SelfShared<CF>& S, const double2* acc, bool conj) {
   const int lane = threadIdx.x;
   const double f = lane == 0 ? 0.5 : 1.0;
   const double fy = conj ? -f : f;
 #pragma unroll
-  for (int l = 0; l < GL_ORDER; ++l) S.acc[l][lane] = make_double2(acc[l].x * f, acc[l].y * fy);
-}
-
-// One radix-4 Stockham pass (as r4_pass) over the NR rows X[l][0..L) at once:
-// NR L / 4 butterflies, NR L / 256 per lane, read before the barrier, written
-// after it.
-template <int L, int Ns, int NR>
-__device__ __forceinline__ void r4_pass_rows(double2 (*X)[64], const double2* tw) {
-  constexpr int NB = L / 4, NBT = NR * NB, PER = NBT >= 64 ? NBT / 64 : 1;
-  const int lane = threadIdx.x;
-  const bool act = NBT >= 64 || lane < NBT;
-  double2 a[PER][4], w[PER][3];
-#pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const int e = lane + 64 * u, row = e / NB, j = e % NB;
-    if (!act) continue;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) a[u][i] = X[row][j + i * NB];
-    if (Ns > 1) {
-      constexpr int step = LD / (4 * Ns);
-      const int k = j & (Ns - 1);
-#pragma unroll
-      for (int i = 1; i < 4; ++i) w[u][i - 1] = tw[twi(i * k * step)];
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const int e = lane + 64 * u, row = e / NB, j = e % NB;
-    if (!act) continue;
-    const int k = j & (Ns - 1);
-    if (Ns > 1) {
-#pragma unroll
-      for (int i = 1; i < 4; ++i) a[u][i] = cmul(a[u][i], w[u][i - 1]);
-    }
-    dft4(a[u][0], a[u][1], a[u][2], a[u][3]);
-    const int o = 4 * (j - k) + k;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) X[row][o + i * Ns] = a[u][i];
-  }
-  __syncthreads();
+  for (int l = 0; l < RH; ++l) S.acc[l][lane] = make_double2(acc[l].x * f, acc[l].y * fy);
 }
 
 // slots_to_nodes for 2N = 16 or 64 (powers of 4): the inverse DFT of every
@@ -777,19 +832,19 @@ __device__ __forceinline__ void r4_pass_rows(double2 (*X)[64], const double2* tw
 // same scale and sign.
 template <int L>
 __device__ __forceinline__ void fft_rows(double2 (*X)[64], const double2* tw) {
-  r4_pass_rows<L, 1, GL_ORDER>(X, tw);
-  r4_pass_rows<L, 4, GL_ORDER>(X, tw);
-  if constexpr (L == 64) r4_pass_rows<L, 16, GL_ORDER>(X, tw);
+  r4_pass_rows<L, 1, RH>(X, tw);
+  r4_pass_rows<L, 4, RH>(X, tw);
+  if constexpr (L == 64) r4_pass_rows<L, 16, RH>(X, tw);
 }
 
 template <bool CF>
-__device__ __forceinline__ void slots_to_nodes_fft(SelfShared<CF>& S, int N, double2 (&g)[GL_ORDER]) {
+__device__ __forceinline__ void slots_to_nodes_fft(SelfShared<CF>& S, int N, double2* g) {
   const int lane = threadIdx.x;
   if (2 * N == 64) fft_rows<64>(S.acc, S.tw);
   else fft_rows<16>(S.acc, S.tw);
   const double scale = ((lane & 1) ? -1.0 : 1.0) / (2 * N);
 #pragma unroll
-  for (int l = 0; l < GL_ORDER; ++l) {
+  for (int l = 0; l < RH; ++l) {
     const double2 v = lane < 2 * N ? S.acc[l][lane] : make_double2(0.0, 0.0);
     g[l] = make_double2(v.x * scale, -v.y * scale);
   }
@@ -802,7 +857,7 @@ __device__ __forceinline__ void slots_to_nodes_fft(SelfShared<CF>& S, int N, dou
 // the single layer interpolates the density times |J|, so its column
 // (ip, l, j) carries |J| at that node.
 template <int FORM>
-__global__ __launch_bounds__(64) void assemble_self_kernel(
+__global__ __launch_bounds__(64, FORM == 0 ? 2 : 1) void assemble_self_kernel(
     const SelfTask* __restrict__ tasks, const BlockDev* __restrict__ blocks,
     const BodyDev* __restrict__ bodies, const double* __restrict__ gl16,
     const OuterRule* __restrict__ orule, double2* __restrict__ pool) {
@@ -934,6 +989,8 @@ __global__ __launch_bounds__(64) void assemble_self_kernel(
     for (int l = 0; l < GL_ORDER; ++l) acs[l] = make_double2(0.0, 0.0);
   }
   const int nsides = (ip == pT) ? 2 : 1;
+  const double sh2 = lane_azimuth();
+  const int mq = min(MQ_CAP, N + 1 + NF_CAP);
   for (int side = 0; side < nsides; ++side) {
     // outer node `lane` (lanes >= the rule's order idle): offset dl from tT
     // and weight (u^5 substitution)
@@ -986,6 +1043,21 @@ __global__ __launch_bounds__(64) void assemble_self_kernel(
       const double rho_max = sqrt((L.r + L.rt) * (L.r + L.rt) + L.c * L.c);
       wide = acosh_chi * ((LD / 2) - N - (k * rho_max + 10.0)) < 40.0;
     }
+    // what the node's route needs of it, kept by its lane and broadcast when
+    // the node is processed
+    ModalNode mn = modal_node(Lme.r, Lme.rt, Lme.c, Lme.chim1, Lme.rmrt);
+    SlotNode sn;
+    sn.arev = Lme.alpha * (1.0 / TWO_PI);
+    sincos_tw(sn.arev, S.tw, &sn.sa, &sn.ca);
+    sn.e1 = Lme.r * Lme.dz;
+    sn.e2 = Lme.r * Lme.dr;
+    sn.fr = 0.5 * Lme.r * Lme.dp;
+    sn.fq = 0.5 * Lme.r * Lme.dq;
+    QStart qst = toroidal_start(modal ? 1.0 + Lme.chim1 : 2.0, modal ? Lme.chim1 : 1.0);
+    if (!modal) {      // the same registers hold the direct route's values
+      mn.rt = Lme.dr; mn.c = Lme.z; mn.chim1 = Lme.dz;
+      mn.hc = Lme.p; mn.a1 = Lme.dp; mn.a2 = Lme.q; mn.b1 = Lme.dq;
+    }
     const unsigned long long mmask = __ballot(modal);
     const int nmodal = __popcll(mmask);
     {
@@ -997,17 +1069,29 @@ __global__ __launch_bounds__(64) void assemble_self_kernel(
     for (int b0 = 0; b0 < nmodal; b0 += QB) {
       const bool qlane = lane < QB && b0 + lane < nmodal;
       const int src = qlane ? S.modal_idx[b0 + lane] : 0;
-      const double cm1 = __shfl(Lme.chim1, src);
-      const double qchim1 = qlane ? cm1 : 1.0;
-      toroidal_q_batch(qlane, 1.0 + qchim1, qchim1, MQ_CAP, S.Q, lane & (QB - 1));
+      QStart qs;
+      qs.q0 = __shfl(qst.q0, src);
+      qs.q1 = __shfl(qst.q1, src);
+      qs.acosh = __shfl(qst.acosh, src);
+      const double qchi = 1.0 + __shfl(mn.chim1, src);
+      const double qscale = toroidal_q_batch(qlane, qchi, qs, mq, S.Q, lane);
       __syncthreads();
       const int cnt = min(QB, nmodal - b0);
       for (int q = 0; q < cnt; ++q) {
         const int sl = __builtin_amdgcn_readfirstlane(S.modal_idx[b0 + q]);
-        const NodeLoc Ln = read_node(Lme, sl);
-        modal_modes<CF>(k, Ln.r, Ln.rt, Ln.c, Ln.chim1, Ln.rmrt, N + 1, S.Q, q, S.u.m, S.tw);
+        auto rl = [&](double v) { return readlane_f64(v, sl); };
+        ModalNode Ln;
+        Ln.r = rl(mn.r); Ln.rt = rl(mn.rt); Ln.c = rl(mn.c); Ln.chim1 = rl(mn.chim1);
+        Ln.hc = rl(mn.hc); Ln.a1 = rl(mn.a1); Ln.a2 = rl(mn.a2); Ln.b1 = rl(mn.b1);
+        Ln.pref = CF ? rl(mn.pref) : 0.0;
+        SlotNode Sn;
+        Sn.arev = rl(sn.arev); Sn.ca = rl(sn.ca); Sn.sa = rl(sn.sa);
+        Sn.e1 = rl(sn.e1); Sn.e2 = rl(sn.e2); Sn.fr = rl(sn.fr); Sn.fq = rl(sn.fq);
+        double s0, c0;      // e^{-i m alpha} of slot m = lane - N
+        sincos_tw((N - lane) * Sn.arev, S.tw, &s0, &c0);
+        modal_modes<CF>(k, Ln, readlane_f64(qscale, q), sh2, N + 1, S.Q, q, S.u.m, S.tw);
         double2 ks;
-        const double2 Kq = modal_slot<CF>(N, Ln, S.u.m, ks);
+        const double2 Kq = modal_slot<CF>(N, Sn, S.u.m, c0, s0, ks);
         accumulate_node(acc, P, sl, Kq);
         if constexpr (CF) accumulate_node(acs, P, sl, ks);
         __syncthreads();
@@ -1021,10 +1105,10 @@ __global__ __launch_bounds__(64) void assemble_self_kernel(
     // samples of node q at L azimuths into S.u.K[part][base + l]
     auto sample = [&](int q, int L, int base) {
       const int tstep = LD / L;
-      const NodeLoc Lq = read_node(Lme, q);
+      auto rl = [&](double v) { return readlane_f64(v, q); };
       Curve cv;
-      cv.r = Lq.r; cv.dr = Lq.dr; cv.z = Lq.z; cv.dz = Lq.dz;
-      cv.p = Lq.p; cv.dp = Lq.dp; cv.q = Lq.q; cv.dq = Lq.dq;
+      cv.r = rl(mn.r); cv.dr = rl(mn.rt); cv.z = rl(mn.c); cv.dz = rl(mn.chim1);
+      cv.p = rl(mn.hc); cv.dp = rl(mn.a1); cv.q = rl(mn.a2); cv.dq = rl(mn.b1);
 #pragma unroll
       for (int hh = 0; hh < LD / 64; ++hh) {
         const int l = lane + 64 * hh;
@@ -1039,7 +1123,7 @@ __global__ __launch_bounds__(64) void assemble_self_kernel(
           const double ir = rsqrt_pos(r2);
           const double rr = r2 * ir;
           double s, c;
-          sincos_2pi(rr * k2pi, &s, &c);
+          sincos_tw(rr * k2pi, S.tw, &s, &c);
           const double sc = (dx * nx + dy * ny + dz * nz) * ir * ir * ir * INV_4PI;
           S.u.K[0][base + l] = make_double2(-fma(k * rr, s, c) * sc, fma(k * rr, c, -s) * sc);
           if constexpr (CF)
@@ -1099,20 +1183,23 @@ __global__ __launch_bounds__(64) void assemble_self_kernel(
   __syncthreads();   // the recurrence batches are done with S.Q (shares S.acc)
   // inverse DFT over the 2N slots: radix-4 FFT passes when 2N is 16 or 64
   const bool fft_inv = 2 * N == 64 || 2 * N == 16;
-  store_slots(S, acc, fft_inv);
-  __syncthreads();
   double2 g[GL_ORDER];
-  if (fft_inv) slots_to_nodes_fft(S, N, g);
-  else if (lane < 2 * N) slots_to_nodes(S, N, g);
+  auto inverse = [&](const double2 (&a)[GL_ORDER], double2 (&o)[GL_ORDER]) {
+#pragma unroll
+    for (int l = 0; l < GL_ORDER; l += RH) {
+      store_slots(S, a + l, fft_inv);
+      __syncthreads();
+      if (fft_inv) slots_to_nodes_fft(S, N, o + l);
+      else if (lane < 2 * N) slots_to_nodes(S, N, o + l);
+      __syncthreads();
+    }
+  };
+  inverse(acc, g);
   if constexpr (CF) {
     // single layer: second inverse DFT, then - i eta |J| (combined field) or
     // |J| (single layer) at the column node
-    __syncthreads();
-    store_slots(S, acs, fft_inv);
-    __syncthreads();
     double2 gs[GL_ORDER];
-    if (fft_inv) slots_to_nodes_fft(S, N, gs);
-    else if (lane < 2 * N) slots_to_nodes(S, N, gs);
+    inverse(acs, gs);
     if (lane < 2 * N) {
       double sj, cj;
       sincos_cw(lane * PI / N, &sj, &cj);
@@ -1226,9 +1313,11 @@ __global__ __launch_bounds__(64) void modal_modes_kernel(const double* __restric
     sincos_cw(-TWO_PI * q / LD, &s, &cc);
     S.tw[twi(q)] = make_double2(cc, s);
   }
-  toroidal_q_batch(lane == 0, 1.0 + chim1[pt], chim1[pt], MQ_CAP, S.Q, lane & (QB - 1));
+  const QStart q = toroidal_start(1.0 + chim1[pt], chim1[pt]);
+  const double qs = readlane_f64(toroidal_q_batch(lane == 0, 1.0 + chim1[pt], q, MQ_CAP, S.Q, lane), 0);
   __syncthreads();
-  modal_modes<false>(k, r[pt], rt[pt], c[pt], chim1[pt], rmrt[pt], nmax, S.Q, 0, S.u.m, S.tw);
+  modal_modes<false>(k, modal_node(r[pt], rt[pt], c[pt], chim1[pt], rmrt[pt]), qs, lane_azimuth(), nmax, S.Q, 0,
+                     S.u.m, S.tw);
   if (lane <= nmax) {
     A[(int64_t)pt * (nmax + 1) + lane] = S.u.m.Am[lane];
     B[(int64_t)pt * (nmax + 1) + lane] = S.u.m.Bm[lane];
