@@ -548,8 +548,9 @@ extern "C" qax_status qax_assemble_self(qax_problem* p, double* t_setup_s) {
     QCHECK(dev_alloc(p, (void**)&p->d_B32, (size_t)p->block_elems * 8), "alloc self blocks fp32");
   }
   QCHECK(setup_sym_apply(p), "reduced inverses");
-  QCHECK(launch_assemble_self(p), "assemble_self");
   QBUF(work, double, "gj_work", invert_blocks_work_bytes(p));
+  QBUF(items, void, "self_items", assemble_self_work_bytes(p));
+  QCHECK(launch_assemble_self(p, items), "assemble_self");
   if (p->factor_prec == QAX_FP64) {
     QCHECK(launch_factor_blocks64(p, work), "invert_blocks (FP64)");
   } else {

@@ -189,6 +189,7 @@ struct qax_problem {
 
   // self blocks (complex128 / complex64 pools)
   double* d_B = nullptr;
+  std::vector<qax::SelfTask> self_tasks;   // assembly work items, kept for their upload
   double* d_Binv = nullptr;
   bool inv64_ready = false;     // d_Binv holds the inverse of the current blocks
   // precision of the factorisation made by qax_assemble_self: QAX_FP64 (the
@@ -397,7 +398,8 @@ hipError_t launch_convert_f32(hipStream_t s, const double* src, float* dst, int6
 hipError_t launch_dense_offdiag(qax_problem* p, double* A);
 
 // selfblock.hip
-hipError_t launch_assemble_self(qax_problem* p);
+size_t assemble_self_work_bytes(const qax_problem* p);
+hipError_t launch_assemble_self(qax_problem* p, void* work);
 hipError_t launch_modal_modes(hipStream_t s, int n, const double* r, const double* rt,
                               const double* c, const double* chim1, const double* rmrt, double k,
                               int nmax, double* A, double* B);
