@@ -446,15 +446,6 @@ __device__ void fft128x2(double2* xa, double2* xb, const double2* tw) {
   __syncthreads();
 }
 
-__device__ void fft128(double2* x, const double2* tw) {
-  const int lane = threadIdx.x;
-  r4_pass<128, 1>(x, lane, lane < 32, tw);
-  r4_pass<128, 4>(x, lane, lane < 32, tw);
-  r4_pass<128, 16>(x, lane, lane < 32, tw);
-  r2_last128(x, lane, tw);
-  __syncthreads();
-}
-
 __device__ void fft256(double2* x, const double2* tw) {
   const int lane = threadIdx.x;
   r4_pass<256, 1>(x, lane, true, tw);
@@ -465,11 +456,6 @@ __device__ void fft256(double2* x, const double2* tw) {
 
 __device__ __forceinline__ double wave_min(double v) {
   for (int off = 32; off > 0; off >>= 1) v = fmin(v, __shfl_xor(v, off));
-  return v;
-}
-
-__device__ __forceinline__ double wave_max(double v) {
-  for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off));
   return v;
 }
 
@@ -856,6 +842,9 @@ __device__ __forceinline__ void slots_to_nodes_fft(SelfShared<CF>& S, int N, dou
 // field 1/2 I + D - i eta S (the combined-field remark of Section 2), where
 // the single layer interpolates the density times |J|, so its column
 // (ip, l, j) carries |J| at that node.
+// One wavefront per SIMD for the combined field and the single layer: within
+// 256 registers their second set of accumulators spills in the node loops (9
+// mirror-symmetric blocks of order 2048: 2.3 ms, with two wavefronts 4.3).
 template <int FORM>
 __global__ __launch_bounds__(64, FORM == 0 ? 2 : 1) void assemble_self_kernel(
     const SelfTask* __restrict__ tasks, const BlockDev* __restrict__ blocks,
