@@ -410,21 +410,85 @@ static void gemv_tables_lpr(hipStream_t s, const BodyDev* bodies, const BlockDev
     gemv_tables_launch<MT, NRC, VEC, 64>(s, bodies, blocks, node_body, pool, rows, v, nrhs, out, acc);
 }
 
+// One right-hand side, square blocks of one order (a multiple of 32) one after another: a
+// group of LPR lanes takes RPG rows of a block, which share the loads of the
+// input.  Bound by the tables' bytes: 6859 blocks of order 96 in 183 us (5.5
+// TB/s; 244 with one row per group), FP32 99 us (142).
+template <typename MT, int VEC, int LPR, int RPG>
+__global__ __launch_bounds__(256) void table_gemv_kernel(const MT* __restrict__ pool, int n, int64_t rows,
+                                                         const double2* __restrict__ v,
+                                                         double2* __restrict__ out, int accumulate) {
+  typedef MT vec_t __attribute__((ext_vector_type(2 * VEC)));
+  const int lane = threadIdx.x & (LPR - 1);
+  const int64_t row = ((int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR) * RPG;
+  if (row >= rows) return;
+  const MT* a = pool + 2 * row * n;
+  const double2* vb = v + row / n * n;
+  double ar[RPG], ai[RPG];
+#pragma unroll
+  for (int r = 0; r < RPG; ++r) ar[r] = ai[r] = 0.0;
+  for (int j = lane * VEC; j < n; j += LPR * VEC) {
+    vec_t m[RPG];
+    double2 x[VEC];
+#pragma unroll
+    for (int r = 0; r < RPG; ++r) m[r] = *(const vec_t*)(a + 2 * ((int64_t)r * n + j));
+#pragma unroll
+    for (int q = 0; q < VEC; ++q) x[q] = vb[j + q];
+#pragma unroll
+    for (int r = 0; r < RPG; ++r)
+#pragma unroll
+      for (int q = 0; q < VEC; ++q) {
+        const double mr = (double)m[r][2 * q], mi = (double)m[r][2 * q + 1];
+        ar[r] = fma(mr, x[q].x, fma(-mi, x[q].y, ar[r]));
+        ai[r] = fma(mr, x[q].y, fma(mi, x[q].x, ai[r]));
+      }
+  }
+#pragma unroll
+  for (int r = 0; r < RPG; ++r)
+#pragma unroll
+    for (int off = LPR / 2; off > 0; off >>= 1) {
+      ar[r] += __shfl_xor(ar[r], off);
+      ai[r] += __shfl_xor(ai[r], off);
+    }
+#pragma unroll
+  for (int r = 0; r < RPG; ++r)
+    if (lane == r) {
+      double2 o = accumulate ? out[row + r] : make_double2(0.0, 0.0);
+      o.x += ar[r];
+      o.y += ai[r];
+      out[row + r] = o;
+    }
+}
+
+template <typename MT, int VEC, int LPR, int RPG>
+static void table_gemv_launch(hipStream_t s, const void* pool, int order, int64_t rows, const double2* v,
+                              double2* out, int acc) {
+  const int64_t per = 256 / LPR * RPG;
+  hipLaunchKernelGGL((table_gemv_kernel<MT, VEC, LPR, RPG>), dim3((unsigned)((rows + per - 1) / per)), dim3(256), 0,
+                     s, (const MT*)pool, order, rows, v, out, acc);
+}
+
 hipError_t launch_gemv_tables(hipStream_t s, const BodyDev* bodies, const BlockDev* blocks,
                               const int32_t* node_body, const void* pool, bool f32, int64_t rows,
                               int order, const double* v, int nrhs, double* out, bool accumulate) {
   const double2* vv = (const double2*)v;
   double2* oo = (double2*)out;
   const int acc = accumulate ? 1 : 0;
-  if (f32) {
-    if (nrhs == 1 && order > 128 * 2)
-      gemv_f32_lds_launch<2>(s, bodies, blocks, node_body, (const float*)pool, rows, v, out, accumulate,
-                             nullptr);
-    else if (nrhs == 1) gemv_tables_lpr<float, 1, 2>(s, bodies, blocks, node_body, pool, rows, order, vv, nrhs, oo, acc);
-    else gemv_tables_lpr<float, 4, 1>(s, bodies, blocks, node_body, pool, rows, order, vv, nrhs, oo, acc);
+  // one right-hand side, short rows: two rows per group of lanes, 32 lanes, 16
+  // below 128 FP32 entries (order 64: 38.5 us against 56 with 32); longer rows
+  // keep one row per wavefront (order 512: 253 us here against 247, 768: 569
+  // against 539), FP32 ones with their input in LDS (281 us both at 768)
+  if (nrhs == 1 && order <= 256) {
+    if (!f32) table_gemv_launch<double, 1, 32, 2>(s, pool, order, rows, vv, oo, acc);
+    else if (order < 128) table_gemv_launch<float, 2, 16, 2>(s, pool, order, rows, vv, oo, acc);
+    else table_gemv_launch<float, 2, 32, 2>(s, pool, order, rows, vv, oo, acc);
+  } else if (nrhs == 1) {
+    if (f32) gemv_f32_lds_launch<2>(s, bodies, blocks, node_body, (const float*)pool, rows, v, out, accumulate, nullptr);
+    else gemv_tables_launch<double, 1, 1, 64>(s, bodies, blocks, node_body, pool, rows, vv, nrhs, oo, acc);
+  } else if (f32) {
+    gemv_tables_lpr<float, 4, 1>(s, bodies, blocks, node_body, pool, rows, order, vv, nrhs, oo, acc);
   } else {
-    if (nrhs == 1) gemv_tables_lpr<double, 1, 1>(s, bodies, blocks, node_body, pool, rows, order, vv, nrhs, oo, acc);
-    else gemv_tables_lpr<double, 4, 1>(s, bodies, blocks, node_body, pool, rows, order, vv, nrhs, oo, acc);
+    gemv_tables_lpr<double, 4, 1>(s, bodies, blocks, node_body, pool, rows, order, vv, nrhs, oo, acc);
   }
   return hipGetLastError();
 }

@@ -98,8 +98,16 @@ __global__ __launch_bounds__(256) void lattice_blocks_kernel(
 // along axis `ax`, the output's extents elsewhere) and every element e < E of
 // a site's contiguous run.  in_node / out_node: first node of each site's
 // body (a run starts at node * mult), for the density and the result in the
-// handle's node order; null for dense site-major arrays.  One thread per
-// output element; loads and stores coalesced along e.
+// handle's node order; null for dense site-major arrays.
+// One thread per element and LAT_OC outputs along the axis (blockIdx.y), which share each
+// input load and whose twiddles are the same in the whole workgroup; loads
+// and stores coalesced along e.  Bound by latency: the transforms of one
+// density are a few MB.  INDEX: 32-bit where the elements of a launch allow it.
+// 10 x 10 x 10 bodies of 96 nodes, the six passes: 71 us with one output per
+// thread and 64-bit divisions, 47 here (ten inputs kept in flight by hand: 87); the tables'
+// three passes over 1 GB: 8.0 ms, 3.5 here.
+constexpr int LAT_OC = 4;
+template <typename INDEX>
 __global__ __launch_bounds__(256) void lattice_dft_kernel(
     const double2* __restrict__ in, const int64_t* __restrict__ in_node, double2* __restrict__ out,
     const int64_t* __restrict__ out_node, int64_t mult, int accumulate, int n0, int n1, int n2,
@@ -111,49 +119,63 @@ __global__ __launch_bounds__(256) void lattice_dft_kernel(
     tw[q] = make_double2(c, sign * s);
   }
   __syncthreads();
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t total = (int64_t)n0 * n1 * n2 * E;
-  if (idx >= total) return;
-  const int64_t e = idx % E;
-  const int64_t so = idx / E;
-  int o[3];
-  o[2] = (int)(so % n2);
-  o[1] = (int)((so / n2) % n1);
-  o[0] = (int)(so / ((int64_t)n1 * n2));
-  int din[3] = {n0, n1, n2};
-  din[ax] = nin;
-  const int oa = o[ax];
-  double ar = 0.0, ai = 0.0;
-  int q = 0;
+  const int nout = ax == 0 ? n0 : ax == 1 ? n1 : n2;
+  // the line's two other coordinates (u, v), strides of the sites along them
+  // and along the axis, in and out
+  const int nv = ax == 2 ? n1 : n2;
+  const INDEX lines = (INDEX)((ax == 0 ? n1 : n0) * nv);
+  const INDEX idx = (INDEX)blockIdx.x * 256 + threadIdx.x;
+  const INDEX line = idx / (INDEX)E;
+  const int64_t e = (int64_t)(idx - line * (INDEX)E);
+  if (line >= lines) return;
+  const int u = (int)line / nv, v = (int)line - u * nv;
+  const int sti = ax == 0 ? n1 * n2 : ax == 1 ? n2 : 1;
+  const int si = ax == 0 ? u * n2 + v : ax == 1 ? u * nin * n2 + v : (u * n1 + v) * nin;
+  const int so = ax == 0 ? u * n2 + v : ax == 1 ? u * n1 * n2 + v : (u * n1 + v) * n2;
+  const int o0 = blockIdx.y * LAT_OC;
+  double ar[LAT_OC], ai[LAT_OC];
+  int q[LAT_OC];
+#pragma unroll
+  for (int c = 0; c < LAT_OC; ++c) {
+    ar[c] = ai[c] = 0.0;
+    q[c] = 0;
+  }
+#pragma unroll 4
   for (int t = 0; t < nin; ++t) {
-    int c[3] = {o[0], o[1], o[2]};
-    c[ax] = t;
-    const int64_t si = ((int64_t)c[0] * din[1] + c[1]) * din[2] + c[2];
-    const int64_t base = in_node ? in_node[si] * mult : si * E;
-    const double2 v = in[base + e];
-    const double2 w = tw[q];
-    ar = fma(v.x, w.x, fma(-v.y, w.y, ar));
-    ai = fma(v.x, w.y, fma(v.y, w.x, ai));
-    q += oa;
-    if (q >= L) q -= L;
+    const int st = si + t * sti;
+    const double2 x = in[(in_node ? in_node[st] * mult : st * E) + e];
+#pragma unroll
+    for (int c = 0; c < LAT_OC; ++c) {
+      const double2 w = tw[q[c]];
+      ar[c] = fma(x.x, w.x, fma(-x.y, w.y, ar[c]));
+      ai[c] = fma(x.x, w.y, fma(x.y, w.x, ai[c]));
+      q[c] += min(o0 + c, L - 1);       // (outputs beyond nout are not stored)
+      if (q[c] >= L) q[c] -= L;
+    }
   }
-  const int64_t ob = (out_node ? out_node[so] * mult : so * E) + e;
-  double2 r = make_double2(ar * scale, ai * scale);
-  if (accumulate) {
-    const double2 prev = out[ob];
-    r.x += prev.x;
-    r.y += prev.y;
+#pragma unroll
+  for (int c = 0; c < LAT_OC; ++c) {
+    if (o0 + c >= nout) break;
+    const int st = so + (o0 + c) * sti;
+    const int64_t ob = (out_node ? out_node[st] * mult : st * E) + e;
+    double2 r = make_double2(ar[c] * scale, ai[c] * scale);
+    if (accumulate) {
+      const double2 prev = out[ob];
+      r.x += prev.x;
+      r.y += prev.y;
+    }
+    out[ob] = r;
   }
-  out[ob] = r;
 }
 
 static hipError_t dft_axis(hipStream_t s, const double2* in, const int64_t* in_node, double2* out,
                            const int64_t* out_node, int64_t mult, bool accumulate, const int n[3],
                            int ax, int nin, int L, int sign, double scale, int64_t E) {
-  const int64_t total = (int64_t)n[0] * n[1] * n[2] * E;
-  hipLaunchKernelGGL(lattice_dft_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, in,
-                     in_node, out, out_node, mult, accumulate ? 1 : 0, n[0], n[1], n[2], ax, nin, L,
-                     sign, scale, E);
+  const int64_t total = (int64_t)n[0] * n[1] * n[2] / n[ax] * E;
+  const dim3 grid((unsigned)((total + 255) / 256), (unsigned)((n[ax] + LAT_OC - 1) / LAT_OC));
+  auto kern = total < ((int64_t)1 << 31) ? lattice_dft_kernel<uint32_t> : lattice_dft_kernel<int64_t>;
+  hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, in, in_node, out, out_node, mult, accumulate ? 1 : 0, n[0], n[1],
+                     n[2], ax, nin, L, sign, scale, E);
   return hipGetLastError();
 }
 
