@@ -1271,7 +1271,7 @@ static void gj_factor_panel(hipStream_t s, typename Cx<T>::V* pool, const MatDes
 // (41-48 TFLOP/s in the updates, bound by the matrix cores, by whole tiles
 // over the chip's places and by the load and store around 64 columns' work).
 //
-// bad[0], bad[1] are set where elimination on the diagonal may lose digits:
+// bad[0] or bad[1] is set where elimination on the diagonal may lose digits:
 // a multiplier beyond 4 within a diagonal block, a 2 x 2 pivot block whose
 // determinant cancels (a diagonal product beyond 8 times it), an entry of G
 // beyond 8, or anything not finite; the caller then inverts again with
@@ -1386,7 +1386,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
   int z, it, jt;
   bool next = false;                    // the next panel's diagonal tile
   if (UPDATE) {
-    if (bad[0]) return;                 // some matrix needs interchanges (not written by this launch)
+    if (bad[0]) {                       // some matrix needs interchanges (written by the other launches only)
+      if (!blockIdx.x && !tid) bad[1] = 1;
+      return;
+    }
     const int d = k0 / GJD + 1 < tiles ? k0 / GJD + 1 : 0;
     int b = blockIdx.x;
     const int first = (batch + 7) & ~7, rest = batch * (tiles * tiles - 1), per = (rest + 7) >> 3;
@@ -1406,6 +1409,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
       jt = b - it * tiles;
     }
   } else {
+    if (bad[1]) {
+      if (!blockIdx.x && !blockIdx.y && !tid) bad[0] = 1;
+      return;
+    }
     z = blockIdx.y;
     it = blockIdx.x;
     jt = 0;
@@ -1545,42 +1552,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
   }
 }
 
-__global__ void gjd_clear_kernel(int* bad) { bad[0] = bad[1] = 0; }
+__global__ void gjd_clear_kernel(int* bad) { bad[threadIdx.x] = 0; }
 
 // In-place inversion of `batch` FP64 matrices on the diagonal, work as
-// gj_invert's; *failed: some matrix needs interchanges (the pool then holds
-// no inverse).  Waits for the stream.
+// gj_invert's.  bad (two values, 0 on entry): nonzero afterwards where some
+// matrix needs interchanges, whose inverse and the others' the pool then does
+// not hold.  The launches after a failure return at once; nothing here waits.
 static hipError_t gjd_invert(qax_problem* p, double2* pool, const MatDesc* d_mats, int batch, int nmax,
-                             double* work, bool* failed) {
+                             double* work, int* bad) {
   if (nmax > 8192) return hipErrorInvalidValue;
   const hipStream_t s = p->stream;
   double2* W = (double2*)work;
   double2* G = W + (int64_t)GJD * nmax * batch;
   double2* dinv = G + (int64_t)GJD * nmax * batch;      // in the recursive panels' part of the workspace
-  int* bad = (int*)(dinv + (int64_t)batch * GJD * GJD);
   const int tiles = (nmax + 63) / 64;
-  hipLaunchKernelGGL(gjd_clear_kernel, dim3(1), dim3(1), 0, s, bad);
-  int h_bad[2] = {0, 0};
-  auto check = [&]() {
-    const hipError_t e = hipMemcpyAsync(h_bad, bad, sizeof(h_bad), hipMemcpyDeviceToHost, s);
-    return e == hipSuccess ? hipStreamSynchronize(s) : e;
-  };
-  hipError_t e = hipSuccess;
   hipLaunchKernelGGL(gjd_first_kernel, dim3(batch), dim3(256), 0, s, d_mats, pool, dinv, bad);
-  for (int k0 = 0; k0 < nmax && e == hipSuccess; k0 += GJD) {
+  for (int k0 = 0; k0 < nmax; k0 += GJD) {
     hipLaunchKernelGGL(gjd_tile_kernel<0>, dim3(2 * tiles, batch), dim3(256), 0, s, d_mats, pool, k0, G, W, dinv,
                        nmax, tiles, batch, bad);
-    // matrices that need interchanges show it early, mostly in the first panel
-    if (k0 / GJD % 8 == 0 && ((e = check()) != hipSuccess || h_bad[0] || h_bad[1])) break;
     timing_begin(p, QAX_K_INVERT_UPDATE);
-    hipLaunchKernelGGL(gjd_tile_kernel<1>, dim3(((batch + 7) & ~7) + ((batch * (tiles * tiles - 1) + 7) & ~7)), dim3(256), 0, s, d_mats, pool, k0, G, W,
-                       dinv, nmax, tiles, batch, bad);
+    hipLaunchKernelGGL(gjd_tile_kernel<1>, dim3(((batch + 7) & ~7) + ((batch * (tiles * tiles - 1) + 7) & ~7)),
+                       dim3(256), 0, s, d_mats, pool, k0, G, W, dinv, nmax, tiles, batch, bad);
     timing_end(p, QAX_K_INVERT_UPDATE);
-    e = hipGetLastError();
   }
-  if (e == hipSuccess && !h_bad[0] && !h_bad[1]) e = check();
-  *failed = h_bad[0] || h_bad[1];
-  return e;
+  return hipGetLastError();
 }
 
 // In-place inversion of `batch` matrices of complex T (interleaved, pool in
@@ -1686,7 +1681,7 @@ struct SymInvPlan {
   std::vector<MatDesc> red, plain;
   int nmax_red = 0, nmax_plain = 0;
   int64_t red_elems = 0;
-  size_t off_red = 0, off_plain = 0, off_desc = 0, off_rows = 0, off_gj = 0, off_pool = 0, bytes = 0;
+  size_t off_red = 0, off_plain = 0, off_desc = 0, off_rows = 0, off_bad = 0, off_gj = 0, off_pool = 0, bytes = 0;
 };
 
 static size_t align256(size_t b) { return (b + 255) / 256 * 256; }
@@ -1719,7 +1714,8 @@ static void plan_sym_inverse(const qax_problem* p, size_t elem_bytes, SymInvPlan
   P.off_plain = align256(P.red.size() * sizeof(MatDesc));
   P.off_desc = P.off_plain + align256(P.plain.size() * sizeof(MatDesc));
   P.off_rows = P.off_desc + align256(P.desc.size() * sizeof(SymInvDesc));
-  P.off_gj = P.off_rows + align256(P.rows.size() * sizeof(SymInvRow));
+  P.off_bad = P.off_rows + align256(P.rows.size() * sizeof(SymInvRow));
+  P.off_gj = P.off_bad + 256;
   const size_t gj = std::max(P.red.empty() ? 0 : gj_work_bytes((int)P.red.size(), P.nmax_red),
                              P.plain.empty() ? 0 : gj_work_bytes((int)P.plain.size(), P.nmax_plain));
   P.off_pool = P.off_gj + align256(gj);
@@ -2016,42 +2012,57 @@ static hipError_t invert_blocks_sym(qax_problem* p, const SymInvPlan& P, char* w
     e = hipMemcpyAsync(d_plain, P.plain.data(), P.plain.size() * sizeof(MatDesc), hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return e;
   timing_begin(p, QAX_K_INVERT);
-  // FP64: on the diagonal, again with interchanges where that fails; the single
-  // layer, whose blocks all need interchanges, at once with them (the attempt
-  // took 0.2 to 0.7 ms)
-  auto invert = [&](typename Cx<T>::V* mats, const MatDesc* d_md, int batch, int nmax, auto&& fill) {
-    hipError_t ie = fill();
-    if (ie != hipSuccess) return ie;
-    if constexpr (sizeof(T) == 8)
-      if (p->form() != QAX_SINGLE_LAYER) {
-        bool failed = false;
-        ie = gjd_invert(p, mats, d_md, batch, nmax, gjw, &failed);
-        if (ie != hipSuccess || !failed) return ie;
-        ie = fill();
-        if (ie != hipSuccess) return ie;
-      }
-    return gj_invert<T>(p, (T*)mats, d_md, batch, nmax, gjw, true);
+  typedef typename Cx<T>::V V;
+  const int n_red = (int)P.red.size(), n_plain = (int)P.plain.size();
+  auto reduce = [&]() {
+    hipLaunchKernelGGL(sym_reduce_kernel<T>, dim3((unsigned)P.rows.size()), dim3(256), 0, s, d_rows, d_desc,
+                       (const double2*)p->d_B, (V*)pool);
+    return hipGetLastError();
   };
-  if (!P.red.empty()) {
-    e = invert((typename Cx<T>::V*)pool, d_red, (int)P.red.size(), P.nmax_red, [&]() {
-      hipLaunchKernelGGL(sym_reduce_kernel<T>, dim3((unsigned)P.rows.size()), dim3(256), 0, s, d_rows, d_desc,
-                         (const double2*)p->d_B, (typename Cx<T>::V*)pool);
-      return hipGetLastError();
+  auto expand = [&]() {
+    hipLaunchKernelGGL(sym_expand_kernel<T>, dim3((unsigned)P.rows.size()), dim3(256), 0, s, d_rows, d_desc,
+                       (const V*)pool, inv_pool, inv32, red32);
+    return hipGetLastError();
+  };
+  auto fill = [&]() {
+    if (sizeof(T) == 4) return hipSuccess;      // (B rounded into the pool by the caller)
+    return plain_runs(P, [&](int64_t off, int64_t elems) {
+      return hipMemcpyAsync(inv_pool + off, (const double2*)p->d_B + off, (size_t)elems * 16,
+                            hipMemcpyDeviceToDevice, s);
     });
-    if (e == hipSuccess) {
-      hipLaunchKernelGGL(sym_expand_kernel<T>, dim3((unsigned)P.rows.size()), dim3(256), 0, s, d_rows,
-                         d_desc, (const typename Cx<T>::V*)pool, inv_pool, inv32, red32);
-      e = hipGetLastError();
+  };
+  bool red = n_red > 0, plain = n_plain > 0;     // still to be inverted
+  // FP64: on the diagonal, again with interchanges where that fails (known
+  // once everything is enqueued: one wait); the single layer, whose blocks all
+  // need interchanges, at once with them (the attempt took 0.2 to 0.7 ms)
+  if constexpr (sizeof(T) == 8)
+    if (p->form() != QAX_SINGLE_LAYER) {
+      int* bad = (int*)(work + P.off_bad);
+      hipLaunchKernelGGL(gjd_clear_kernel, dim3(1), dim3(4), 0, s, bad);
+      if (red) {
+        e = reduce();
+        if (e == hipSuccess) e = gjd_invert(p, (V*)pool, d_red, n_red, P.nmax_red, gjw, bad);
+        if (e == hipSuccess) e = expand();
+      }
+      if (plain && e == hipSuccess) {
+        e = fill();
+        if (e == hipSuccess) e = gjd_invert(p, inv_pool, d_plain, n_plain, P.nmax_plain, gjw, bad + 2);
+      }
+      int h[4] = {0, 0, 0, 0};
+      if (e == hipSuccess) e = hipMemcpyAsync(h, bad, sizeof(h), hipMemcpyDeviceToHost, s);
+      if (e == hipSuccess) e = hipStreamSynchronize(s);
+      red = red && (h[0] || h[1]);
+      plain = plain && (h[2] || h[3]);
     }
+  if (red && e == hipSuccess) {
+    e = reduce();
+    if (e == hipSuccess) e = gj_invert<T>(p, pool, d_red, n_red, P.nmax_red, gjw, true);
+    if (e == hipSuccess) e = expand();
   }
-  if (e == hipSuccess && !P.plain.empty())
-    e = invert(inv_pool, d_plain, (int)P.plain.size(), P.nmax_plain, [&]() {
-      if (sizeof(T) == 4) return hipSuccess;      // (B rounded into the pool by the caller)
-      return plain_runs(P, [&](int64_t off, int64_t elems) {
-        return hipMemcpyAsync(inv_pool + off, (const double2*)p->d_B + off, (size_t)elems * 16,
-                              hipMemcpyDeviceToDevice, s);
-      });
-    });
+  if (plain && e == hipSuccess) {
+    e = fill();
+    if (e == hipSuccess) e = gj_invert<T>(p, (T*)inv_pool, d_plain, n_plain, P.nmax_plain, gjw, true);
+  }
   timing_end(p, QAX_K_INVERT);
   return e;
 }
