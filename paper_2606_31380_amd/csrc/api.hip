@@ -1010,7 +1010,7 @@ static qax_status solve_core(qax_problem* p, qax_prec prec, const double* dirs, 
     return hipMemcpyAsync(p->h_flags + j, G.notdone + j, 4, hipMemcpyDeviceToHost, p->stream);
   };
   const bool graphs = p->use_graphs && !p->timing;
-  if (nrhs >= 4) QCHECK(ensure_gemm_tasks(p), "block GEMM tiles");
+  if (nrhs > 1) QCHECK(ensure_gemm_tasks(p), "block product tiles");
   if (graphs) {
     char key[512];
     std::snprintf(key, sizeof(key), "%llu %d %d %d %d %p %p %p %p %p %p %p %p %p %p %p %p",

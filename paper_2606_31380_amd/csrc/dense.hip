@@ -21,75 +21,48 @@
 namespace qax {
 
 // ---------------------------------------------------------------- block apply
-// LPR lanes per row (64: one wavefront per row; 32 or 16 for short rows, two
-// or four rows per wavefront); each lane loads VEC consecutive complex entries
-// per step (block orders are multiples of 16).
-template <typename MT, int NRC, int VEC, int LPR = 64>
+// One right-hand side, FP64: one wavefront per row, VEC consecutive complex
+// entries per lane and step.
+template <int VEC>
 __global__ __launch_bounds__(256) void block_gemv_kernel(
     const BodyDev* __restrict__ bodies, const BlockDev* __restrict__ blocks,
-    const int32_t* __restrict__ node_body, const MT* __restrict__ pool, int64_t N,
-    const double2* __restrict__ v, int nrhs, double2* __restrict__ out, int accumulate,
+    const int32_t* __restrict__ node_body, const double* __restrict__ pool, int64_t N,
+    const double2* __restrict__ v, double2* __restrict__ out, int accumulate,
     const int32_t* __restrict__ seg_active) {
-  typedef MT vec_t __attribute__((ext_vector_type(2 * VEC)));
-  const int lane = threadIdx.x & (LPR - 1);
-  const int64_t row = (int64_t)blockIdx.x * (256 / LPR) + (threadIdx.x / LPR);
-  const int rc0 = blockIdx.y * NRC;
+  typedef double vec_t __attribute__((ext_vector_type(2 * VEC)));
+  const int lane = threadIdx.x & 63;
+  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= N) return;
-  const int b = node_body[row];
-  const BodyDev& B = bodies[b];
-  if (seg_active) {
-    // converged lockstep segments: their input is zero, so is the output
-    bool any = false;
-    for (int r = rc0; r < rc0 + NRC && r < nrhs; ++r) any = any || seg_active[B.problem * nrhs + r] != 0;
-    if (!any) {
-      if (lane == 0 && !accumulate)
-        for (int r = rc0; r < rc0 + NRC && r < nrhs; ++r) out[row * nrhs + r] = make_double2(0.0, 0.0);
-      return;
-    }
+  const BodyDev& B = bodies[node_body[row]];
+  if (seg_active && seg_active[B.problem] == 0) {
+    // a converged lockstep segment: its input is zero, so is the output
+    if (lane == 0 && !accumulate) out[row] = make_double2(0.0, 0.0);
+    return;
   }
   const BlockDev& K = blocks[B.block];
   const int n = K.n;
-  const int lr = (int)(row - B.off);
-  const MT* a = pool + 2 * (K.elem_off + (int64_t)lr * n);
-  const double2* vb = v + B.off * nrhs;
-  double ar[NRC], ai[NRC];
-#pragma unroll
-  for (int r = 0; r < NRC; ++r) { ar[r] = 0.0; ai[r] = 0.0; }
-  for (int j0 = lane * VEC; j0 < n; j0 += LPR * VEC) {
-    const vec_t av = *(const vec_t*)(a + 2 * j0);
+  const double* a = pool + 2 * (K.elem_off + (row - B.off) * n);
+  const double2* vb = v + B.off;
+  double ar = 0.0, ai = 0.0;
+  for (int j = lane * VEC; j < n; j += 64 * VEC) {
+    const vec_t m = *(const vec_t*)(a + 2 * j);
 #pragma unroll
     for (int q = 0; q < VEC; ++q) {
-      const double mr = (double)av[2 * q], mi = (double)av[2 * q + 1];
-      const int j = j0 + q;
-#pragma unroll
-      for (int r = 0; r < NRC; ++r) {
-        if (rc0 + r < nrhs) {
-          const double2 x = vb[(int64_t)j * nrhs + rc0 + r];
-          ar[r] += mr * x.x - mi * x.y;
-          ai[r] += mr * x.y + mi * x.x;
-        }
-      }
+      const double2 x = vb[j + q];
+      ar += m[2 * q] * x.x - m[2 * q + 1] * x.y;
+      ai += m[2 * q] * x.y + m[2 * q + 1] * x.x;
     }
   }
 #pragma unroll
-  for (int r = 0; r < NRC; ++r) {
-#pragma unroll
-    for (int off = LPR / 2; off > 0; off >>= 1) {
-      ar[r] += __shfl_xor(ar[r], off);
-      ai[r] += __shfl_xor(ai[r], off);
-    }
+  for (int off = 32; off > 0; off >>= 1) {
+    ar += __shfl_xor(ar, off);
+    ai += __shfl_xor(ai, off);
   }
   if (lane == 0) {
-#pragma unroll
-    for (int r = 0; r < NRC; ++r) {
-      if (rc0 + r < nrhs) {
-        const int64_t e = row * nrhs + rc0 + r;
-        double2 o = accumulate ? out[e] : make_double2(0.0, 0.0);
-        o.x += ar[r];
-        o.y += ai[r];
-        out[e] = o;
-      }
-    }
+    double2 o = accumulate ? out[row] : make_double2(0.0, 0.0);
+    o.x += ar;
+    o.y += ai;
+    out[row] = o;
   }
 }
 
@@ -174,16 +147,15 @@ static void gemv_f32_lds_launch(hipStream_t s, const BodyDev* bodies, const Bloc
                      (double2*)out, acc ? 1 : 0, seg_active);
 }
 
-template <typename MT, int NRC, int VEC>
-static void gemv_launch(qax_problem* p, const MT* pool, const double* v, double* out, int nrhs,
-                        bool acc) {
-  dim3 grid((unsigned)((p->N + 3) / 4), (unsigned)((nrhs + NRC - 1) / NRC));
-  hipLaunchKernelGGL((block_gemv_kernel<MT, NRC, VEC>), grid, dim3(256), 0, p->stream, p->d_bodies,
-                     p->d_blocks, p->d_node_body, pool, p->N, (const double2*)v, nrhs,
-                     (double2*)out, acc ? 1 : 0, p->seg_active);
+template <int VEC>
+static void gemv_launch(hipStream_t s, const BodyDev* bodies, const BlockDev* blocks, const int32_t* node_body,
+                        const double* pool, int64_t N, const double* v, double* out, bool acc,
+                        const int32_t* seg_active) {
+  hipLaunchKernelGGL((block_gemv_kernel<VEC>), dim3((unsigned)((N + 3) / 4)), dim3(256), 0, s, bodies, blocks,
+                     node_body, pool, N, (const double2*)v, (double2*)out, acc ? 1 : 0, seg_active);
 }
 
-hipError_t launch_block_gemm(qax_problem* p, int inverse, int prec, const double* v, double* out,
+hipError_t launch_block_mm(qax_problem* p, int inverse, int prec, const double* v, double* out,
                              int nrhs, bool accumulate);
 
 static void launch_sym_apply(qax_problem* p, int prec, const double* v, double* out, bool accumulate);
@@ -211,18 +183,17 @@ hipError_t launch_block_apply(qax_problem* p, int inverse, int prec, const doubl
     timing_end(p, kind);
     return hipGetLastError();
   }
-  if (nrhs >= 4) {
-    // several right-hand sides: batched complex GEMM on the matrix cores
+  if (nrhs > 1) {
+    // several right-hand sides: on the matrix cores
     timing_begin(p, kind);
-    hipError_t e = launch_block_gemm(p, inverse, prec, v, out, nrhs, accumulate);
+    hipError_t e = launch_block_mm(p, inverse, prec, v, out, nrhs, accumulate);
     timing_end(p, kind);
     return e;
   }
   timing_begin(p, kind);
   if (prec == QAX_MIXED) {
     const float* pool = inverse ? p->d_Binv32 : p->d_B32;
-    if (nrhs > 1) gemv_launch<float, 4, 1>(p, pool, v, out, nrhs, accumulate);
-    else if (p->tune.gemv_vec[1] == 4)
+    if (p->tune.gemv_vec[1] == 4)
       gemv_f32_lds_launch<4>(p->stream, p->d_bodies, p->d_blocks, p->d_node_body, pool, p->N, v, out,
                              accumulate, p->seg_active);
     else if (p->tune.gemv_vec[1] == 2)
@@ -233,22 +204,18 @@ hipError_t launch_block_apply(qax_problem* p, int inverse, int prec, const doubl
                              accumulate, p->seg_active);
   } else {
     const double* pool = inverse ? p->d_Binv : p->d_B;
-    if (nrhs > 1) gemv_launch<double, 4, 1>(p, pool, v, out, nrhs, accumulate);
-    else if (p->tune.gemv_vec[0] == 2) gemv_launch<double, 1, 2>(p, pool, v, out, nrhs, accumulate);
-    else gemv_launch<double, 1, 1>(p, pool, v, out, nrhs, accumulate);
+    if (p->tune.gemv_vec[0] == 2)
+      gemv_launch<2>(p->stream, p->d_bodies, p->d_blocks, p->d_node_body, pool, p->N, v, out, accumulate,
+                     p->seg_active);
+    else
+      gemv_launch<1>(p->stream, p->d_bodies, p->d_blocks, p->d_node_body, pool, p->N, v, out, accumulate,
+                     p->seg_active);
   }
   timing_end(p, kind);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- block apply, several RHS (MFMA)
-// Y_b = M_b V_b for every body with V, Y node-major (RHS fastest).  The
-// complex product is the real product A' B' with A' = M_b viewed as a real
-// n x 2n matrix (interleaved storage, read in place) and B' the 2n x 2nrhs
-// expansion of V: B'[2j] = (Re V_j0, Im V_j0, ...), B'[2j+1] = (-Im V_j0,
-// Re V_j0, ...), built while staging V in LDS.  64 x 64 real output tiles per
-// workgroup of 4 wavefronts (32 x 32 each = 2 x 2 MFMA 16x16 tiles), K steps
-// of 16 staged through LDS; MFMA 16x16x4 in FP64 (B) or FP32 (FP32 inverse).
 template <typename T>
 struct MfmaAcc;
 template <>
@@ -270,89 +237,127 @@ struct MfmaAcc<float> {
   static __device__ __forceinline__ int row(int lane, int e) { return 4 * (lane >> 4) + e; }
 };
 
-template <typename T>
-__global__ __launch_bounds__(256) void block_gemm_kernel(
-    const GemmTask* __restrict__ tasks, const BodyDev* __restrict__ bodies,
-    const BlockDev* __restrict__ blocks, const T* __restrict__ pool,
-    const double* __restrict__ v, int nrhs, double* __restrict__ out, int accumulate) {
-  typedef typename MfmaAcc<T>::v4 v4;
+// Y_b = M_b V_b for every body with V, Y node-major (RHS fastest): a wavefront
+// per 16 rows, whose entries go from memory straight into the first operand's
+// registers (row lane % 16, VEC entries from VEC (lane / 16) on, the next 32
+// columns' in flight), NT groups of 8 right-hand sides from LDS as the second
+// (real and imaginary parts in columns c and c + 8): out += Re(m) [Re v, Im v] +
+// Im(m) [-Im v, Re v], all in FP64.  Bound by the matrix's bytes up to 8
+// right-hand sides (16 in FP64), by the matrix cores beyond.  Tiles of 64 x 64
+// real outputs with both operands in LDS (and FP32 sums of FP32 matrices) cost
+// every count the time of 32: 4913 blocks of order 96, 8 right-hand sides
+// 525 -> 177 us (4.1 TB/s; FP32 265 -> 100), 32: 570 -> 377 (313 -> 307), 2:
+// 237 -> 167 (230 -> 96; four right-hand sides a row on the vector units); 343
+// blocks of order 768, 8: 1858 -> 663 (896 -> 354), 64: 3494 -> 2186 (1694 ->
+// 1718).
+template <typename MT, int VEC, int NT>
+__global__ __launch_bounds__(256) void block_mm_kernel(
+    const GemmTask* __restrict__ tasks, const BodyDev* __restrict__ bodies, const BlockDev* __restrict__ blocks,
+    const MT* __restrict__ pool, const double2* __restrict__ v, int nrhs, double2* __restrict__ out,
+    int accumulate, const int32_t* __restrict__ seg_active) {
+  typedef MfmaAcc<double> MA;
+  typedef MT vec_t __attribute__((ext_vector_type(2 * VEC)));
+  constexpr int KC = 32, NL = KC / (4 * VEC), NR = 8 * NT;   // (orders are multiples of 32)
   const GemmTask task = tasks[blockIdx.x];
   const BodyDev& Bd = bodies[task.body];
   const BlockDev& K = blocks[Bd.block];
-  const int n = K.n;
-  const int ncol = 2 * nrhs;                  // real columns of V and Y
-  const int c0 = blockIdx.y * 64;
-  const int row0 = task.row0;
-  const T* A = pool + 2 * K.elem_off;         // real n x 2n, row stride 2n
-  const double* Vb = v + 2 * Bd.off * nrhs;   // real n x 2 nrhs
-  double* Yb = out + 2 * Bd.off * nrhs;
-  __shared__ T As[16][64 + 1];
-  __shared__ T Bs[16][64 + 1];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
-  v4 acc[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[a][b][e] = 0;
-  for (int k0 = 0; k0 < 2 * n; k0 += 16) {
-    // A tile: rows row0..row0+63, real columns k0..k0+15
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int e = tid + 256 * q;
-      const int rr = e >> 4, kk = e & 15;
-      const int i = row0 + rr;
-      As[kk][rr] = (i < n) ? A[(int64_t)i * 2 * n + k0 + kk] : (T)0;
-    }
-    // B' tile: real rows k0..k0+15 (complex rows k0/2..k0/2+7), columns c0..c0+63
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int e = tid + 256 * q;             // 512 = 8 complex rows x 64 columns
-      const int jr = e >> 6, cc = e & 63;
-      const int c = c0 + cc;
-      const int j = k0 / 2 + jr;
-      T re = 0, alt = 0;
-      if (c < ncol) {
-        const double x = Vb[(int64_t)j * ncol + c];
-        const double y = Vb[(int64_t)j * ncol + (c ^ 1)];
-        re = (T)x;
-        alt = (c & 1) ? (T)y : (T)(-y);        // row 2j+1: (-Im, Re) pairs
+  const int n = K.n, r0 = blockIdx.y * NR;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 15, kq = lane >> 4;
+  const int row = task.row0 + 16 * wave;
+  double2* dst = out + Bd.off * nrhs;
+  if (seg_active) {
+    // converged lockstep segments: their input is zero, so is the output
+    bool any = false;
+    for (int r = r0; r < min(r0 + NR, nrhs); ++r) any = any || seg_active[Bd.problem * nrhs + r] != 0;
+    if (!any) {
+      for (int e = tid; e < 64 * NR && !accumulate; e += 256) {
+        const int i = task.row0 + e / NR, r = r0 + e % NR;
+        if (i < n && r < nrhs) dst[(int64_t)i * nrhs + r] = make_double2(0.0, 0.0);
       }
-      Bs[2 * jr][cc] = re;
-      Bs[2 * jr + 1][cc] = alt;
+      return;
     }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; kk += 4) {
-      const int kr = kk + (lane >> 4), ci = lane & 15;
-      T af[2], bf[2];
-#pragma unroll
-      for (int a = 0; a < 2; ++a) af[a] = As[kr][wr + 16 * a + ci];
-#pragma unroll
-      for (int b = 0; b < 2; ++b) bf[b] = Bs[kr][wc + 16 * b + ci];
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = MfmaAcc<T>::mma(af[a], bf[b], acc[a][b]);
-    }
-    __syncthreads();
   }
-  // accumulator element e of the lane holds column lane % 16 of the tile
+  const MT* a = pool + 2 * (K.elem_off + (int64_t)min(row + col, n - 1) * n + VEC * kq);
+  const double2* vb = v + Bd.off * nrhs;
+  __shared__ double2 xs[2][KC][NR];
+  vec_t ra[NL], rn[NL];
+  double2 px[NT];
+  auto load_a = [&](int k0, vec_t* r) {
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+    for (int s = 0; s < NL; ++s) r[s] = *(const vec_t*)(a + 2 * (k0 + 4 * VEC * s));
+  };
+  auto load_x = [&](int k0) {
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int t = 0; t < NT; ++t) {
+      const int e = tid + 256 * t, j = e / NR, r = r0 + e % NR;
+      px[t] = r < nrhs ? vb[(int64_t)(k0 + j) * nrhs + r] : make_double2(0.0, 0.0);
+    }
+  };
+  MA::v4 acc[NT];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int i = row0 + wr + 16 * a + MfmaAcc<T>::row(lane, e);
-        const int c = c0 + wc + 16 * b + (lane & 15);
-        if (i < n && c < ncol) {
-          double* y = Yb + (int64_t)i * ncol + c;
-          *y = (accumulate ? *y : 0.0) + (double)acc[a][b][e];
+  for (int t = 0; t < NT; ++t) acc[t] = MA::v4{0.0, 0.0, 0.0, 0.0};
+  const uint32_t flip = col < 8 ? 0x80000000u : 0u;   // sign of the second operand's columns
+  load_a(0, ra);
+  load_x(0);
+  int buf = 0;
+  for (int k0 = 0; k0 < n; k0 += KC) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int e = tid + 256 * t;
+      xs[buf][e / NR][e % NR] = px[t];
+    }
+    __syncthreads();
+    if (k0 + KC < n) {
+      load_a(k0 + KC, rn);
+      load_x(k0 + KC);
+    }
+#pragma unroll
+    for (int s = 0; s < NL; ++s)
+#pragma unroll
+      for (int u = 0; u < VEC; ++u) {
+        const double mr = (double)ra[s][2 * u], mi = (double)ra[s][2 * u + 1];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const double* m = (const double*)&xs[buf][4 * VEC * s + VEC * kq + u][8 * t + (col & 7)];
+          const double x = m[1 - (col >> 3)];
+          acc[t] = MA::mma(mr, m[col >> 3], acc[t]);
+          acc[t] = MA::mma(mi, __hiloint2double(__double2hiint(x) ^ flip, __double2loint(x)), acc[t]);
         }
       }
+#pragma unroll
+    for (int s = 0; s < NL; ++s) ra[s] = rn[s];
+    buf ^= 1;
+  }
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const double re = acc[t][e], im = __shfl_down(re, 8);
+      const int i = row + MA::row(lane, e), r = r0 + 8 * t + col;
+      if (i < n && col < 8 && r < nrhs) {
+        double2 o = accumulate ? dst[(int64_t)i * nrhs + r] : make_double2(0.0, 0.0);
+        dst[(int64_t)i * nrhs + r] = make_double2(o.x + re, o.y + im);
+      }
+    }
+}
+
+template <typename MT, int VEC>
+static void block_mm_launch(hipStream_t s, const GemmTask* tasks, int ntasks, const BodyDev* bodies,
+                            const BlockDev* blocks, const void* pool, const double* v, int nrhs, double* out,
+                            bool accumulate, const int32_t* seg_active) {
+  auto go = [&](auto nt) {
+    constexpr int NT = decltype(nt)::value;
+    hipLaunchKernelGGL((block_mm_kernel<MT, VEC, NT>), dim3((unsigned)ntasks, (unsigned)((nrhs + 8 * NT - 1) / (8 * NT))),
+                       dim3(256), 0, s, tasks, bodies, blocks, (const MT*)pool, (const double2*)v, nrhs,
+                       (double2*)out, accumulate ? 1 : 0, seg_active);
+  };
+  // as few passes over the matrix as 32 right-hand sides each allow, evenly wide
+  // (16 at a time instead: 24 right-hand sides 413 us against 350)
+  const int passes = (nrhs + 31) / 32, nt = (nrhs + 8 * passes - 1) / (8 * passes);
+  if (nt == 1) go(std::integral_constant<int, 1>{});
+  else if (nt == 2) go(std::integral_constant<int, 2>{});
+  else if (nt == 3) go(std::integral_constant<int, 3>{});
+  else go(std::integral_constant<int, 4>{});
 }
 
 // Row tiles of the block GEMM (built once per geometry; synchronous copy, so
@@ -370,44 +375,19 @@ hipError_t ensure_gemm_tasks(qax_problem* p) {
                    hipMemcpyHostToDevice);
 }
 
-hipError_t launch_block_gemm(qax_problem* p, int inverse, int prec, const double* v, double* out,
+hipError_t launch_block_mm(qax_problem* p, int inverse, int prec, const double* v, double* out,
                              int nrhs, bool accumulate) {
   hipError_t e = ensure_gemm_tasks(p);
   if (e != hipSuccess) return e;
-  dim3 grid((unsigned)p->gemm_tasks.size(), (unsigned)((2 * nrhs + 63) / 64));
   const GemmTask* t = (const GemmTask*)p->d_gemm_tasks;
+  const int nt = (int)p->gemm_tasks.size();
   if (prec == QAX_MIXED)
-    hipLaunchKernelGGL(block_gemm_kernel<float>, grid, dim3(256), 0, p->stream, t, p->d_bodies,
-                       p->d_blocks, inverse ? p->d_Binv32 : p->d_B32, v, nrhs, out, accumulate ? 1 : 0);
+    block_mm_launch<float, 2>(p->stream, t, nt, p->d_bodies, p->d_blocks, inverse ? p->d_Binv32 : p->d_B32, v, nrhs,
+                              out, accumulate, p->seg_active);
   else
-    hipLaunchKernelGGL(block_gemm_kernel<double>, grid, dim3(256), 0, p->stream, t, p->d_bodies,
-                       p->d_blocks, inverse ? p->d_Binv : p->d_B, v, nrhs, out, accumulate ? 1 : 0);
+    block_mm_launch<double, 1>(p->stream, t, nt, p->d_bodies, p->d_blocks, inverse ? p->d_Binv : p->d_B, v, nrhs,
+                               out, accumulate, p->seg_active);
   return hipGetLastError();
-}
-
-// Block-diagonal products over caller-built tables (the lattice apply's
-// per-frequency matrices): rows = sum of the orders, every order a multiple
-// of 16.
-template <typename MT, int NRC, int VEC, int LPR>
-static void gemv_tables_launch(hipStream_t s, const BodyDev* bodies, const BlockDev* blocks,
-                               const int32_t* node_body, const void* pool, int64_t rows,
-                               const double2* v, int nrhs, double2* out, int acc) {
-  dim3 grid((unsigned)((rows + 256 / LPR - 1) / (256 / LPR)), (unsigned)((nrhs + NRC - 1) / NRC));
-  hipLaunchKernelGGL((block_gemv_kernel<MT, NRC, VEC, LPR>), grid, dim3(256), 0, s, bodies, blocks,
-                     node_body, (const MT*)pool, rows, v, nrhs, out, acc, nullptr);
-}
-
-template <typename MT, int NRC, int VEC>
-static void gemv_tables_lpr(hipStream_t s, const BodyDev* bodies, const BlockDev* blocks,
-                            const int32_t* node_body, const void* pool, int64_t rows, int order,
-                            const double2* v, int nrhs, double2* out, int acc) {
-  // short rows: up to four loads per lane, several rows per wavefront
-  if (order <= 64 * VEC)
-    gemv_tables_launch<MT, NRC, VEC, 16>(s, bodies, blocks, node_body, pool, rows, v, nrhs, out, acc);
-  else if (order <= 128 * VEC)
-    gemv_tables_launch<MT, NRC, VEC, 32>(s, bodies, blocks, node_body, pool, rows, v, nrhs, out, acc);
-  else
-    gemv_tables_launch<MT, NRC, VEC, 64>(s, bodies, blocks, node_body, pool, rows, v, nrhs, out, acc);
 }
 
 // One right-hand side, square blocks of one order (a multiple of 32) one after another: a
@@ -468,41 +448,31 @@ static void table_gemv_launch(hipStream_t s, const void* pool, int order, int64_
                      s, (const MT*)pool, order, rows, v, out, acc);
 }
 
-hipError_t launch_gemv_tables(hipStream_t s, const BodyDev* bodies, const BlockDev* blocks,
-                              const int32_t* node_body, const void* pool, bool f32, int64_t rows,
-                              int order, const double* v, int nrhs, double* out, bool accumulate) {
+// Block-diagonal products over caller-built tables (the lattice apply's
+// per-frequency matrices): rows = sum of the orders, every order a multiple
+// of 32.
+hipError_t launch_table_product(hipStream_t s, const GemmTask* tasks, int ntasks, const BodyDev* bodies,
+                                const BlockDev* blocks, const int32_t* node_body, const void* pool, bool f32,
+                                int64_t rows, int order, const double* v, int nrhs, double* out, bool accumulate) {
   const double2* vv = (const double2*)v;
   double2* oo = (double2*)out;
   const int acc = accumulate ? 1 : 0;
-  // one right-hand side, short rows: two rows per group of lanes, 32 lanes, 16
-  // below 128 FP32 entries (order 64: 38.5 us against 56 with 32); longer rows
-  // keep one row per wavefront (order 512: 253 us here against 247, 768: 569
-  // against 539), FP32 ones with their input in LDS (281 us both at 768)
-  if (nrhs == 1 && order <= 256) {
+  if (nrhs > 1) {
+    if (f32) block_mm_launch<float, 2>(s, tasks, ntasks, bodies, blocks, pool, v, nrhs, out, accumulate, nullptr);
+    else block_mm_launch<double, 1>(s, tasks, ntasks, bodies, blocks, pool, v, nrhs, out, accumulate, nullptr);
+  } else if (order <= 256) {
+    // short rows: two rows per group of lanes, 32 lanes, 16 below 128 FP32
+    // entries (order 64: 38.5 us against 56 with 32); longer rows keep one row
+    // per wavefront (order 512: 253 us here against 247, 768: 569 against
+    // 539), FP32 ones with their input in LDS (281 us both at 768)
     if (!f32) table_gemv_launch<double, 1, 32, 2>(s, pool, order, rows, vv, oo, acc);
     else if (order < 128) table_gemv_launch<float, 2, 16, 2>(s, pool, order, rows, vv, oo, acc);
     else table_gemv_launch<float, 2, 32, 2>(s, pool, order, rows, vv, oo, acc);
-  } else if (nrhs == 1) {
-    if (f32) gemv_f32_lds_launch<2>(s, bodies, blocks, node_body, (const float*)pool, rows, v, out, accumulate, nullptr);
-    else gemv_tables_launch<double, 1, 1, 64>(s, bodies, blocks, node_body, pool, rows, vv, nrhs, oo, acc);
   } else if (f32) {
-    gemv_tables_lpr<float, 4, 1>(s, bodies, blocks, node_body, pool, rows, order, vv, nrhs, oo, acc);
+    gemv_f32_lds_launch<2>(s, bodies, blocks, node_body, (const float*)pool, rows, v, out, accumulate, nullptr);
   } else {
-    gemv_tables_lpr<double, 4, 1>(s, bodies, blocks, node_body, pool, rows, order, vv, nrhs, oo, acc);
+    gemv_launch<1>(s, bodies, blocks, node_body, (const double*)pool, rows, v, out, accumulate, nullptr);
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_gemm_tables(hipStream_t s, const GemmTask* tasks, int ntasks,
-                              const BodyDev* bodies, const BlockDev* blocks, const void* pool,
-                              bool f32, const double* v, int nrhs, double* out, bool accumulate) {
-  dim3 grid((unsigned)ntasks, (unsigned)((2 * nrhs + 63) / 64));
-  if (f32)
-    hipLaunchKernelGGL(block_gemm_kernel<float>, grid, dim3(256), 0, s, tasks, bodies, blocks,
-                       (const float*)pool, v, nrhs, out, accumulate ? 1 : 0);
-  else
-    hipLaunchKernelGGL(block_gemm_kernel<double>, grid, dim3(256), 0, s, tasks, bodies, blocks,
-                       (const double*)pool, v, nrhs, out, accumulate ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -15,8 +15,8 @@
 //   mu^_xi = sum_t mu_t e^{-2 pi i xi.t / L}          (per apply)
 //   w_t' = (1/F) sum_xi e^{+2 pi i xi.t' / L} T_xi mu^_xi,  F = L0 L1 L2.
 // The transforms are direct DFTs along one axis at a time (the periods are
-// small); the products reuse the block-diagonal GEMV / MFMA GEMM kernels
-// with one "block" per frequency.  Memory per apply: F n_b^2 table entries
+// small); the products reuse the block-diagonal kernels with one
+// "block" per frequency.  Memory per apply: F n_b^2 table entries
 // read once (16 B FP64, 8 B FP32) against N^2 kernel evaluations for the
 // direct pair sum.
 #include <algorithm>
@@ -347,11 +347,7 @@ hipError_t launch_lattice_apply(qax_problem* p, int prec, const double* mu, doub
   const int kind = f32 ? QAX_K_LATTICE_F32 : QAX_K_LATTICE_F64;
   const void* pool = f32 ? (const void*)t.T32 : (const void*)t.T64;
   timing_begin(p, kind);
-  if (nrhs >= 4)
-    e = launch_gemm_tables(s, t.d_ftasks, t.nftasks, t.d_fbodies, t.d_fblocks, pool, f32,
-                           (const double*)W1, nrhs, (double*)W2, false);
-  else
-    e = launch_gemv_tables(s, t.d_fbodies, t.d_fblocks, t.d_frow, pool, f32, t.F * t.nb, t.nb,
+  e = launch_table_product(s, t.d_ftasks, t.nftasks, t.d_fbodies, t.d_fblocks, t.d_frow, pool, f32, t.F * t.nb, t.nb,
                            (const double*)W1, nrhs, (double*)W2, false);
   timing_end(p, kind);
   if (e != hipSuccess) return e;
