@@ -1085,6 +1085,8 @@ static void plan_sym_supers(qax_problem* p, int pi, int s, int64_t cap, int cu_c
     return S.blk_body_lo[I] == S.blk_body_hi[I] && S.blk_body_lo[J] == S.blk_body_hi[J] &&
            S.blk_body_lo[I] == S.blk_body_lo[J];
   };
+  // block rows [i0, i1) and blocks from j0 on share no body (bodies in node order)
+  auto apart = [&](int i0, int i1, int j0) { return j0 >= i1 && S.blk_body_lo[j0] > S.blk_body_hi[i1 - 1]; };
   // squares by their corner and cost; the super-tasks themselves once the
   // order is known
   struct Corner { int32_t pr, r0, c0; };
@@ -1103,6 +1105,14 @@ static void plan_sym_supers(qax_problem* p, int pi, int s, int64_t cap, int cu_c
       for (int c0 = r0; c0 < g1; c0 += s) {
         double c = 0.0;
         int visits = 0;
+        if (apart(r0, std::min(r0 + s, g1), c0)) {   // no body on both sides: the whole square
+          double nr = 0.0, nc = 0.0;
+          for (int I = r0; I < std::min(r0 + s, g1); ++I) nr += S.blocks[I].n;
+          for (int J = c0; J < std::min(c0 + s, g1); ++J) nc += S.blocks[J].n;
+          corner.push_back(Corner{pr, r0, c0});
+          cost.push_back(nr * nc);
+          continue;
+        }
         for (int I = r0; I < std::min(r0 + s, g1); ++I)
           for (int J = r0 == c0 ? I : c0; J < std::min(c0 + s, g1); ++J) {
             if (same_body(I, J)) continue;
@@ -1156,9 +1166,10 @@ static void plan_sym_supers(qax_problem* p, int pi, int s, int64_t cap, int cu_c
     T.problem = C.pr;
     T.k = p->k[C.pr];
     T.skip = 0;
-    for (int ii = 0; ii < T.ni; ++ii)
-      for (int jj = T.diag ? ii : 0; jj < T.nj; ++jj)
-        if (same_body(C.r0 + ii, C.c0 + jj)) T.skip |= 1ull << (ii * SYM_SMAX + jj);
+    if (!apart(C.r0, C.r0 + T.ni, C.c0))
+      for (int ii = 0; ii < T.ni; ++ii)
+        for (int jj = T.diag ? ii : 0; jj < T.nj; ++jj)
+          if (same_body(C.r0 + ii, C.c0 + jj)) T.skip |= 1ull << (ii * SYM_SMAX + jj);
     T.toff = T.soff = 0;
     T.c0 = 0;
     T.c1 = SYM_T;
@@ -1222,6 +1233,17 @@ static void plan_sym_supers(qax_problem* p, int pi, int s, int64_t cap, int cu_c
       else std::copy(lp, lp + nblk + 1, fill.begin());
       for (int64_t i = P.launch_super[l]; i < P.launch_super[l + 1]; ++i) {
         const SymSuper& T = P.supers[i];
+        if (T.skip == 0 && !T.diag) {      // every row and column of the square
+          for (int ii = 0; ii < T.ni; ++ii) {
+            if (pass == 0) ++fill[T.i0 + ii];
+            else P.list[fill[T.i0 + ii]++] = T.toff + (int64_t)ii * SYM_T;
+          }
+          for (int jj = 0; jj < (T.c0 ? 0 : T.nj); ++jj) {
+            if (pass == 0) ++fill[T.j0 + jj];
+            else P.list[fill[T.j0 + jj]++] = T.soff + (int64_t)jj * SYM_T;
+          }
+          continue;
+        }
         uint32_t colseen = 0;
         for (int ii = 0; ii < T.ni; ++ii) {
           bool row = false;
