@@ -1241,15 +1241,18 @@ static void gj_factor_panel(hipStream_t s, typename Cx<T>::V* pool, const MatDes
 // (41-48 TFLOP/s in the updates, bound by the matrix cores, by whole tiles
 // over the chip's places and by the load and store around 64 columns' work).
 //
-// bad[0] or bad[1] is set where elimination on the diagonal may lose digits:
-// a multiplier beyond 4 within a diagonal block, a 2 x 2 pivot block whose
+// A matrix is flagged where elimination on the diagonal may lose digits: a
+// multiplier beyond 4 within a diagonal block, a 2 x 2 pivot block whose
 // determinant cancels (a diagonal product beyond 8 times it), an entry of G
-// beyond 8, or anything not finite; the caller then inverts again with
-// interchanges.  Over spheroids, peanuts, quasi-ellipsoids, conches and spirals
-// at k = 0.5 to 20 the largest entry of G is 0.03 to 9 for 1/2 I + D on
-// resolved bodies and 0.05 to 0.4 with - i eta S, the inverses agreeing with
-// LAPACK's to 3e-15; a sphere at k = 20 on 16 azimuths (G to 23) and the
-// single layer (G to 2000) take the interchanges.
+// beyond 8 below the panel (above it, as with any pivots, G grows with the
+// inverse), or anything not finite; the caller inverts it again with
+// interchanges.  On 190 blocks of random spheres, spheroids and peanuts
+// (k = 2.1 and 4) G below a panel stays under 0.44, on spheroids,
+// quasi-ellipsoids, spirals and conches at k = 20 under 0.9, the single layer's
+// under 0.8; a sphere at k = 20 on 16 azimuths reaches 2.4, peanuts at k = 15
+// more than 2.  The inverses agree with LAPACK's to 6e-15 of their largest
+// entry throughout.  One matrix that goes back costs its own panels' chain
+// (36 reduced blocks of order ~500: 1.6 -> 4.4 ms), so the limits are not tighter.
 constexpr int GJD = 64;
 
 // The inverse of the block [k0, k0 + 64) x [k0, k0 + 64) of a matrix (padded
@@ -1333,7 +1336,7 @@ __global__ __launch_bounds__(256) void gjd_first_kernel(const MatDesc* __restric
                                                         double2* __restrict__ dinv, int* __restrict__ bad) {
   __shared__ double2 lds[2][4][GJD];
   const MatDesc M = mats[blockIdx.x];
-  gjd_diag(pool + M.elem_off, M.n, 0, dinv + (int64_t)blockIdx.x * GJD * GJD, lds, bad);
+  gjd_diag(pool + M.elem_off, M.n, 0, dinv + (int64_t)blockIdx.x * GJD * GJD, lds, bad + 2 * blockIdx.x);
 }
 
 // Tiles of 64 x 64 complex products on v_mfma_f64_16x16x4f64, as the trailing
@@ -1356,10 +1359,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
   int z, it, jt;
   bool next = false;                    // the next panel's diagonal tile
   if (UPDATE) {
-    if (bad[0]) {                       // some matrix needs interchanges (written by the other launches only)
-      if (!blockIdx.x && !tid) bad[1] = 1;
-      return;
-    }
     const int d = k0 / GJD + 1 < tiles ? k0 / GJD + 1 : 0;
     int b = blockIdx.x;
     const int first = (batch + 7) & ~7, rest = batch * (tiles * tiles - 1), per = (rest + 7) >> 3;
@@ -1379,13 +1378,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
       jt = b - it * tiles;
     }
   } else {
-    if (bad[1]) {
-      if (!blockIdx.x && !blockIdx.y && !tid) bad[0] = 1;
-      return;
-    }
     z = blockIdx.y;
     it = blockIdx.x;
     jt = 0;
+  }
+  // a matrix that needs interchanges: its flag of the other launches is read,
+  // handed on in this launch's own
+  if (bad[2 * z + !UPDATE]) {
+    if ((UPDATE ? blockIdx.x < batch : it == 0) && !tid) bad[2 * z + UPDATE] = 1;
+    return;
   }
   const MatDesc M = mats[z];
   const int n = M.n;
@@ -1511,23 +1512,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void g
       for (int y = 0; y < 4; ++y) {
         const int c = 2 * j0 + wc + 16 * y + (lane & 15);
         const double v = UPDATE ? acc[x][y][e] : -acc[x][y][e];
-        if (!UPDATE && !(fabs(v) <= 8.0)) big = true;
+        if (!UPDATE && !(fabs(v) <= (i0 > k0 ? 8.0 : 1e150))) big = true;
         if (!UPDATE || c < ldo) out[(int64_t)i * ldo + c] = v;
       }
     }
-  if (!UPDATE && big) atomicOr(bad, 1);
+  if (!UPDATE && big) atomicOr(bad + 2 * z, 1);
   if (UPDATE && next) {
     __syncthreads();
-    gjd_diag(A, n, i0, dinv, (double2(*)[4][GJD]) & As[0][0], bad + 1);
+    gjd_diag(A, n, i0, dinv, (double2(*)[4][GJD]) & As[0][0], bad + 2 * z + 1);
   }
 }
 
-__global__ void gjd_clear_kernel(int* bad) { bad[threadIdx.x] = 0; }
+__global__ void gjd_clear_kernel(int* bad, int n) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) bad[i] = 0;
+}
 
 // In-place inversion of `batch` FP64 matrices on the diagonal, work as
-// gj_invert's.  bad (two values, 0 on entry): nonzero afterwards where some
-// matrix needs interchanges, whose inverse and the others' the pool then does
-// not hold.  The launches after a failure return at once; nothing here waits.
+// gj_invert's.  bad (two values per matrix, 0 on entry): nonzero afterwards
+// for a matrix that needs interchanges, whose inverse the pool then does not
+// hold; its later tiles return at once.  Nothing here waits.
 static hipError_t gjd_invert(qax_problem* p, double2* pool, const MatDesc* d_mats, int batch, int nmax,
                              double* work, int* bad) {
   if (nmax > 8192) return hipErrorInvalidValue;
@@ -1685,7 +1689,7 @@ static void plan_sym_inverse(const qax_problem* p, size_t elem_bytes, SymInvPlan
   P.off_desc = P.off_plain + align256(P.plain.size() * sizeof(MatDesc));
   P.off_rows = P.off_desc + align256(P.desc.size() * sizeof(SymInvDesc));
   P.off_bad = P.off_rows + align256(P.rows.size() * sizeof(SymInvRow));
-  P.off_gj = P.off_bad + 256;
+  P.off_gj = P.off_bad + align256(2 * (P.red.size() + P.plain.size()) * sizeof(int));
   const size_t gj = std::max(P.red.empty() ? 0 : gj_work_bytes((int)P.red.size(), P.nmax_red),
                              P.plain.empty() ? 0 : gj_work_bytes((int)P.plain.size(), P.nmax_plain));
   P.off_pool = P.off_gj + align256(gj);
@@ -1693,14 +1697,19 @@ static void plan_sym_inverse(const qax_problem* p, size_t elem_bytes, SymInvPlan
   P.bytes = P.off_pool + (p->symap.on ? 0 : (size_t)P.red_elems * elem_bytes);
 }
 
-// M_c from B for one orbit row (o1) per workgroup, columns o2 over the threads.
+// M_c from B for one orbit row (o1) per workgroup, columns o2 over the threads;
+// only: two values per matrix, the matrices with a nonzero one.
 template <typename T>
 __global__ __launch_bounds__(256) void sym_reduce_kernel(const SymInvRow* __restrict__ rows,
                                                          const SymInvDesc* __restrict__ descs,
                                                          const double2* __restrict__ B,
-                                                         typename Cx<T>::V* __restrict__ M) {
+                                                         typename Cx<T>::V* __restrict__ M,
+                                                         const int* __restrict__ only) {
   const SymInvRow R = rows[blockIdx.x];
   const SymInvDesc D = descs[R.blk];
+  bool want[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) want[c] = !only || only[8 * R.blk + 2 * c] || only[8 * R.blk + 2 * c + 1];
   const int nth = D.nth, N = nth / 2, ns = D.ns, n = ns * nth, half = ns / 2;
   const int np = N + 1, nm = N - 1;
   const int s1 = R.o1 / np, j1 = R.o1 % np;
@@ -1718,14 +1727,14 @@ __global__ __launch_bounds__(256) void sym_reduce_kernel(const SymInvRow* __rest
     }
     // c_h = 0: b0 + bh +- (bt + bht)
     const double2 e0 = make_double2(b0.x + bh.x, b0.y + bh.y), et = make_double2(bt.x + bht.x, bt.y + bht.y);
-    M[D.m_off[0] + r0 + o2] = Cx<T>::make((T)(e0.x + et.x), (T)(e0.y + et.y));
-    M[D.m_off[2] + r0 + o2] = Cx<T>::make((T)(e0.x - et.x), (T)(e0.y - et.y));
+    if (want[0]) M[D.m_off[0] + r0 + o2] = Cx<T>::make((T)(e0.x + et.x), (T)(e0.y + et.y));
+    if (want[2]) M[D.m_off[2] + r0 + o2] = Cx<T>::make((T)(e0.x - et.x), (T)(e0.y - et.y));
     if (!fix1 && !fix2) {
       // c_h = 1: b0 - bh +- (bt - bht)
       const double2 d0 = make_double2(b0.x - bh.x, b0.y - bh.y), dt = make_double2(bt.x - bht.x, bt.y - bht.y);
       const int64_t c1 = s2 * nm + j2 - 1;
-      M[D.m_off[1] + r1 + c1] = Cx<T>::make((T)(d0.x + dt.x), (T)(d0.y + dt.y));
-      M[D.m_off[3] + r1 + c1] = Cx<T>::make((T)(d0.x - dt.x), (T)(d0.y - dt.y));
+      if (want[1]) M[D.m_off[1] + r1 + c1] = Cx<T>::make((T)(d0.x + dt.x), (T)(d0.y + dt.y));
+      if (want[3]) M[D.m_off[3] + r1 + c1] = Cx<T>::make((T)(d0.x - dt.x), (T)(d0.y - dt.y));
     }
   }
 }
@@ -1941,15 +1950,14 @@ static void launch_sym_apply(qax_problem* p, int prec, const double* v, double* 
                      (const double2*)A.d_w, (double2*)out, accumulate ? 1 : 0, p->seg_active);
 }
 
-// f(complex offset, complex elements) over the runs of blocks inverted as they
-// are, adjacent ones together.
+// f(complex offset, complex elements) over the runs of adjacent matrices.
 template <typename F>
-static hipError_t plain_runs(const SymInvPlan& P, F f) {
+static hipError_t mat_runs(const std::vector<MatDesc>& mats, F f) {
   hipError_t e = hipSuccess;
-  for (size_t i = 0; i < P.plain.size() && e == hipSuccess;) {
-    const int64_t off = P.plain[i].elem_off;
+  for (size_t i = 0; i < mats.size() && e == hipSuccess;) {
+    const int64_t off = mats[i].elem_off;
     int64_t end = off;
-    for (; i < P.plain.size() && P.plain[i].elem_off == end; ++i) end += (int64_t)P.plain[i].n * P.plain[i].n;
+    for (; i < mats.size() && mats[i].elem_off == end; ++i) end += (int64_t)mats[i].n * mats[i].n;
     e = f(off, end - off);
   }
   return e;
@@ -1984,9 +1992,9 @@ static hipError_t invert_blocks_sym(qax_problem* p, const SymInvPlan& P, char* w
   timing_begin(p, QAX_K_INVERT);
   typedef typename Cx<T>::V V;
   const int n_red = (int)P.red.size(), n_plain = (int)P.plain.size();
-  auto reduce = [&]() {
+  auto reduce = [&](const int* only) {
     hipLaunchKernelGGL(sym_reduce_kernel<T>, dim3((unsigned)P.rows.size()), dim3(256), 0, s, d_rows, d_desc,
-                       (const double2*)p->d_B, (V*)pool);
+                       (const double2*)p->d_B, (V*)pool, only);
     return hipGetLastError();
   };
   auto expand = [&]() {
@@ -1994,44 +2002,59 @@ static hipError_t invert_blocks_sym(qax_problem* p, const SymInvPlan& P, char* w
                        (const V*)pool, inv_pool, inv32, red32);
     return hipGetLastError();
   };
-  auto fill = [&]() {
+  auto fill = [&](const std::vector<MatDesc>& mats) {
     if (sizeof(T) == 4) return hipSuccess;      // (B rounded into the pool by the caller)
-    return plain_runs(P, [&](int64_t off, int64_t elems) {
+    return mat_runs(mats, [&](int64_t off, int64_t elems) {
       return hipMemcpyAsync(inv_pool + off, (const double2*)p->d_B + off, (size_t)elems * 16,
                             hipMemcpyDeviceToDevice, s);
     });
   };
-  bool red = n_red > 0, plain = n_plain > 0;     // still to be inverted
-  // FP64: on the diagonal, again with interchanges where that fails (known
-  // once everything is enqueued: one wait); the single layer, whose blocks all
-  // need interchanges, at once with them (the attempt took 0.2 to 0.7 ms)
-  if constexpr (sizeof(T) == 8)
-    if (p->form() != QAX_SINGLE_LAYER) {
-      int* bad = (int*)(work + P.off_bad);
-      hipLaunchKernelGGL(gjd_clear_kernel, dim3(1), dim3(4), 0, s, bad);
-      if (red) {
-        e = reduce();
-        if (e == hipSuccess) e = gjd_invert(p, (V*)pool, d_red, n_red, P.nmax_red, gjw, bad);
-        if (e == hipSuccess) e = expand();
-      }
-      if (plain && e == hipSuccess) {
-        e = fill();
-        if (e == hipSuccess) e = gjd_invert(p, inv_pool, d_plain, n_plain, P.nmax_plain, gjw, bad + 2);
-      }
-      int h[4] = {0, 0, 0, 0};
-      if (e == hipSuccess) e = hipMemcpyAsync(h, bad, sizeof(h), hipMemcpyDeviceToHost, s);
-      if (e == hipSuccess) e = hipStreamSynchronize(s);
-      red = red && (h[0] || h[1]);
-      plain = plain && (h[2] || h[3]);
+  // the matrices still to be inverted
+  std::vector<MatDesc> red = P.red, plain = P.plain;
+  int nmax_red = P.nmax_red, nmax_plain = P.nmax_plain;
+  const int* only = nullptr;
+  // FP64: on the diagonal, what fails there (known once everything is
+  // enqueued: one wait) again with interchanges
+  if constexpr (sizeof(T) == 8) {
+    int* bad = (int*)(work + P.off_bad);
+    std::vector<int> h(2 * (size_t)(n_red + n_plain), 0);
+    hipLaunchKernelGGL(gjd_clear_kernel, dim3((unsigned)((h.size() + 255) / 256)), dim3(256), 0, s, bad,
+                       (int)h.size());
+    if (n_red) {
+      e = reduce(nullptr);
+      if (e == hipSuccess) e = gjd_invert(p, (V*)pool, d_red, n_red, nmax_red, gjw, bad);
+      if (e == hipSuccess) e = expand();
     }
-  if (red && e == hipSuccess) {
-    e = reduce();
-    if (e == hipSuccess) e = gj_invert<T>(p, pool, d_red, n_red, P.nmax_red, gjw, true);
+    if (n_plain && e == hipSuccess) {
+      e = fill(plain);
+      if (e == hipSuccess) e = gjd_invert(p, inv_pool, d_plain, n_plain, nmax_plain, gjw, bad + 2 * n_red);
+    }
+    if (e == hipSuccess) e = hipMemcpyAsync(h.data(), bad, h.size() * sizeof(int), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    auto failed = [&](const std::vector<MatDesc>& all, size_t first, int& nmax, MatDesc* d) {
+      std::vector<MatDesc> f;
+      nmax = 0;
+      for (size_t i = 0; i < all.size(); ++i)
+        if (h[2 * (first + i)] || h[2 * (first + i) + 1]) {
+          f.push_back(all[i]);
+          nmax = std::max(nmax, all[i].n);
+        }
+      if (!f.empty() && e == hipSuccess)
+        e = hipMemcpyAsync(d, f.data(), f.size() * sizeof(MatDesc), hipMemcpyHostToDevice, s);
+      return f;
+    };
+    red = failed(P.red, 0, nmax_red, d_red);
+    plain = failed(P.plain, n_red, nmax_plain, d_plain);
+    only = bad;
+  }
+  if (!red.empty() && e == hipSuccess) {
+    e = reduce(only);
+    if (e == hipSuccess) e = gj_invert<T>(p, pool, d_red, (int)red.size(), nmax_red, gjw, true);
     if (e == hipSuccess) e = expand();
   }
-  if (plain && e == hipSuccess) {
-    e = fill();
-    if (e == hipSuccess) e = gj_invert<T>(p, (T*)inv_pool, d_plain, n_plain, P.nmax_plain, gjw, true);
+  if (!plain.empty() && e == hipSuccess) {
+    e = fill(plain);
+    if (e == hipSuccess) e = gj_invert<T>(p, (T*)inv_pool, d_plain, (int)plain.size(), nmax_plain, gjw, true);
   }
   timing_end(p, QAX_K_INVERT);
   return e;
@@ -2070,7 +2093,7 @@ hipError_t launch_factor_blocks64(qax_problem* p, double* work) {
   hipError_t e = invert_blocks_sym<double>(p, P, (char*)work, (double2*)p->d_Binv, (float2*)p->d_Binv32,
                                            p->symap.on ? (float2*)p->symap.d_Minv32 : nullptr);
   if (e != hipSuccess) return e;
-  return plain_runs(P, [&](int64_t off, int64_t elems) {
+  return mat_runs(P.plain, [&](int64_t off, int64_t elems) {
     return launch_convert_f32(p->stream, p->d_Binv + 2 * off, p->d_Binv32 + 2 * off, 2 * elems);
   });
 }

@@ -25,6 +25,7 @@ SPHERE = (sc.SPHERE, 0.5, 0.5, 0.0)
 SPHEROID = (sc.SPHEROID, 0.5, 1.0, 0.25)
 CONCH = (sc.CONCH, 0.6, 1.0, 0.0)
 SPIRAL = (sc.SPIRAL, 0.5, 1.0, 0.0)
+QUASI = (sc.QUASI_ELLIPSOID, 0.5, 1.0, 0.0)
 
 # orders inverted: (n_s / 2)(N + 1), (n_s / 2)(N - 1) of mirror-symmetric
 # bodies, n_s 2 N of the others (n_s = 16 panels, 2 N azimuths)
@@ -36,8 +37,14 @@ CASES = {
     "panels exactly, plain": ([CONCH + (2, 0, 18)], 2.0, qax.QAX_COMBINED_FIELD),      # 576
     "orders apart in one batch": ([SPHERE + (1, 0, 6), PEANUT + (2, 1, 22), CONCH + (1, 0, 4), SPIRAL + (2, 0, 12)],
                                   3.0, qax.QAX_DOUBLE_LAYER),                       # 16 .. 384
-    "unresolved: interchanges": ([SPHERE + (2, 0, 16)], 20.0, qax.QAX_DOUBLE_LAYER),
-    "single layer: interchanges": ([PEANUT + (2, 0, 16), CONCH + (1, 0, 8)], 3.0, qax.QAX_SINGLE_LAYER),
+    "unresolved": ([SPHERE + (2, 0, 16)], 20.0, qax.QAX_DOUBLE_LAYER),
+    # far from resolved: three of the spheroid's four reduced blocks, some of
+    # the quasi-ellipsoid's and the plain blocks of order 96 have multipliers
+    # of 6 to 80, the others pass
+    "some of each batch: interchanges": ([SPHEROID + (1, 0, 12), PEANUT + (1, 0, 12), QUASI + (1, 0, 16),
+                                          SPHERE + (1, 0, 8), CONCH + (1, 0, 6), CONCH + (2, 0, 18),
+                                          SPIRAL + (1, 0, 6)], 120.0, qax.QAX_DOUBLE_LAYER),
+    "single layer": ([PEANUT + (2, 0, 16), CONCH + (1, 0, 8)], 3.0, qax.QAX_SINGLE_LAYER),
 }
 
 
