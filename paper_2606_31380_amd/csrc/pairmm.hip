@@ -111,7 +111,11 @@ __global__ void mm_zero_kernel(uint64_t* __restrict__ p, int n) {
 
 // Largest |Re|, |Im| of mu / S_b per problem and right-hand side, as the bits
 // of a non-negative double (which order like the values; NaN above infinity).
-// Workgroup: 256 consecutive nodes (of any problems) x 8 right-hand sides.
+// Workgroup: 256 consecutive nodes (of any problems) x 8 right-hand sides; a
+// wavefront whose nodes are of one problem meets in one lane per right-hand
+// side (with one maximum per lane, all on the same few addresses, calls at
+// N = 55,296 took 2635 us with 8 right-hand sides and 3836 with 32, now 2517
+// and 3608; N = 5120: 73 and 88, now 67 and 71).
 __global__ __launch_bounds__(256) void mm_colmax_kernel(const double2* __restrict__ mu, int64_t N, int nrhs,
                                                         const BodyDev* __restrict__ bodies,
                                                         const int32_t* __restrict__ node_body,
@@ -119,19 +123,28 @@ __global__ __launch_bounds__(256) void mm_colmax_kernel(const double2* __restric
                                                         unsigned long long* __restrict__ colmax) {
   const int r = blockIdx.y * 8 + (threadIdx.x & 7);
   const int64_t n0 = (int64_t)blockIdx.x * 256 + (threadIdx.x >> 3) * 8;
-  if (r >= nrhs || n0 >= N) return;
+  const bool in = r < nrhs && n0 < N;
   // eight consecutive nodes of one body (node counts are multiples of 32)
-  const int b = node_body[n0];
+  const int b = node_body[min(n0, N - 1)];
+  const int problem = bodies[b].problem;
   unsigned long long m = 0;
-  for (int s = 0; s < 8; ++s) {
-    const double2 v = mu[(n0 + s) * nrhs + r];
-    const unsigned long long x = __double_as_longlong(fabs(v.x)), y = __double_as_longlong(fabs(v.y));
-    m = max(m, max(x, y));
+  if (in) {
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      const double2 v = mu[(n0 + s) * nrhs + r];
+      const unsigned long long x = __double_as_longlong(fabs(v.x)), y = __double_as_longlong(fabs(v.y));
+      m = max(m, max(x, y));
+    }
+    const double is = 1.0 / (double)mb[b].S;
+    m = __double_as_longlong(fabs(__longlong_as_double(m)) * is);
   }
-  const double is = 1.0 / (double)mb[b].S;
-  m = __double_as_longlong(fabs(__longlong_as_double(m)) * is);
-  unsigned long long* dst = colmax + (int64_t)bodies[b].problem * nrhs + r;
-  if (m > *(volatile unsigned long long*)dst) atomicMax(dst, m);
+  bool lead = in;
+  if (__all(problem == __builtin_amdgcn_readfirstlane(problem))) {
+    for (int off = 8; off < 64; off <<= 1) m = max(m, (unsigned long long)__shfl_xor((long long)m, off));
+    lead = in && (threadIdx.x & 63) < 8;
+  }
+  unsigned long long* dst = colmax + (int64_t)problem * nrhs + r;
+  if (lead && m > *(volatile unsigned long long*)dst) atomicMax(dst, m);
 }
 
 // sigma of a column from its largest value (1 when that is zero or not finite)
