@@ -37,13 +37,15 @@
 // latency of its LDS round trips and FP64 chains: half of the issue slots are
 // filled with two wavefronts per SIMD, which the LDS (19 KB: the recurrence in
 // batches of QB nodes, the final transform in halves of RH functions) and 256
-// registers (some spilled, outside the node loops) allow; with one (34 KB, 444
+// registers (100 values spilled, outside the node loops) allow; with one (34 KB, 444
 // registers, 32 nodes a batch) the 27-body lattice took 5.76 ms, with two
 // 5.10.  Fewer instructions per node gave the rest: what each node needs
 // computed once by its lane, the even smooth factors on half the azimuths and
 // a transform of half the length, sines and cosines from the twiddle table,
 // the recurrence's normalisation as a factor, static modes stored for both
-// signs: 3.86 ms (a spiral and a conch of 2304 nodes 3.51 -> 2.32).
+// signs: 3.86 ms (a spiral and a conch of 2304 nodes 3.51 -> 2.32); compiled
+// without the loop-invariant motion of constants, which spilled them (222
+// values): 3.30 (1.99).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
