@@ -846,7 +846,8 @@ __device__ __forceinline__ void slots_to_nodes_fft(SelfShared<CF>& S, int N, dou
 // (ip, l, j) carries |J| at that node.
 // One wavefront per SIMD for the combined field and the single layer: within
 // 256 registers their second set of accumulators spills in the node loops (9
-// mirror-symmetric blocks of order 2048: 2.3 ms, with two wavefronts 4.3).
+// mirror-symmetric blocks of order 2048: 2.3 ms, with two wavefronts 2.5; 12
+// blocks of order 256: 0.43 and 0.69).
 template <int FORM>
 __global__ __launch_bounds__(64, FORM == 0 ? 2 : 1) void assemble_self_kernel(
     const SelfTask* __restrict__ tasks, const BlockDev* __restrict__ blocks,
