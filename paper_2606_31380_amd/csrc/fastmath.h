@@ -110,14 +110,19 @@ __device__ __forceinline__ void sincos_tab512(double u, const double2* tab, doub
 constexpr double U512 = 512.0 / 6.283185307179586476925;
 constexpr double U512_LOW = -5.037741228846716e-15;
 
-// sin and cos of 2 pi (x (u + ul)) / 512 from the same table, x u not rounded:
-// the remainder against its nearest integer is one fma, the part ul (far below
-// u) another.
+// x + NEAREST (|x| < 2^51) is NEAREST plus the integer nearest to x, whose low bits
+// are those of the sum.
+constexpr double NEAREST = 6755399441055744.0;     // 1.5 x 2^52
+
+// sin and cos of 2 pi (x (u + ul)) / 512 (|x u| < 2^51) from the same table, x u
+// not rounded: the remainder against its nearest integer is one fma, the part ul
+// (far below u) another.  The table's index is taken from the low bits of
+// x u + NEAREST: a conversion to 32 bits ends at 2^31, that is x = k r = 2.6e7.
 __device__ __forceinline__ void sincos_tab512_scaled(double x, double u, double ul, const double2* tab, double* sp,
                                                      double* cp) {
-  const double m = rint(x * u);
-  const double g = fma(x, ul, fma(x, u, -m));
-  const double2 T = tab[(int)m & 511];
+  const double t = fma(x, u, NEAREST);
+  const double g = fma(x, ul, fma(x, u, -(t - NEAREST)));
+  const double2 T = tab[__double2loint(t) & 511];
   const double g2 = g * g;
   const double S = g * fma(fma(g2, 2.3193606829202922e-12, -3.080196845561248e-07), g2, 0.01227184630308513);
   const double Cm1 = g2 * fma(g2, 9.44992556799382e-10, -7.529910584327208e-05);
