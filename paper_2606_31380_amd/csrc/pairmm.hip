@@ -32,8 +32,10 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // is below 2^-22 of the product, of random sign).  Powers of two keep the
 // factors in range: K is scaled per source body by S_b so that the largest
 // entry that a target at least rho_b = R_b / 2 off the body's bounding ball
-// (radius R_b) can have is below 2^14, mu by 1 / S_b and, per problem and
-// right-hand side, by sigma so that its largest entry is below 2^15.
+// (radius R_b) can have is below 2^14, mu per source body and right-hand side by
+// sigma so that its largest entry there is below 2^15.  Sums are taken out of
+// these scales where the sources' body changes, so that a body's densities keep
+// their digits beside another's larger ones, or ones that are not finite.
 __device__ __forceinline__ void split2(float x0, float x1, uint32_t& h, uint32_t& l) {
   f32x2 r = {x0, x1};
   h = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, f16x2));
@@ -48,6 +50,7 @@ __device__ __forceinline__ void split2(float x0, float x1, uint32_t& h, uint32_t
 // (single layer: |aw| / (k^3 r)).
 struct MmBody {
   float S, near2;   // near: |D|^2 below this
+  int32_t e;        // log2 S_b
 };
 
 __global__ __launch_bounds__(256) void mm_body_kernel(const BodyDev* __restrict__ bodies,
@@ -79,7 +82,9 @@ __global__ __launch_bounds__(256) void mm_body_kernel(const BodyDev* __restrict_
                        (form == 2 ? B.eta / k : sqrt(1.0 + q * q) + (form == 1 ? B.eta / k : 0.0));
     int e = 0;
     (void)frexp(lim, &e);
-    mb[blockIdx.x].S = (float)ldexp(1.0, max(-120, min(120, 14 - e)));
+    e = max(-120, min(120, 14 - e));
+    mb[blockIdx.x].e = e;
+    mb[blockIdx.x].S = (float)ldexp(1.0, e);
     mb[blockIdx.x].near2 = (float)(1.0001 * (R + rho) * (R + rho));
   }
 }
@@ -104,29 +109,26 @@ __global__ void mm_records_kernel(const BodyDev* __restrict__ bodies, const int3
   ewk[n] = ew32[n] * (float)(1.0 / (k * k)) * S;
 }
 
-__global__ void mm_zero_kernel(uint64_t* __restrict__ p, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void mm_zero_kernel(uint64_t* __restrict__ p, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0;
 }
 
-// Largest |Re|, |Im| of mu / S_b per problem and right-hand side, as the bits
+// Largest |Re|, |Im| of mu per body and right-hand side, as the bits
 // of a non-negative double (which order like the values; NaN above infinity).
-// Workgroup: 256 consecutive nodes (of any problems) x 8 right-hand sides; a
-// wavefront whose nodes are of one problem meets in one lane per right-hand
+// Workgroup: 256 consecutive nodes (of any bodies) x 8 right-hand sides; a
+// wavefront whose nodes are of one body meets in one lane per right-hand
 // side (with one maximum per lane, all on the same few addresses, calls at
 // N = 55,296 took 2635 us with 8 right-hand sides and 3836 with 32, now 2517
 // and 3608; N = 5120: 73 and 88, now 67 and 71).
 __global__ __launch_bounds__(256) void mm_colmax_kernel(const double2* __restrict__ mu, int64_t N, int nrhs,
-                                                        const BodyDev* __restrict__ bodies,
                                                         const int32_t* __restrict__ node_body,
-                                                        const MmBody* __restrict__ mb,
                                                         unsigned long long* __restrict__ colmax) {
   const int r = blockIdx.y * 8 + (threadIdx.x & 7);
   const int64_t n0 = (int64_t)blockIdx.x * 256 + (threadIdx.x >> 3) * 8;
   const bool in = r < nrhs && n0 < N;
   // eight consecutive nodes of one body (node counts are multiples of 32)
   const int b = node_body[min(n0, N - 1)];
-  const int problem = bodies[b].problem;
   unsigned long long m = 0;
   if (in) {
 #pragma unroll
@@ -135,25 +137,30 @@ __global__ __launch_bounds__(256) void mm_colmax_kernel(const double2* __restric
       const unsigned long long x = __double_as_longlong(fabs(v.x)), y = __double_as_longlong(fabs(v.y));
       m = max(m, max(x, y));
     }
-    const double is = 1.0 / (double)mb[b].S;
-    m = __double_as_longlong(fabs(__longlong_as_double(m)) * is);
   }
   bool lead = in;
-  if (__all(problem == __builtin_amdgcn_readfirstlane(problem))) {
+  if (__all(b == __builtin_amdgcn_readfirstlane(b))) {
     for (int off = 8; off < 64; off <<= 1) m = max(m, (unsigned long long)__shfl_xor((long long)m, off));
     lead = in && (threadIdx.x & 63) < 8;
   }
-  unsigned long long* dst = colmax + (int64_t)problem * nrhs + r;
+  unsigned long long* dst = colmax + (int64_t)b * nrhs + r;
   if (lead && m > *(volatile unsigned long long*)dst) atomicMax(dst, m);
 }
 
-// sigma of a column from its largest value (1 when that is zero or not finite)
-__device__ __forceinline__ double mm_sigma(unsigned long long bits) {
+// log2 sigma of a body's column from its largest value (0 when that is zero or
+// not finite)
+__device__ __forceinline__ int mm_sigma(unsigned long long bits) {
   const double m = __longlong_as_double(bits);
-  if (!(m > 0.0) || !(m < 1.0e300)) return 1.0;
+  if (!(m > 0.0) || !(m <= 1.7e308)) return 0;
   int e = 0;
   (void)frexp(m, &e);
-  return ldexp(1.0, min(15 - e, 1000));
+  return max(-780, min(15 - e, 780));
+}
+
+// log2 of what takes the sums over a body's sources out of the scales
+__device__ __forceinline__ int mm_undo(const MmBody* __restrict__ mb, const unsigned long long* __restrict__ colmax,
+                                       int body, int nrhs, int r) {
+  return r < nrhs ? -(mm_sigma(colmax[(int64_t)body * nrhs + r]) + mb[body].e) : 0;
 }
 
 // Densities scaled, split and laid out as the B operands of the 32x32x16
@@ -164,9 +171,7 @@ __device__ __forceinline__ double mm_sigma(unsigned long long bits) {
 // a fragment holds column l % 32 and the sources 8 (l / 32) ... + 7.
 __global__ __launch_bounds__(256) void mm_pack_kernel(const double2* __restrict__ mu, int64_t halves, int nrhs,
                                                       int r0, int wide, int tiles,
-                                                      const BodyDev* __restrict__ bodies,
                                                       const int32_t* __restrict__ node_body,
-                                                      const MmBody* __restrict__ mb,
                                                       const unsigned long long* __restrict__ colmax,
                                                       u32x4* __restrict__ out) {
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -179,7 +184,7 @@ __global__ __launch_bounds__(256) void mm_pack_kernel(const double2* __restrict_
   const int r = r0 + tile * 32 + (wide ? col : (col & 15));
   const double2* v = mu + (hc * 16 + (lane >> 5) * 8) * nrhs + r;
   const int body = node_body[hc * 16];
-  const double sc = r < nrhs ? mm_sigma(colmax[(int64_t)bodies[body].problem * nrhs + r]) / (double)mb[body].S : 0.0;
+  const double sc = r < nrhs ? ldexp(1.0, mm_sigma(colmax[(int64_t)body * nrhs + r])) : 0.0;
   float a[8], b[8];
 #pragma unroll
   for (int s = 0; s < 8; ++s) {
@@ -323,36 +328,37 @@ __device__ __forceinline__ void mm_products(u32x4* f, const u32x4* fb, f32x16* a
   acc[0] = mm_mma3(f + 2, b + 2, acc[0]);
 }
 
-// FP32 sums of at most eight chunks (256 sources), added up in FP64
+// FP32 sums of at most eight chunks (256 sources) of one body, added up in FP64
+// times 2^e
 template <int NA>
 struct MmSums {
   f32x16 acc[NA];
   double sum[NA][16];
-  int n;
+  int n, e;
   __device__ __forceinline__ void clear() {
+    n = e = 0;
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        acc[a][i] = 0.0f;
+        sum[a][i] = 0.0;
+      }
+  }
+  __device__ __forceinline__ void flush(double f = 1.0) {
+    f *= __hiloint2double((1023 + e) << 20, 0);   // 2^e
     n = 0;
 #pragma unroll
     for (int a = 0; a < NA; ++a)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        acc[a][e] = 0.0f;
-        sum[a][e] = 0.0;
+      for (int i = 0; i < 16; ++i) {
+        sum[a][i] = fma((double)acc[a][i], f, sum[a][i]);
+        acc[a][i] = 0.0f;
       }
   }
-  __device__ __forceinline__ void flush(double f) {
-#pragma unroll
-    for (int a = 0; a < NA; ++a)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        sum[a][e] = fma((double)acc[a][e], f, sum[a][e]);
-        acc[a][e] = 0.0f;
-      }
-  }
-  __device__ __forceinline__ void end_chunk() {
-    if (++n == 8) {
-      n = 0;
-      flush(1.0);
-    }
+  // last: of its body, or of all
+  __device__ __forceinline__ void end_chunk(bool last) {
+    if (++n == 8 || last) flush();
   }
 };
 
@@ -424,9 +430,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ? 3 : 
   __shared__ u32x4 sR[2][64];
   __shared__ float sE[2][FORM ? 32 : 1];
   const double k = T.k;
+  __shared__ double sX[3][128];                  // the targets, read where the sources' body changes
   const int mybody = live ? node_body[tile0] : -1;
   const int64_t ti = live ? tile0 + col : T.t0;
-  const double xi = pos[ti], yi = pos[N + ti], zi = pos[2 * N + ti];
+  for (int d = half; d < 3; d += 2) sX[d][wave * 32 + col] = pos[d * N + ti];
 
   MmSums<NA> S;
   S.clear();
@@ -464,27 +471,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ? 3 : 
     if (live && W.body != mybody) {
       if (W.body != cur) {
         cur = W.body;
-        near = __any(mm_target(bodies[cur], mb[cur], xi, yi, zi, k, G));
+        const int tc = wave * 32 + col;
+        near = __any(mm_target(bodies[cur], mb[cur], sX[0][tc], sX[1][tc], sX[2][tc], k, G));
+        S.e = mm_undo(mb, colmax, cur, nrhs, r0 + (WIDE ? col : (col & 15)));
       }
 #pragma unroll
       for (int hc = 0; hc < 2; ++hc) {
         u32x4 f[4];
         const float undo = mm_operands<FORM>((const float4*)&sR[buf][(hc * 16 + half * 8) * 2],
                                              &sE[buf][FORM ? hc * 16 + half * 8 : 0], G, near, f);
-        if (undo != 1.0f) S.flush(1.0);
+        if (undo != 1.0f) S.flush();
         mm_products<WIDE>(f, &sB[buf][hc * 4 * 64 + lane], S.acc);
         if (undo != 1.0f) S.flush((double)undo);
       }
-      S.end_chunk();
+      S.end_chunk(cn >= min(W.end, T.c1));
     }
     buf ^= 1;
     c = cn;
   }
-  S.flush(1.0);
   if (!live) return;
   // element e of the lane: column l % 32, row 8 (e / 4) + 4 (l / 32) + e % 4
   const int r = r0 + (WIDE ? col : (col & 15));
-  const double sc = r < nrhs ? k * k * k / FOUR_PI / mm_sigma(colmax[(int64_t)T.problem * nrhs + r]) : 0.0;
+  const double sc = k * k * k / FOUR_PI;
 #pragma unroll
   for (int e = 0; e < 16; ++e) {
     const int64_t i = tile0 + 8 * (e >> 2) + 4 * half + (e & 3);
@@ -527,12 +535,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
   const int mybody = live ? node_body[tile0] : -1;
   const int64_t ti = live ? tile0 + col : T.t0;
   const double xi = pos[ti], yi = pos[N + ti], zi = pos[2 * N + ti];
+  const int r = r0 + hw * 32 + col;              // the lane's right-hand side
 
   MmSums<2> S;
   S.clear();
   MmTarget G;
   bool near = false;
-  int cur = -1;
+  int cur = -1, summed = -1;                     // bodies evaluated, multiplied
   MmWalk W(T, bodies);
   u32x4 preB[4], preR;
   float preE = 0.0f;
@@ -556,12 +565,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
     sR[buf][lane] = preR;
     if (FORM) sE[buf][col] = preE;
   };
-  // whether the tile meets the chunk W is at (G and near set for it)
+  // whether the tile meets the chunk W is at (G, near and scales set for it)
+  int scales = 0;
   auto meets = [&]() {
     if (!live || W.body == mybody) return false;
     if (W.body != cur) {
       cur = W.body;
       near = __any(mm_target(bodies[cur], mb[cur], xi, yi, zi, k, G));
+      scales = mm_undo(mb, colmax, cur, nrhs, r);
     }
     return true;
   };
@@ -601,6 +612,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
     use = meets();
     scaled = near;
     if (use) evaluate(0, 0, scaled);
+    S.e = scales;
+    summed = cur;
   }
   for (int i = 0; c0 < T.c1; ++i) {
     __syncthreads();
@@ -626,23 +639,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
 #pragma unroll 1
         for (int hc = 0; hc < 2; ++hc) {
           const float undo = scaled ? sU[p0][tile][hc] : 1.0f;
-          if (undo != 1.0f) S.flush(1.0);
+          if (undo != 1.0f) S.flush();
           multiply(p0, hc);
           if (undo != 1.0f) S.flush((double)undo);
         }
       }
     }
-    S.end_chunk();
+    S.end_chunk(summed != cur || c1 >= T.c1);
+    S.e = scales;
+    summed = cur;
     use = use1;
     scaled = near;
     c0 = c1;
     c1 = c2;
     c2 = c3;
   }
-  S.flush(1.0);
-  const int r = r0 + hw * 32 + col;
   if (!live || r >= nrhs) return;
-  const double sc = k * k * k / FOUR_PI / mm_sigma(colmax[(int64_t)T.problem * nrhs + r]);
+  const double sc = k * k * k / FOUR_PI;
   // element e of the lane: column l % 32, row 8 (e / 4) + 4 (l / 32) + e % 4
 #pragma unroll
   for (int e = 0; e < 16; ++e)
@@ -1031,7 +1044,7 @@ static size_t mm_pack_values(const qax_problem* p, int nrhs) {
 size_t mm_work_bytes(const qax_problem* p, int prec, int nrhs) {
   size_t b = align256((size_t)p->mm.slots * p->N * nrhs * 16);
   if (prec != QAX_FP64)
-    b += align256((size_t)p->n_problems * nrhs * 8) + mm_pack_values(p, nrhs) * sizeof(u32x4);
+    b += align256((size_t)p->n_bodies * nrhs * 8) + mm_pack_values(p, nrhs) * sizeof(u32x4);
   return b;
 }
 
@@ -1045,20 +1058,19 @@ hipError_t launch_pair_mmf(qax_problem* p, const double* mu, int nrhs, double* w
   };
   double2* partial = (double2*)take((size_t)p->mm.slots * p->N * nrhs * 16);
   const MmBody* mb = (const MmBody*)p->mm.d_bodies;
-  unsigned long long* colmax = (unsigned long long*)take((size_t)p->n_problems * nrhs * 8);
+  unsigned long long* colmax = (unsigned long long*)take((size_t)p->n_bodies * nrhs * 8);
   u32x4* pack = (u32x4*)m;
   const int form = p->form();
   const hipStream_t s = p->stream;
-  const int ncol = p->n_problems * nrhs;
+  const int64_t ncol = (int64_t)p->n_bodies * nrhs;
   const int64_t halves = p->N / 16;
   hipLaunchKernelGGL(mm_zero_kernel, dim3((unsigned)((ncol + 255) / 256)), dim3(256), 0, s, (uint64_t*)colmax, ncol);
   hipLaunchKernelGGL(mm_colmax_kernel, dim3((unsigned)((p->N + 255) / 256), (unsigned)((nrhs + 7) / 8)), dim3(256), 0,
-                     s, (const double2*)mu, p->N, nrhs, p->d_bodies, p->d_node_body, mb, colmax);
+                     s, (const double2*)mu, p->N, nrhs, p->d_node_body, colmax);
   for (int r0 = 0; r0 < nrhs; r0 += 64) {
     const int left = nrhs - r0, wide = left > 16, tiles = left > 32 ? 2 : 1;
     hipLaunchKernelGGL(mm_pack_kernel, dim3((unsigned)((halves * 64 + 255) / 256), (unsigned)tiles), dim3(256), 0, s,
-                       (const double2*)mu, halves, nrhs, r0, wide, tiles, p->d_bodies, p->d_node_body, mb, colmax,
-                       pack);
+                       (const double2*)mu, halves, nrhs, r0, wide, tiles, p->d_node_body, colmax, pack);
     auto go = [&](auto kern) {
       hipLaunchKernelGGL(kern, dim3((unsigned)(p->mm.n_tasks * tiles)), dim3(256), 0, s, p->mm.d_tasks, p->d_bodies,
                          p->d_node_body, p->d_pos, p->N, mb, (const u32x4*)p->mm.d_rec, p->mm.d_ewk, pack, colmax, nrhs, r0,
