@@ -259,6 +259,7 @@ struct qax_problem {
     float* d_ewk = nullptr;
     int n_tasks = 0;
     int slots = 1;
+    bool far = false;                   // bodies that see others from far off
   } mm;
   qax::Tune tune;
 

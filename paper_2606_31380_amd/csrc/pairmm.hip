@@ -12,6 +12,7 @@
 // n_theta is even), so the exclusion of pairs on one body is uniform over a
 // wavefront and a chunk.
 #include <algorithm>
+#include <cmath>
 #include <vector>
 
 #include "fastmath.h"
@@ -32,8 +33,9 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // is below 2^-22 of the product, of random sign).  Powers of two keep the
 // factors in range: K is scaled per source body by S_b so that the largest
 // entry that a target at least rho_b = R_b / 2 off the body's bounding ball
-// (radius R_b) can have is below 2^14, mu per source body and right-hand side by
-// sigma so that its largest entry there is below 2^15.  Sums are taken out of
+// (radius R_b) can have is below 2^14, for a tile of targets so far off that none
+// can pass 2^4 by what brings that bound up to 2^14 as well, mu per source body and
+// right-hand side by sigma so that its largest entry there is below 2^15.  Sums are taken out of
 // these scales where the sources' body changes, so that a body's densities keep
 // their digits beside another's larger ones, or ones that are not finite.
 __device__ __forceinline__ void split2(float x0, float x1, uint32_t& h, uint32_t& l) {
@@ -45,13 +47,28 @@ __device__ __forceinline__ void split2(float x0, float x1, uint32_t& h, uint32_t
   l = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, f16x2));
 }
 
-// Scale S_b of a body and the distance from its centre below which a target
-// is near: |K| k^3 / 4 pi <= |aw| / (k^2 r) (sqrt(1 + 1 / (k r)^2) + eta / k) / (4 pi / k^3)
-// (single layer: |aw| / (k^3 r)).
+// Scale S_b of a body and the distances from its centre below which a target
+// is near and above which it is far.  |K| 4 pi / k^3 <= (|aw| / k) t (sqrt(1 + t^2) + eta / k),
+// t = 1 / (k r) (single layer: (|aw| / k) t eta / k).
 struct MmBody {
-  float S, near2;   // near: |D|^2 below this
-  int32_t e;        // log2 S_b
+  float S, near2;        // near: |D|^2 below this
+  float kfar, kR, wk;    // far: k |D| above kfar; k R_b; S_b max |aw| / k
+  float ek;              // eta / k
+  int32_t e;             // log2 S_b
 };
+template <typename T>
+__host__ __device__ __forceinline__ T mm_bound(int form, T wk, T t, T ek) {
+  return wk * t * (form == 2 ? ek : sqrt((T)1 + t * t) + (form == 1 ? ek : (T)0));
+}
+
+// Distance from a body's centre beyond which the bound is 2^-10 of that at rho_b
+// (to a factor of two).
+__host__ __device__ __forceinline__ double mm_far(int form, double R, double k, double eta) {
+  const double lim = 0x1p-10 * mm_bound(form, 1.0, 2.0 / (k * R), eta / k);
+  double r = 0.5 * R;
+  while (r < 512.0 * R && mm_bound(form, 1.0, 1.0 / (k * r), eta / k) > lim) r *= 2.0;
+  return R + r;
+}
 
 __global__ __launch_bounds__(256) void mm_body_kernel(const BodyDev* __restrict__ bodies,
                                                       const float4* __restrict__ loc32,
@@ -77,15 +94,20 @@ __global__ __launch_bounds__(256) void mm_body_kernel(const BodyDev* __restrict_
   }
   if (threadIdx.x == 0) {
     const double R = 1.0001 * sqrt((double)s0[0]), W = 1.0001 * sqrt((double)s1[0]), k = B.k;
-    const double rho = 0.5 * R, q = 1.0 / (k * rho);
-    const double lim = W / (k * k * rho) *
-                       (form == 2 ? B.eta / k : sqrt(1.0 + q * q) + (form == 1 ? B.eta / k : 0.0));
+    const double rho = 0.5 * R, ek = B.eta / k;
+    const double lim = mm_bound(form, W / k, 1.0 / (k * rho), ek);
     int e = 0;
     (void)frexp(lim, &e);
     e = max(-120, min(120, 14 - e));
-    mb[blockIdx.x].e = e;
-    mb[blockIdx.x].S = (float)ldexp(1.0, e);
-    mb[blockIdx.x].near2 = (float)(1.0001 * (R + rho) * (R + rho));
+    MmBody M;
+    M.S = (float)ldexp(1.0, e);
+    M.near2 = (float)(1.0001 * (R + rho) * (R + rho));
+    M.kfar = (float)(k * mm_far(form, R, k, B.eta));
+    M.kR = (float)(k * R);
+    M.wk = (float)(W / k * ldexp(1.0, e));
+    M.ek = (float)ek;
+    M.e = e;
+    mb[blockIdx.x] = M;
   }
 }
 
@@ -214,8 +236,11 @@ struct MmTarget {   // per target and source body (see the reciprocal FP32 kerne
   float mx, my, mz, d2s, dns, ph0;
 };
 
-// The target at (x, y, z) against body B; returns whether it is near.
-__device__ __forceinline__ bool mm_target(const BodyDev& B, const MmBody& M, double x, double y, double z, double k,
+// The target at (x, y, z) against body B.  Returns how the wavefront's entries are
+// scaled beyond S_b: -1 by their sizes (a target is near), 0 not at all, else by
+// that power of two (all are far; FARS only).
+template <int FORM, int FARS>
+__device__ __forceinline__ int mm_target(const BodyDev& B, const MmBody& M, double x, double y, double z, double k,
                                           MmTarget& G) {
   const double c2 = 2.0 * k * k / TWO_PI;
   const double Dx = B.cen[0] - x, Dy = B.cen[1] - y, Dz = B.cen[2] - z;
@@ -229,7 +254,14 @@ __device__ __forceinline__ bool mm_target(const BodyDev& B, const MmBody& M, dou
   G.d2s = (float)(k * k * D2);
   G.dns = (float)(k * Dn);
   G.ph0 = (float)ph;
-  return !(D2 >= (double)M.near2);
+  if (__any(!(D2 >= (double)M.near2))) return -1;
+  if (!FARS || !__all(G.dns > M.kfar)) return 0;
+  float d = G.dns;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) d = fminf(d, __shfl_xor(d, o));
+  int e = 0;
+  (void)frexpf(mm_bound(FORM, M.wk, 1.0f / (d - M.kR), M.ek), &e);
+  return __builtin_amdgcn_readfirstlane(max(0, min(14 - e, 100)));
 }
 
 // K (in units of k^3 / 4 pi, scaled by the records' S) of a target and the
@@ -261,16 +293,24 @@ __device__ __forceinline__ void mm_eval(const float4 Y, const float4 W, float E,
 }
 
 // The A operands (h, l of Re K, h, l of Im K) of the lane's target and eight
-// sources with records at R and E.  With `near` set, entries beyond the bound
-// of S_b scale the whole half chunk down; returns the power of two that undoes
+// sources with records at R and E, scaled as mm_target says.  Near: entries beyond
+// the bound of S_b scale the whole half chunk down; returns the power of two that undoes
 // that (1 otherwise; entries that are not finite stay so).
-template <int FORM>
-__device__ __forceinline__ float mm_operands(const float4* R, const float* E, const MmTarget& G, bool near,
+template <int FORM, int FARS>
+__device__ __forceinline__ float mm_operands(const float4* R, const float* E, const MmTarget& G, int scaled,
                                              u32x4* f) {
   float kr[8], ki[8], undo = 1.0f;
 #pragma unroll
   for (int s = 0; s < 8; ++s) mm_eval<FORM>(R[2 * s], R[2 * s + 1], E[FORM ? s : 0], G, kr[s], ki[s]);
-  if (near) {
+  if (FARS && scaled > 0) {
+    const float g = ldexpf(1.0f, scaled);
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      kr[s] *= g;
+      ki[s] *= g;
+    }
+  }
+  if (scaled < 0) {
     float m = 0.0f;
 #pragma unroll
     for (int s = 0; s < 8; ++s) m = fmaxf(m, fmaxf(fabsf(kr[s]), fabsf(ki[s])));
@@ -410,7 +450,7 @@ struct MmWalk {
 // wavefronts per SIMD are 4 % faster than 3 and 2.  Bfloat16 in three parts (six
 // products, nine vector instructions more per pair) took 51 and 73 ms; moving
 // the products of one half chunk between the evaluations of the next gave nothing.
-template <int WIDE, int FORM>
+template <int WIDE, int FORM, int FARS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ? 3 : 4))) void pair_mmf_kernel(
     const MmTask* __restrict__ tasks, const BodyDev* __restrict__ bodies, const int32_t* __restrict__ node_body,
     const double* __restrict__ pos, int64_t N, const MmBody* __restrict__ mb, const u32x4* __restrict__ rec,
@@ -438,8 +478,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ? 3 : 
   MmSums<NA> S;
   S.clear();
   MmTarget G;
-  bool near = false;
-  int cur = -1, buf = 0;
+  int scaled = 0, cur = -1, buf = 0;
   MmWalk W(T, bodies);
   u32x4 pre[2], prec;
   float pew = 0.0f;
@@ -472,14 +511,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ? 3 : 
       if (W.body != cur) {
         cur = W.body;
         const int tc = wave * 32 + col;
-        near = __any(mm_target(bodies[cur], mb[cur], sX[0][tc], sX[1][tc], sX[2][tc], k, G));
-        S.e = mm_undo(mb, colmax, cur, nrhs, r0 + (WIDE ? col : (col & 15)));
+        scaled = mm_target<FORM, FARS>(bodies[cur], mb[cur], sX[0][tc], sX[1][tc], sX[2][tc], k, G);
+        S.e = mm_undo(mb, colmax, cur, nrhs, r0 + (WIDE ? col : (col & 15))) - (FARS ? max(scaled, 0) : 0);
       }
 #pragma unroll
       for (int hc = 0; hc < 2; ++hc) {
         u32x4 f[4];
-        const float undo = mm_operands<FORM>((const float4*)&sR[buf][(hc * 16 + half * 8) * 2],
-                                             &sE[buf][FORM ? hc * 16 + half * 8 : 0], G, near, f);
+        const float undo = mm_operands<FORM, FARS>((const float4*)&sR[buf][(hc * 16 + half * 8) * 2],
+                                             &sE[buf][FORM ? hc * 16 + half * 8 : 0], G, scaled, f);
         if (undo != 1.0f) S.flush();
         mm_products<WIDE>(f, &sB[buf][hc * 4 * 64 + lane], S.acc);
         if (undo != 1.0f) S.flush((double)undo);
@@ -507,7 +546,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ? 3 : 
 // so every entry of K is evaluated once for all 64: 82 ms on the 100 bodies
 // above, against 95 ms for two passes of the kernel above and 394 ms for the
 // per-target kernel.
-template <int FORM>
+template <int FORM, int FARS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void pair_mmf64_kernel(
     const MmTask* __restrict__ tasks, const BodyDev* __restrict__ bodies, const int32_t* __restrict__ node_body,
     const double* __restrict__ pos, int64_t N, const MmBody* __restrict__ mb, const u32x4* __restrict__ rec,
@@ -540,7 +579,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
   MmSums<2> S;
   S.clear();
   MmTarget G;
-  bool near = false;
+  int how = 0;                                   // mm_target's scaling of the body evaluated
   int cur = -1, summed = -1;                     // bodies evaluated, multiplied
   MmWalk W(T, bodies);
   u32x4 preB[4], preR;
@@ -565,23 +604,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
     sR[buf][lane] = preR;
     if (FORM) sE[buf][col] = preE;
   };
-  // whether the tile meets the chunk W is at (G, near and scales set for it)
+  // whether the tile meets the chunk W is at (G, how and scales set for it)
   int scales = 0;
   auto meets = [&]() {
     if (!live || W.body == mybody) return false;
     if (W.body != cur) {
       cur = W.body;
-      near = __any(mm_target(bodies[cur], mb[cur], xi, yi, zi, k, G));
-      scales = mm_undo(mb, colmax, cur, nrhs, r);
+      how = mm_target<FORM, FARS>(bodies[cur], mb[cur], xi, yi, zi, k, G);
+      scales = mm_undo(mb, colmax, cur, nrhs, r) - (FARS ? max(how, 0) : 0);
     }
     return true;
   };
   // K of the wavefront's half chunk, from record buffer rb to operand buffer ab
-  auto evaluate = [&](int rb, int ab, bool scaled) {
+  auto evaluate = [&](int rb, int ab, int scaled) {
     u32x4 f[4];
-    const float undo = mm_operands<FORM>((const float4*)&sR[rb][(hw * 16 + half * 8) * 2],
+    const float undo = mm_operands<FORM, FARS>((const float4*)&sR[rb][(hw * 16 + half * 8) * 2],
                                          &sE[rb][FORM ? hw * 16 + half * 8 : 0], G, scaled, f);
-    if (scaled && lane == 0) sU[ab][tile][hw] = undo;
+    if (scaled < 0 && lane == 0) sU[ab][tile][hw] = undo;
     u32x4* o = &sA[ab][tile][hw][lane];
 #pragma unroll
     for (int q = 0; q < 4; ++q) o[q * 64] = f[q];
@@ -597,7 +636,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
   // and the densities of i + 1 and the records of i + 2 stored into the buffers
   // that step i - 1 was the last to read
   int c0 = W.next(T.c0), c1 = W.next(c0 + 1), c2 = W.next(c1 + 1);
-  bool use = false, scaled = false;   // of chunk i
+  bool use = false;   // chunk i
+  int scaled = 0;
   if (c0 < T.c1) {
     fetch_b(c0);
     fetch_r(c0);
@@ -610,7 +650,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
     __syncthreads();
     W.start(c0, bodies, node_body);
     use = meets();
-    scaled = near;
+    scaled = how;
     if (use) evaluate(0, 0, scaled);
     S.e = scales;
     summed = cur;
@@ -628,17 +668,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
       W.to(c1, bodies);
       use1 = meets();
     }
-    if (use && use1 && !scaled && !near) {
+    if (use && use1 && scaled >= 0 && how == 0) {
       // no branch between the two products and the evaluation: 5 % faster
       multiply(p0, 0);
-      evaluate(p1, p1, false);
+      evaluate(p1, p1, 0);
       multiply(p0, 1);
     } else {
-      if (use1) evaluate(p1, p1, near);
+      if (use1) evaluate(p1, p1, how);
       if (use) {
 #pragma unroll 1
         for (int hc = 0; hc < 2; ++hc) {
-          const float undo = scaled ? sU[p0][tile][hc] : 1.0f;
+          const float undo = scaled < 0 ? sU[p0][tile][hc] : 1.0f;
           if (undo != 1.0f) S.flush();
           multiply(p0, hc);
           if (undo != 1.0f) S.flush((double)undo);
@@ -649,7 +689,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
     S.e = scales;
     summed = cur;
     use = use1;
-    scaled = near;
+    scaled = how;
     c0 = c1;
     c1 = c2;
     c2 = c3;
@@ -992,6 +1032,30 @@ static void plan_mm(qax_problem* p, int cu_count, std::vector<MmTask>& tasks) {
   });
 }
 
+// Whether a problem's bodies lie so far apart that tiles of targets may be far
+// from a body (mm_far): the kernels that look for them hold more registers (100
+// bodies of 2048 nodes: 32 right-hand sides 46.7 ms without, 49.5 with, 64 79.7 and
+// 81.2; bodies of radius 0.5 at k = 4 are far from 180 on, 17 at k = 0.01).
+static bool mm_any_far(const qax_problem* p) {
+  for (int pr = 0; pr < p->n_problems; ++pr) {
+    double lo[3], hi[3], reach = 1e300, big = 0.0;
+    for (int64_t b = p->prob_body0[pr]; b < p->prob_body0[pr + 1]; ++b) {
+      const BodyDev& B = p->hbodies[b];
+      // generous radii: the far distance grows with them
+      const double z = B.shape == QAX_SPHERE ? B.a : B.shape == QAX_SPHEROID ? B.c : B.a * (1.0 + B.c);
+      const double R = B.shape > QAX_PEANUT ? 3.2 * B.a : hypot(std::max(B.a, B.shape == QAX_PEANUT ? z : 0.0) + B.kappa * z * z, z);
+      reach = std::min(reach, mm_far(p->form(), R, B.k, B.eta));
+      big = std::max(big, R);
+      for (int c = 0; c < 3; ++c) {
+        lo[c] = b == p->prob_body0[pr] ? B.cen[c] : std::min(lo[c], B.cen[c]);
+        hi[c] = b == p->prob_body0[pr] ? B.cen[c] : std::max(hi[c], B.cen[c]);
+      }
+    }
+    if (hypot(hypot(hi[0] - lo[0], hi[1] - lo[1]), hi[2] - lo[2]) + big > reach) return true;
+  }
+  return false;
+}
+
 // The task table, and the bodies' scales and source records of the FP32 path
 // (functions of the geometry and the formulation), made on first use after a
 // build (not inside a capture).
@@ -1027,6 +1091,7 @@ hipError_t ensure_mm_plan(qax_problem* p, int cu_count) {
   M.d_rec = rec;
   M.d_ewk = ewk;
   M.n_tasks = (int)tasks.size();
+  M.far = mm_any_far(p);
   ++p->generation;
   return hipSuccess;
 }
@@ -1036,6 +1101,9 @@ void free_mm_plan(qax_problem* p) {
   p->mm.d_tasks = nullptr;
   p->mm.n_tasks = 0;
 }
+
+template <int V>
+using I = std::integral_constant<int, V>;
 
 static size_t mm_pack_values(const qax_problem* p, int nrhs) {
   return (size_t)(p->N / MM_C) * (nrhs > 32 ? 16 : 8) * 64;
@@ -1076,17 +1144,17 @@ hipError_t launch_pair_mmf(qax_problem* p, const double* mu, int nrhs, double* w
                          p->d_node_body, p->d_pos, p->N, mb, (const u32x4*)p->mm.d_rec, p->mm.d_ewk, pack, colmax, nrhs, r0,
                          p->seg_active, partial);
     };
-    if (tiles == 2) go(form == 1 ? pair_mmf64_kernel<1> : form == 2 ? pair_mmf64_kernel<2> : pair_mmf64_kernel<0>);
-    else if (wide) go(form == 1 ? pair_mmf_kernel<1, 1> : form == 2 ? pair_mmf_kernel<1, 2> : pair_mmf_kernel<1, 0>);
-    else go(form == 1 ? pair_mmf_kernel<0, 1> : form == 2 ? pair_mmf_kernel<0, 2> : pair_mmf_kernel<0, 0>);
+    auto forms = [&](auto fm, auto fars) {
+      constexpr int FM = decltype(fm)::value, FARS = decltype(fars)::value;
+      go(tiles == 2 ? pair_mmf64_kernel<FM, FARS> : wide ? pair_mmf_kernel<1, FM, FARS> : pair_mmf_kernel<0, FM, FARS>);
+    };
+    auto bodies = [&](auto fm) { p->mm.far ? forms(fm, I<1>{}) : forms(fm, I<0>{}); };
+    form == 1 ? bodies(I<1>{}) : form == 2 ? bodies(I<2>{}) : bodies(I<0>{});
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
-
-template <int V>
-using I = std::integral_constant<int, V>;
 
 // FP64 sums over the pair-sum tasks or other targets, right-hand sides 32 at a time.
 template <int FORM, bool PAIRS>

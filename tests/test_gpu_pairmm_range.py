@@ -65,6 +65,21 @@ def close(got, K, mu, tol, rows=slice(None)):
 
 
 @pytest.mark.parametrize("nrhs", COUNTS)
+@pytest.mark.parametrize("form", sorted(FORMS))
+@pytest.mark.parametrize("dist,k", [(300.0, 0.01), (1e3, 0.01), (1e3, 1e-3), (1e4, 1e-3), (1e4, 1e-4), (1e5, 1e-6)])
+def test_bodies_far_apart(dist, k, form, nrhs):
+    # two a few radii apart, one far off: targets of every scale in a tile's bodies
+    s = spheres(k, [(1.0, 20, (0.0, 0.0, 0.0)), (0.5, 14, (0.8 * dist, 0.0, 0.6 * dist)), (0.7, 10, (3.0, 1.0, 0.0))])
+    mu = densities(s.n_unknowns(), nrhs)
+    K, d = matrix(s, form)
+    with qax.Problem(s, formulation=FORMS[form]) as P:
+        close(run(P, mu), K, mu, 1e-6)
+        for b in range(3):                  # one body's sources at a time
+            one = np.where((d.body == b)[:, None], mu, 0.0)
+            close(run(P, one), K, one, 1e-6)
+
+
+@pytest.mark.parametrize("nrhs", COUNTS)
 def test_densities_apart_between_bodies(nrhs):
     # 2^-60 ... 2^60 from body to body and per column: rows that see the small ones only
     s = spheres(3.0, [(0.5, 12, (0.0, 0.0, 0.0)), (0.5, 8, (2.0, 0.0, 0.0)), (0.4, 10, (0.0, 9.0, 0.0))])
