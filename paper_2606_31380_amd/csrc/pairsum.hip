@@ -1574,9 +1574,9 @@ static void launch_any(qax_problem* p, bool f64, int tpb, int nrc, const double*
 // [1e-6, 1e6]; FP32 powers of k r overflow beyond): two right-hand sides take
 // 33 ms against the per-target kernel's 42 ms on 100 bodies of 2048 nodes in
 // FP32 (FP64, 40 bodies: 10.3 against 17.4 ms), and the ratio grows with their
-// number.
+// number.  Not while the array apply is on, which takes every pair sum.
 bool pair_uses_mm(const qax_problem* p, int nrhs) {
-  if (nrhs < 2) return false;
+  if (nrhs < 2 || p->lat.active) return false;
   for (double k : p->k)
     if (!mm_k_ok(k)) return false;
   return true;
@@ -1594,9 +1594,10 @@ hipError_t ensure_pair_plan(qax_problem* p, int prec, int nrhs) {
 // task table was planned with; right-hand sides per pass from the tuning
 // (clamped to a supported configuration).
 size_t pair_work_bytes(const qax_problem* p, int prec, int nrhs) {
-  if (pair_uses_mm(p, nrhs)) return std::max(mm_work_bytes(p, prec, nrhs), lattice_work_bytes(p, nrhs));
+  if (p->lat.active) return lattice_work_bytes(p, nrhs);
+  if (pair_uses_mm(p, nrhs)) return mm_work_bytes(p, prec, nrhs);
   const int slots = prec == QAX_FP64 ? p->slots64 : p->slots32;
-  size_t b = std::max((size_t)slots * p->N * nrhs * 16, lattice_work_bytes(p, nrhs));
+  size_t b = (size_t)slots * p->N * nrhs * 16;
   if (nrhs == 1 && p->sym.ok)
     b = std::max(b, (size_t)p->sym.plan[prec == QAX_FP64 ? 0 : 1].max_slots * (prec == QAX_FP64 ? 16 : 8));
   return b;
