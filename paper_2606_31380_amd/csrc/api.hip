@@ -205,7 +205,7 @@ extern "C" qax_status qax_create(int device, void* hip_stream, qax_problem** out
   return QAX_OK;
 }
 
-// The reciprocal pair sums' blocks and plans (a function of the node ranges
+// The pair sums' blocks, plans and tasks (a function of the node ranges
 // of the bodies and problems and of the wavenumbers only).
 static void free_pair_plans(qax_problem* p) {
   dev_release(p, p->sym.d_bmem);
@@ -213,6 +213,7 @@ static void free_pair_plans(qax_problem* p) {
   for (int pi = 0; pi < 2; ++pi) (void)release_sym_plan(p, pi);
   p->sym.blocks.clear();
   p->sym.key.clear();
+  free_mm_tasks(p);
 }
 
 static void free_geometry(qax_problem* p, bool keep_plans = false) {
@@ -229,7 +230,7 @@ static void free_geometry(qax_problem* p, bool keep_plans = false) {
   p->d_ew = nullptr; p->d_ew32 = nullptr;
   dev_release(p, p->d_gemm_tasks);
   p->d_gemm_tasks = nullptr;
-  free_mm_plan(p);
+  free_mm_records(p);
   if (!keep_plans) free_pair_plans(p);
   free_sym_apply(p);
   p->gemm_tasks.clear();
@@ -284,7 +285,7 @@ extern "C" qax_status qax_set_formulation(qax_problem* p, int32_t formulation, d
   QCHECK(hipSetDevice(p->device), "hipSetDevice");
   QCHECK(hipStreamSynchronize(p->stream), "sync");
   lattice_free(p);
-  free_mm_plan(p);
+  free_mm_records(p);
   for (auto& d : p->hbodies) d.eta = p->eta_of(d.k);
   QCHECK(hipMemcpyAsync(p->d_bodies, p->hbodies.data(), sizeof(BodyDev) * p->hbodies.size(),
                         hipMemcpyHostToDevice, p->stream), "copy bodies");

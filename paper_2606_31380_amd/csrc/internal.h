@@ -250,14 +250,15 @@ struct qax_problem {
       int64_t* d_list = nullptr;
     } plan[2];                        // [0] FP64, [1] FP32
   } sym;
-  // matrix-core pair sums (several right-hand sides, k > 0 in every problem):
-  // made on first use after a build, one allocation from d_tasks on
+  // matrix-core pair sums (several right-hand sides, k > 0 in every problem),
+  // made on first use (ensure_mm_plan)
   struct Mm {
+    std::vector<qax::MmTask> tasks;     // kept for their upload
     qax::MmTask* d_tasks = nullptr;
+    void* d_mem = nullptr;              // FP32, one allocation:
     void* d_bodies = nullptr;           // scale and near distance per body
-    void* d_rec = nullptr;              // FP32 source records, 32 bytes per node
+    void* d_rec = nullptr;              // source records, 32 bytes per node
     float* d_ewk = nullptr;
-    int n_tasks = 0;
     int slots = 1;
     bool far = false;                   // bodies that see others from far off
   } mm;
@@ -365,8 +366,9 @@ int sym_default_s(const qax_problem* p, int cu_count);
 // launch choices the kernels support (LDS within 64 KB)
 bool pair_config_ok(int prec, int tpb, int nrc);
 // pairmm.hip
-hipError_t ensure_mm_plan(qax_problem* p, int cu_count);
-void free_mm_plan(qax_problem* p);
+hipError_t ensure_mm_plan(qax_problem* p, int prec, int cu_count);
+void free_mm_records(qax_problem* p);
+void free_mm_tasks(qax_problem* p);
 size_t mm_work_bytes(const qax_problem* p, int prec, int nrhs);
 int mm_slots(const qax_problem* p, int64_t count, int prob0, int nprob, int cu_count);
 hipError_t launch_mm_near(qax_problem* p, const double* mu, int nrhs, const double* pts, int64_t M, int problem,

@@ -1003,33 +1003,47 @@ static void plan_mm(qax_problem* p, int cu_count, std::vector<MmTask>& tasks) {
   int64_t slots = (24LL * cu_count + tblocks - 1) / std::max<int64_t>(tblocks, 1);
   slots = std::max<int64_t>(1, std::min<int64_t>({slots, 32, cmax / 8}));
   M.slots = (int)slots;
-  tasks.clear();
+  // the body that holds every target of a block, or -1
+  std::vector<int32_t> body;
+  body.reserve(tblocks);
+  // a problem's tasks take at most four costs (whole and last blocks, source
+  // ranges a chunk apart): listed class by class
+  struct Class { int64_t cost, block0; int32_t pr; bool last, longer; };
+  std::vector<Class> classes;
   for (int pr = 0; pr < p->n_problems; ++pr) {
     const int b0 = (int)p->prob_body0[pr], b1 = (int)p->prob_body0[pr + 1];
-    const int64_t n0 = p->off[b0], n1 = p->off[b1];
-    const int64_t c0 = n0 / MM_C, nc = (n1 - n0) / MM_C;
+    const int64_t n0 = p->off[b0], n1 = p->off[b1], q = (n1 - n0) / MM_C / slots;
+    const int64_t block0 = (int64_t)body.size();
     int lo = b0;
     for (int64_t t0 = n0; t0 < n1; t0 += MM_T) {
-      const int nt = (int)std::min<int64_t>(MM_T, n1 - t0);
       while (lo + 1 < b1 && p->off[lo + 1] <= t0) ++lo;
-      const bool one = p->off[lo + 1] >= t0 + nt;
+      body.push_back(p->off[lo + 1] >= std::min<int64_t>(t0 + MM_T, n1) ? lo : -1);
+    }
+    for (int last = 0; last < 2; ++last)
+      for (int longer = 0; longer < 2; ++longer)
+        classes.push_back(Class{(last ? (n1 - n0) % MM_T : MM_T) * (q + longer), block0, pr, last != 0, longer != 0});
+  }
+  std::stable_sort(classes.begin(), classes.end(), [](const Class& a, const Class& b) { return a.cost > b.cost; });
+  tasks.clear();
+  tasks.reserve((size_t)(tblocks * slots));
+  for (const Class& C : classes) {
+    const int64_t n0 = p->off[p->prob_body0[C.pr]], n1 = p->off[p->prob_body0[C.pr + 1]];
+    const int64_t c0 = n0 / MM_C, nc = (n1 - n0) / MM_C, whole = (n1 - n0) / MM_T;
+    const int64_t end = C.last ? (n1 - n0 + MM_T - 1) / MM_T : whole;
+    for (int64_t b = C.last ? whole : 0; b < end; ++b)
       for (int s = 0; s < slots; ++s) {
         MmTask T;
-        T.t0 = t0;
-        T.nt = nt;
+        T.t0 = n0 + b * MM_T;
+        T.nt = (int32_t)std::min<int64_t>(MM_T, n1 - T.t0);
         T.c0 = (int32_t)(c0 + nc * s / slots);
         T.c1 = (int32_t)(c0 + nc * (s + 1) / slots);
         T.slot = s;
-        T.body = one ? lo : -1;
-        T.problem = pr;
-        T.k = p->k[pr];
-        tasks.push_back(T);
+        T.body = body[C.block0 + b];
+        T.problem = C.pr;
+        T.k = p->k[C.pr];
+        if ((T.c1 - T.c0 > nc / slots) == C.longer) tasks.push_back(T);
       }
-    }
   }
-  std::stable_sort(tasks.begin(), tasks.end(), [](const MmTask& a, const MmTask& b) {
-    return (int64_t)a.nt * (a.c1 - a.c0) > (int64_t)b.nt * (b.c1 - b.c0);
-  });
 }
 
 // Whether a problem's bodies lie so far apart that tiles of targets may be far
@@ -1056,50 +1070,55 @@ static bool mm_any_far(const qax_problem* p) {
   return false;
 }
 
-// The task table, and the bodies' scales and source records of the FP32 path
-// (functions of the geometry and the formulation), made on first use after a
-// build (not inside a capture).
-hipError_t ensure_mm_plan(qax_problem* p, int cu_count) {
+// Made on first use (not inside a capture; nothing here waits): the task table, a
+// function of the node ranges and wavenumbers, which a rebuild that keeps them
+// keeps too, and for FP32 the bodies' scales and source records, functions of the
+// geometry and the formulation.  First call after a build, above the next ones:
+// N = 5120 44 us and N = 44,800 128 with both made, sorted and waited for each
+// time; 3 to 15 now with the table kept, 18 to 54 with another.
+hipError_t ensure_mm_plan(qax_problem* p, int prec, int cu_count) {
   auto& M = p->mm;
-  if (M.d_tasks) return hipSuccess;
-  std::vector<MmTask> tasks;
-  plan_mm(p, cu_count, tasks);
-  const size_t bt = align256(sizeof(MmTask) * tasks.size()), bb = align256(sizeof(MmBody) * p->n_bodies),
-               br = align256((size_t)p->N * 32);
-  char* m = nullptr;
-  hipError_t e = dev_alloc(p, (void**)&m, bt + bb + br + (size_t)p->N * 4);
-  if (e != hipSuccess) return e;
-  MmBody* mb = (MmBody*)(m + bt);
-  float4* rec = (float4*)(m + bt + bb);
-  float* ewk = (float*)(m + bt + bb + br);
-  e = hipMemcpyAsync(m, tasks.data(), sizeof(MmTask) * tasks.size(), hipMemcpyHostToDevice, p->stream);
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL(mm_body_kernel, dim3((unsigned)p->n_bodies), dim3(256), 0, p->stream, p->d_bodies,
-                       (const float4*)p->d_loc32, (const float4*)p->d_aw32, p->form(), mb);
-    hipLaunchKernelGGL(mm_records_kernel, dim3((unsigned)((p->N + 255) / 256)), dim3(256), 0, p->stream, p->d_bodies,
-                       p->d_node_body, (const float4*)p->d_loc32, (const float4*)p->d_aw32, p->d_ew32, mb, p->N, rec,
-                       ewk);
-    e = hipGetLastError();
+  hipError_t e = hipSuccess;
+  if (!M.d_tasks) {
+    plan_mm(p, cu_count, M.tasks);
+    if ((e = dev_alloc(p, (void**)&M.d_tasks, sizeof(MmTask) * M.tasks.size())) != hipSuccess) return e;
+    e = hipMemcpyAsync(M.d_tasks, M.tasks.data(), sizeof(MmTask) * M.tasks.size(), hipMemcpyHostToDevice, p->stream);
+    if (e != hipSuccess) {
+      free_mm_tasks(p);
+      return e;
+    }
+    ++p->generation;
   }
-  if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
-  if (e != hipSuccess) {
-    dev_release(p, m);
-    return e;
-  }
-  M.d_tasks = (MmTask*)m;
-  M.d_bodies = mb;
-  M.d_rec = rec;
-  M.d_ewk = ewk;
-  M.n_tasks = (int)tasks.size();
+  if (prec == QAX_FP64 || M.d_mem) return hipSuccess;
+  const size_t bb = align256(sizeof(MmBody) * p->n_bodies), br = align256((size_t)p->N * 32);
+  if ((e = dev_alloc(p, &M.d_mem, bb + br + (size_t)p->N * 4)) != hipSuccess) return e;
+  char* m = (char*)M.d_mem;
+  M.d_bodies = m;
+  M.d_rec = m + bb;
+  M.d_ewk = (float*)(m + bb + br);
   M.far = mm_any_far(p);
+  hipLaunchKernelGGL(mm_body_kernel, dim3((unsigned)p->n_bodies), dim3(256), 0, p->stream, p->d_bodies,
+                     (const float4*)p->d_loc32, (const float4*)p->d_aw32, p->form(), (MmBody*)M.d_bodies);
+  hipLaunchKernelGGL(mm_records_kernel, dim3((unsigned)((p->N + 255) / 256)), dim3(256), 0, p->stream, p->d_bodies,
+                     p->d_node_body, (const float4*)p->d_loc32, (const float4*)p->d_aw32, p->d_ew32,
+                     (const MmBody*)M.d_bodies, p->N, (float4*)M.d_rec, M.d_ewk);
+  e = hipGetLastError();
+  if (e != hipSuccess) free_mm_records(p);
   ++p->generation;
-  return hipSuccess;
+  return e;
 }
 
-void free_mm_plan(qax_problem* p) {
+// after a change of the geometry or formulation
+void free_mm_records(qax_problem* p) {
+  dev_release(p, p->mm.d_mem);
+  p->mm.d_mem = nullptr;
+}
+
+// after a change of the node ranges or wavenumbers
+void free_mm_tasks(qax_problem* p) {
   dev_release(p, p->mm.d_tasks);
   p->mm.d_tasks = nullptr;
-  p->mm.n_tasks = 0;
+  p->mm.tasks.clear();
 }
 
 template <int V>
@@ -1140,7 +1159,7 @@ hipError_t launch_pair_mmf(qax_problem* p, const double* mu, int nrhs, double* w
     hipLaunchKernelGGL(mm_pack_kernel, dim3((unsigned)((halves * 64 + 255) / 256), (unsigned)tiles), dim3(256), 0, s,
                        (const double2*)mu, halves, nrhs, r0, wide, tiles, p->d_node_body, colmax, pack);
     auto go = [&](auto kern) {
-      hipLaunchKernelGGL(kern, dim3((unsigned)(p->mm.n_tasks * tiles)), dim3(256), 0, s, p->mm.d_tasks, p->d_bodies,
+      hipLaunchKernelGGL(kern, dim3((unsigned)(p->mm.tasks.size() * tiles)), dim3(256), 0, s, p->mm.d_tasks, p->d_bodies,
                          p->d_node_body, p->d_pos, p->N, mb, (const u32x4*)p->mm.d_rec, p->mm.d_ewk, pack, colmax, nrhs, r0,
                          p->seg_active, partial);
     };
@@ -1193,7 +1212,7 @@ static hipError_t launch_mm_forms(qax_problem* p, const MmTask* tasks, const MmT
 // Partial sums of the FP64 pair sum (slots x N x nrhs at `work`).
 hipError_t launch_pair_mmd(qax_problem* p, const double* mu, int nrhs, double* work) {
   const MmTargets P = {p->d_pos, 1, p->N, p->N, nullptr, p->N, nullptr, 0, 0};
-  return launch_mm_forms<MM_DOUBLE, false>(p, p->mm.d_tasks, P, dim3((unsigned)p->mm.n_tasks), mu, nrhs, work);
+  return launch_mm_forms<MM_DOUBLE, false>(p, p->mm.d_tasks, P, dim3((unsigned)p->mm.tasks.size()), mu, nrhs, work);
 }
 
 // Ranges of the sources for `count` targets of `nprob` problems from prob0 on:

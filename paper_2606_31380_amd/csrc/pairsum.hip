@@ -1583,10 +1583,10 @@ bool pair_uses_mm(const qax_problem* p, int nrhs) {
 }
 
 hipError_t ensure_pair_plan(qax_problem* p, int prec, int nrhs) {
-  if (!pair_uses_mm(p, nrhs) || p->mm.d_tasks) return hipSuccess;
+  if (!pair_uses_mm(p, nrhs) || (p->mm.d_tasks && (prec == QAX_FP64 || p->mm.d_mem))) return hipSuccess;
   int cus = 0;
   hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device);
-  return e == hipSuccess ? ensure_mm_plan(p, std::max(cus, 1)) : e;
+  return e == hipSuccess ? ensure_mm_plan(p, prec, std::max(cus, 1)) : e;
 }
 
 // partial: slots x N x nrhs complex128 workspace; out = pair sum, plus base
@@ -1678,7 +1678,7 @@ hipError_t launch_pair_sum(qax_problem* p, int prec, const double* mu, double* o
     return hipSuccess;
   }
   if (pair_uses_mm(p, nrhs)) {
-    if (!p->mm.d_tasks) return hipErrorInvalidConfiguration;
+    if (!p->mm.d_tasks || !(f64 || p->mm.d_mem)) return hipErrorInvalidConfiguration;
     timing_begin(p, kind);
     hipError_t e = f64 ? launch_pair_mmd(p, mu, nrhs, partial) : launch_pair_mmf(p, mu, nrhs, partial);
     timing_end(p, kind);
