@@ -245,10 +245,11 @@ qax_status qax_solve_dense(qax_problem* p, const double* dirs, int32_t nrhs, voi
  * far-field pattern, in its double-layer form):
  * u_inf_p(xhat) = (1/4 pi) sum_{j in p} (-i k_p xhat.n_j) e^{-i k_p xhat.y_j}
  * mu_j |J_j| w_j (combined field: plus -i eta |J_j| w_j e^{...}; single layer:
- * |J_j| w_j e^{...} mu_j alone).  xhat: host, n_dirs x 3 (finite; where an
- * eighth of the directions or more are pairs of a direction and its exact
- * negation, those share one phase evaluation, with the same results).  d_mu: N x nrhs; d_u_inf: n_problems x n_dirs x nrhs
- * complex128 (problem, then direction, then right-hand side). */
+ * |J_j| w_j e^{...} mu_j alone).  xhat: host, n_dirs x 3 (finite; where pairs
+ * of a direction and its exact negation number at least an eighth of n_dirs,
+ * each pair shares its phase evaluations, with the same results).  d_mu:
+ * N x nrhs; d_u_inf: n_problems x n_dirs x nrhs complex128 (problem, then
+ * direction, then right-hand side). */
 qax_status qax_farfield(qax_problem* p, const void* d_mu, int32_t nrhs,
                         const double* xhat, int32_t n_dirs, void* d_u_inf);
 

@@ -721,7 +721,7 @@ extern "C" qax_status qax_farfield(qax_problem* p, const void* d_mu, int32_t nrh
     }
     // a few pairs are not worth a launch of their own (50 of them among 40,000
     // directions took 108 us for their share of 6 us)
-    if (n_pairs < n_dirs / 8) {
+    if (8 * (int64_t)n_pairs < n_dirs) {
       n_pairs = 0;
       std::fill(partner.begin(), partner.end(), -1);
     }
