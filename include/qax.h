@@ -134,8 +134,8 @@ qax_status qax_nodes(const qax_problem* p, double* d_pos, double* d_aw);
 /* Assemble every distinct self block B = 1/2 I + D_bb in FP64 (Sections
  * 3.1-3.4: modal Green's functions by recurrence, FFT and convolution; product
  * integration in s), then factor it: by default its inverse is computed in
- * FP64 (Gauss-Jordan with partial pivoting; the block-diagonal preconditioner
- * of Section 6) and B^-1 is rounded to FP32 for the mixed path (B itself is
+ * FP64 (Gauss-Jordan on the diagonal, with partial pivoting where that is not
+ * safe; the block-diagonal preconditioner of Section 6) and B^-1 is rounded to FP32 for the mixed path (B itself is
  * rounded to FP32 by the first call that applies it in FP32).  Bodies mapped
  * onto themselves by both reflections theta -> -theta and t -> -t (sphere,
  * spheroid and peanut, bent or not, and the quasi-ellipsoid) have a quarter of their rows assembled
@@ -224,9 +224,12 @@ qax_status qax_set_solver(qax_problem* p, int32_t solver);
 qax_status qax_solve_rhs(qax_problem* p, qax_prec prec, const void* d_rhs, int32_t nrhs,
                          double tol, int32_t maxit, void* d_mu_out, qax_info* info);
 
-/* Batched in-place inversion of caller matrices with the Gauss-Jordan
- * elimination (partial pivoting, 128-column panels) that inverts the self
- * blocks for the block-diagonal preconditioner of the hybrid solver (Section 6):
+/* Batched in-place inversion of caller matrices by Gauss-Jordan elimination
+ * with partial pivoting throughout (128-column panels).  qax_assemble_self
+ * inverts with it what QAX_MIXED factorisations ask for in FP32; its FP64
+ * inverses (Section 6) are eliminated on the diagonal in 64-column panels and
+ * come here only where that is flagged as unsafe, so this call does not show
+ * their accuracy.
  * d_mats holds `count` complex128 matrices, orders[i] x orders[i] each
  * (host array, orders in [1, 8192]), row-major, stored one after another;
  * each is replaced by its inverse.  prec QAX_FP64 inverts in FP64;
