@@ -347,9 +347,9 @@ static void block_mm_launch(hipStream_t s, const GemmTask* tasks, int ntasks, co
                             bool accumulate, const int32_t* seg_active) {
   auto go = [&](auto nt) {
     constexpr int NT = decltype(nt)::value;
-    hipLaunchKernelGGL((block_mm_kernel<MT, VEC, NT>), dim3((unsigned)ntasks, (unsigned)((nrhs + 8 * NT - 1) / (8 * NT))),
-                       dim3(256), 0, s, tasks, bodies, blocks, (const MT*)pool, (const double2*)v, nrhs,
-                       (double2*)out, accumulate ? 1 : 0, seg_active);
+    const dim3 grid((unsigned)ntasks, (unsigned)((nrhs + 8 * NT - 1) / (8 * NT)));
+    hipLaunchKernelGGL((block_mm_kernel<MT, VEC, NT>), grid, dim3(256), 0, s, tasks, bodies, blocks, (const MT*)pool,
+                       (const double2*)v, nrhs, (double2*)out, accumulate ? 1 : 0, seg_active);
   };
   // as few passes over the matrix as 32 right-hand sides each allow, evenly wide
   // (16 at a time instead: 24 right-hand sides 413 us against 350)

@@ -130,13 +130,13 @@ __device__ __forceinline__ void sincos_tab512_scaled(double x, double u, double 
   *cp = fma(T.y, Cm1, fma(-T.x, S, T.y));
 }
 
-// The table for sincos_tab512: (sin, cos)(2 pi i / 512) in tab[i], filled by
+// The table for sincos_tab512: f (sin, cos)(2 pi i / 512) in tab[i], filled by
 // the `nthreads` threads of a workgroup (a barrier must follow before use).
-__device__ __forceinline__ void fill_tab512(double2* tab, int tid, int nthreads) {
+__device__ __forceinline__ void fill_tab512(double2* tab, int tid, int nthreads, double f = 1.0) {
   for (int i = tid; i < 512; i += nthreads) {
     double s, c;
     sincos_2pi(i * (1.0 / 512.0), &s, &c);
-    tab[i] = make_double2(s, c);
+    tab[i] = make_double2(f * s, f * c);
   }
 }
 

@@ -243,7 +243,7 @@ struct qax_problem {
       std::vector<int64_t> lptr;           // per launch: n_blocks + 1 list offsets
       std::vector<int64_t> list;           // slot offsets
       int64_t max_slots = 0;               // complex values of the largest launch
-    size_t bytes = 0;        // of d_mem
+      size_t bytes = 0;                    // of d_mem
       void* d_mem = nullptr;
       qax::SymSuper* d_supers = nullptr;
       int64_t* d_lptr = nullptr;

@@ -19,8 +19,6 @@
 
 namespace qax {
 
-constexpr double INV_FOUR_PI_K = 0.0795774715459476678844;
-
 __global__ void rhs_kernel(const BodyDev* __restrict__ bodies, const int32_t* __restrict__ node_body,
                            const double* __restrict__ pos, int64_t N, const double* __restrict__ dirs,
                            int nrhs, double2* __restrict__ out) {
@@ -300,8 +298,8 @@ void Krylov::dots(const double* V, int64_t vstride, int m, const double* w, doub
   const int nthr = (256 / nrhs) * nrhs;
   hipLaunchKernelGGL(mdot_kernel, dim3(nchunks, m), dim3(nthr), 0, stream, (const double2*)V,
                      vstride / 2, (const double2*)w, nrhs, d_chunks, (double2*)d_partial, nchunks);
-  hipLaunchKernelGGL(mdot_reduce_kernel, dim3((unsigned)(nprob * nrhs), m), dim3(64), 0, stream, (const double2*)d_partial, nchunks, nrhs, d_prob_chunk0, nprob,
-                     (double2*)h);
+  hipLaunchKernelGGL(mdot_reduce_kernel, dim3((unsigned)(nprob * nrhs), m), dim3(64), 0, stream,
+                     (const double2*)d_partial, nchunks, nrhs, d_prob_chunk0, nprob, (double2*)h);
 }
 
 void Krylov::orth(const double* V, int64_t vstride, int m, const double* h, double* w) {

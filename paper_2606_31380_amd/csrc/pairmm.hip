@@ -797,11 +797,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT > 2 ? 2 
   __shared__ double sE[2][EW ? MM_C : 1];        // ew (ew / k)
   __shared__ double2 sM[2][NM][MM_C][8];
   __shared__ double2 sTab[512];
-  for (int i = tid; i < 512; i += 256) {         // ordered by the first chunk's barrier
-    double s, c;
-    sincos_2pi(i * (1.0 / 512.0), &s, &c);
-    sTab[i] = FAR ? make_double2(s, c) : make_double2(k * s, k * c);
-  }
+  fill_tab512(sTab, tid, 256, FAR ? 1.0 : k);    // ordered by the first chunk's barrier
 
   f64x4 acc[2][NT ? NT : 1];
   double vr[2][VEC ? VEC : 1], vi[2][VEC ? VEC : 1];
@@ -1057,7 +1053,8 @@ static bool mm_any_far(const qax_problem* p) {
       const BodyDev& B = p->hbodies[b];
       // generous radii: the far distance grows with them
       const double z = B.shape == QAX_SPHERE ? B.a : B.shape == QAX_SPHEROID ? B.c : B.a * (1.0 + B.c);
-      const double R = B.shape > QAX_PEANUT ? 3.2 * B.a : hypot(std::max(B.a, B.shape == QAX_PEANUT ? z : 0.0) + B.kappa * z * z, z);
+      const double x = std::max(B.a, B.shape == QAX_PEANUT ? z : 0.0) + B.kappa * z * z;
+      const double R = B.shape > QAX_PEANUT ? 3.2 * B.a : hypot(x, z);
       reach = std::min(reach, mm_far(p->form(), R, B.k, B.eta));
       big = std::max(big, R);
       for (int c = 0; c < 3; ++c) {
@@ -1159,9 +1156,9 @@ hipError_t launch_pair_mmf(qax_problem* p, const double* mu, int nrhs, double* w
     hipLaunchKernelGGL(mm_pack_kernel, dim3((unsigned)((halves * 64 + 255) / 256), (unsigned)tiles), dim3(256), 0, s,
                        (const double2*)mu, halves, nrhs, r0, wide, tiles, p->d_node_body, colmax, pack);
     auto go = [&](auto kern) {
-      hipLaunchKernelGGL(kern, dim3((unsigned)(p->mm.tasks.size() * tiles)), dim3(256), 0, s, p->mm.d_tasks, p->d_bodies,
-                         p->d_node_body, p->d_pos, p->N, mb, (const u32x4*)p->mm.d_rec, p->mm.d_ewk, pack, colmax, nrhs, r0,
-                         p->seg_active, partial);
+      hipLaunchKernelGGL(kern, dim3((unsigned)(p->mm.tasks.size() * tiles)), dim3(256), 0, s, p->mm.d_tasks,
+                         p->d_bodies, p->d_node_body, p->d_pos, p->N, mb, (const u32x4*)p->mm.d_rec, p->mm.d_ewk,
+                         pack, colmax, nrhs, r0, p->seg_active, partial);
     };
     auto forms = [&](auto fm, auto fars) {
       constexpr int FM = decltype(fm)::value, FARS = decltype(fars)::value;

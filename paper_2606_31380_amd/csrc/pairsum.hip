@@ -37,7 +37,6 @@ namespace qax {
 
 constexpr double INV_FOUR_PI = 0.0795774715459476678844;
 
-
 // Lockstep solves pass seg_active[problem * nrhs + r] (0 once that GMRES
 // segment has converged in the current cycle; its basis vectors are then
 // zero).  A task none of whose right-hand sides is active writes zeros to its

@@ -305,9 +305,10 @@ __device__ __forceinline__ double toroidal_q_batch(bool act, double chi, const Q
 // position of twiddle q in the padded table (see below)
 __device__ __forceinline__ int twi(int q) { return q + (q >> 4); }
 
-// sin and cos of 2 pi t from the twiddle table (tw[twi(q)] = e^{-2 pi i q /
-// LD}): the nearest entry turned by the remainder |g| <= 1/512, whose series
-// end below 1e-19.
+// sin and cos of 2 pi t (|t| < 2^31 / LD, k rho of 5e7: far beyond what the
+// azimuths resolve) from the twiddle table (tw[twi(q)] = e^{-2 pi i q / LD}):
+// the nearest entry turned by the remainder |g| <= 1/512, whose series end
+// below 1e-19.
 __device__ __forceinline__ void sincos_tw(double t, const double2* tw, double* sp, double* cp) {
   const double n = rint(t * LD);
   const double g = fma(n, -1.0 / LD, t);
