@@ -1251,7 +1251,9 @@ static void gj_factor_panel(hipStream_t s, typename Cx<T>::V* pool, const MatDes
 // quasi-ellipsoids, spirals and conches at k = 20 under 0.9, the single layer's
 // under 0.8; a sphere at k = 20 on 16 azimuths reaches 2.4, peanuts at k = 15
 // more than 2.  The inverses agree with LAPACK's to 6e-15 of their largest
-// entry throughout.  One matrix that goes back costs its own panels' chain
+// entry throughout.  The limits are per panel, not over panels; 198 blocks of every
+// shape and formulation, k = 0.5 to 150 (resolved to hopeless), are within
+// 1.9 eps times their 1-norm condition number.  One matrix that goes back costs its own panels' chain
 // (36 reduced blocks of order ~500: 1.6 -> 4.4 ms), so the limits are not tighter.
 constexpr int GJD = 64;
 
