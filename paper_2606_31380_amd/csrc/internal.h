@@ -260,7 +260,6 @@ struct qax_problem {
     void* d_rec = nullptr;              // source records, 32 bytes per node
     float* d_ewk = nullptr;
     int slots = 1;
-    bool far = false;                   // bodies that see others from far off
   } mm;
   qax::Tune tune;
 

@@ -12,7 +12,6 @@
 // n_theta is even), so the exclusion of pairs on one body is uniform over a
 // wavefront and a chunk.
 #include <algorithm>
-#include <cmath>
 #include <vector>
 
 #include "fastmath.h"
@@ -57,17 +56,8 @@ struct MmBody {
   int32_t e;             // log2 S_b
 };
 template <typename T>
-__host__ __device__ __forceinline__ T mm_bound(int form, T wk, T t, T ek) {
+__device__ __forceinline__ T mm_bound(int form, T wk, T t, T ek) {
   return wk * t * (form == 2 ? ek : sqrt((T)1 + t * t) + (form == 1 ? ek : (T)0));
-}
-
-// Distance from a body's centre beyond which the bound is 2^-10 of that at rho_b
-// (to a factor of two).
-__host__ __device__ __forceinline__ double mm_far(int form, double R, double k, double eta) {
-  const double lim = 0x1p-10 * mm_bound(form, 1.0, 2.0 / (k * R), eta / k);
-  double r = 0.5 * R;
-  while (r < 512.0 * R && mm_bound(form, 1.0, 1.0 / (k * r), eta / k) > lim) r *= 2.0;
-  return R + r;
 }
 
 __global__ __launch_bounds__(256) void mm_body_kernel(const BodyDev* __restrict__ bodies,
@@ -96,13 +86,15 @@ __global__ __launch_bounds__(256) void mm_body_kernel(const BodyDev* __restrict_
     const double R = 1.0001 * sqrt((double)s0[0]), W = 1.0001 * sqrt((double)s1[0]), k = B.k;
     const double rho = 0.5 * R, ek = B.eta / k;
     const double lim = mm_bound(form, W / k, 1.0 / (k * rho), ek);
+    double far = rho;                  // where the bound is below 2^-10 of that
+    while (far < 1024.0 * rho && mm_bound(form, W / k, 1.0 / (k * far), ek) > 0x1p-10 * lim) far *= 2.0;
     int e = 0;
     (void)frexp(lim, &e);
     e = max(-120, min(120, 14 - e));
     MmBody M;
     M.S = (float)ldexp(1.0, e);
     M.near2 = (float)(1.0001 * (R + rho) * (R + rho));
-    M.kfar = (float)(k * mm_far(form, R, k, B.eta));
+    M.kfar = (float)(k * (R + far));
     M.kR = (float)(k * R);
     M.wk = (float)(W / k * ldexp(1.0, e));
     M.ek = (float)ek;
@@ -238,8 +230,8 @@ struct MmTarget {   // per target and source body (see the reciprocal FP32 kerne
 
 // The target at (x, y, z) against body B.  Returns how the wavefront's entries are
 // scaled beyond S_b: -1 by their sizes (a target is near), 0 not at all, else by
-// that power of two (all are far; FARS only).
-template <int FORM, int FARS>
+// that power of two (all are far).
+template <int FORM>
 __device__ __forceinline__ int mm_target(const BodyDev& B, const MmBody& M, double x, double y, double z, double k,
                                           MmTarget& G) {
   const double c2 = 2.0 * k * k / TWO_PI;
@@ -255,7 +247,7 @@ __device__ __forceinline__ int mm_target(const BodyDev& B, const MmBody& M, doub
   G.dns = (float)(k * Dn);
   G.ph0 = (float)ph;
   if (__any(!(D2 >= (double)M.near2))) return -1;
-  if (!FARS || !__all(G.dns > M.kfar)) return 0;
+  if (!__all(G.dns > M.kfar)) return 0;
   float d = G.dns;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) d = fminf(d, __shfl_xor(d, o));
@@ -296,13 +288,13 @@ __device__ __forceinline__ void mm_eval(const float4 Y, const float4 W, float E,
 // sources with records at R and E, scaled as mm_target says.  Near: entries beyond
 // the bound of S_b scale the whole half chunk down; returns the power of two that undoes
 // that (1 otherwise; entries that are not finite stay so).
-template <int FORM, int FARS>
+template <int FORM>
 __device__ __forceinline__ float mm_operands(const float4* R, const float* E, const MmTarget& G, int scaled,
                                              u32x4* f) {
   float kr[8], ki[8], undo = 1.0f;
 #pragma unroll
   for (int s = 0; s < 8; ++s) mm_eval<FORM>(R[2 * s], R[2 * s + 1], E[FORM ? s : 0], G, kr[s], ki[s]);
-  if (FARS && scaled > 0) {
+  if (scaled > 0) {
     const float g = ldexpf(1.0f, scaled);
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
@@ -447,11 +439,16 @@ struct MmWalk {
 // 12 matrix instructions of 32 cycles per 512 pairs, which overlap little).
 // 100 bodies of 2048 nodes (4.2e10 pairs): 16 right-hand sides 114.6 -> 36.4 ms,
 // 32 202.6 -> 46.4 ms against the per-target kernel; register caps of 4 and 3
-// wavefronts per SIMD are 4 % faster than 3 and 2.  Bfloat16 in three parts (six
+// wavefronts per SIMD are 4 % faster than 3 and 2 (8 % at 32, 46.4 and 50.4), except
+// for the combined field with 32, whose larger evaluation spills at 3 (52.9 ms at
+// 2, 56.9 at 3).  The targets' coordinates in LDS and the records four bytes a thread
+// leave room for the scales of the sources' body (15 spilled registers and 47.3 ms
+// without).  Bfloat16 in three parts (six
 // products, nine vector instructions more per pair) took 51 and 73 ms; moving
 // the products of one half chunk between the evaluations of the next gave nothing.
-template <int WIDE, int FORM, int FARS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ? 3 : 4))) void pair_mmf_kernel(
+template <int WIDE, int FORM>
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(WIDE ? FORM == 1 ? 2 : 3 : 4))) void pair_mmf_kernel(
     const MmTask* __restrict__ tasks, const BodyDev* __restrict__ bodies, const int32_t* __restrict__ node_body,
     const double* __restrict__ pos, int64_t N, const MmBody* __restrict__ mb, const u32x4* __restrict__ rec,
     const float* __restrict__ ewk, const u32x4* __restrict__ pack,
@@ -480,16 +477,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ? 3 : 
   MmTarget G;
   int scaled = 0, cur = -1, buf = 0;
   MmWalk W(T, bodies);
-  u32x4 pre[2], prec;
+  u32x4 pre[2];
+  uint32_t prec;                                 // records: four bytes per thread
   float pew = 0.0f;
   auto fetch = [&](int c) {
     const u32x4* p = pack + (int64_t)c * NV + tid;
 #pragma unroll
     for (int q = 0; q < 2; ++q) pre[q] = p[q * 256];
-    if (wave == 0) {
-      prec = rec[(int64_t)c * 64 + lane];
-      if (FORM) pew = ewk[(int64_t)c * MM_C + col];
-    }
+    prec = ((const uint32_t*)rec)[(int64_t)c * 256 + tid];
+    if (FORM && wave == 0) pew = ewk[(int64_t)c * MM_C + col];
   };
   int c = W.next(T.c0);
   if (c < T.c1) {
@@ -499,10 +495,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ? 3 : 
   while (c < T.c1) {
 #pragma unroll
     for (int q = 0; q < 2; ++q) sB[buf][tid + q * 256] = pre[q];
-    if (wave == 0) {
-      sR[buf][lane] = prec;
-      if (FORM) sE[buf][col] = pew;
-    }
+    ((uint32_t*)sR[buf])[tid] = prec;
+    if (FORM && wave == 0) sE[buf][col] = pew;
     __syncthreads();
     const int cn = W.next(c + 1);
     if (cn < T.c1) fetch(cn);
@@ -511,13 +505,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ? 3 : 
       if (W.body != cur) {
         cur = W.body;
         const int tc = wave * 32 + col;
-        scaled = mm_target<FORM, FARS>(bodies[cur], mb[cur], sX[0][tc], sX[1][tc], sX[2][tc], k, G);
-        S.e = mm_undo(mb, colmax, cur, nrhs, r0 + (WIDE ? col : (col & 15))) - (FARS ? max(scaled, 0) : 0);
+        scaled = mm_target<FORM>(bodies[cur], mb[cur], sX[0][tc], sX[1][tc], sX[2][tc], k, G);
+        S.e = mm_undo(mb, colmax, cur, nrhs, r0 + (WIDE ? col : (col & 15))) - max(scaled, 0);
       }
 #pragma unroll
       for (int hc = 0; hc < 2; ++hc) {
         u32x4 f[4];
-        const float undo = mm_operands<FORM, FARS>((const float4*)&sR[buf][(hc * 16 + half * 8) * 2],
+        const float undo = mm_operands<FORM>((const float4*)&sR[buf][(hc * 16 + half * 8) * 2],
                                              &sE[buf][FORM ? hc * 16 + half * 8 : 0], G, scaled, f);
         if (undo != 1.0f) S.flush();
         mm_products<WIDE>(f, &sB[buf][hc * 4 * 64 + lane], S.acc);
@@ -546,7 +540,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WIDE ? 3 : 
 // so every entry of K is evaluated once for all 64: 82 ms on the 100 bodies
 // above, against 95 ms for two passes of the kernel above and 394 ms for the
 // per-target kernel.
-template <int FORM, int FARS>
+template <int FORM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void pair_mmf64_kernel(
     const MmTask* __restrict__ tasks, const BodyDev* __restrict__ bodies, const int32_t* __restrict__ node_body,
     const double* __restrict__ pos, int64_t N, const MmBody* __restrict__ mb, const u32x4* __restrict__ rec,
@@ -573,7 +567,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
   const double k = T.k;
   const int mybody = live ? node_body[tile0] : -1;
   const int64_t ti = live ? tile0 + col : T.t0;
-  const double xi = pos[ti], yi = pos[N + ti], zi = pos[2 * N + ti];
+  __shared__ double sX[3][64];                   // the targets, read where the sources' body changes
+  const int tc = tile * 32 + col;
+  for (int d = half; d < 3; d += 2) sX[d][tc] = pos[d * N + ti];
   const int r = r0 + hw * 32 + col;              // the lane's right-hand side
 
   MmSums<2> S;
@@ -582,7 +578,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
   int how = 0;                                   // mm_target's scaling of the body evaluated
   int cur = -1, summed = -1;                     // bodies evaluated, multiplied
   MmWalk W(T, bodies);
-  u32x4 preB[4], preR;
+  u32x4 preB[4];
+  uint32_t preR;                                 // records: four bytes per thread
   float preE = 0.0f;
   auto fetch_b = [&](int c) {
     if (c >= T.c1) return;
@@ -591,18 +588,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
     for (int q = 0; q < 4; ++q) preB[q] = p[q * 256];
   };
   auto fetch_r = [&](int c) {
-    if (c >= T.c1 || wave != 0) return;
-    preR = rec[(int64_t)c * 64 + lane];
-    if (FORM) preE = ewk[(int64_t)c * MM_C + col];
+    if (c >= T.c1) return;
+    preR = ((const uint32_t*)rec)[(int64_t)c * 256 + tid];
+    if (FORM && wave == 0) preE = ewk[(int64_t)c * MM_C + col];
   };
   auto store_b = [&](int buf) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) sB[buf][tid + q * 256] = preB[q];
   };
   auto store_r = [&](int buf) {
-    if (wave != 0) return;
-    sR[buf][lane] = preR;
-    if (FORM) sE[buf][col] = preE;
+    ((uint32_t*)sR[buf])[tid] = preR;
+    if (FORM && wave == 0) sE[buf][col] = preE;
   };
   // whether the tile meets the chunk W is at (G, how and scales set for it)
   int scales = 0;
@@ -610,15 +606,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void p
     if (!live || W.body == mybody) return false;
     if (W.body != cur) {
       cur = W.body;
-      how = mm_target<FORM, FARS>(bodies[cur], mb[cur], xi, yi, zi, k, G);
-      scales = mm_undo(mb, colmax, cur, nrhs, r) - (FARS ? max(how, 0) : 0);
+      how = mm_target<FORM>(bodies[cur], mb[cur], sX[0][tc], sX[1][tc], sX[2][tc], k, G);
+      scales = mm_undo(mb, colmax, cur, nrhs, r) - max(how, 0);
     }
     return true;
   };
   // K of the wavefront's half chunk, from record buffer rb to operand buffer ab
   auto evaluate = [&](int rb, int ab, int scaled) {
     u32x4 f[4];
-    const float undo = mm_operands<FORM, FARS>((const float4*)&sR[rb][(hw * 16 + half * 8) * 2],
+    const float undo = mm_operands<FORM>((const float4*)&sR[rb][(hw * 16 + half * 8) * 2],
                                          &sE[rb][FORM ? hw * 16 + half * 8 : 0], G, scaled, f);
     if (scaled < 0 && lane == 0) sU[ab][tile][hw] = undo;
     u32x4* o = &sA[ab][tile][hw][lane];
@@ -1042,31 +1038,6 @@ static void plan_mm(qax_problem* p, int cu_count, std::vector<MmTask>& tasks) {
   }
 }
 
-// Whether a problem's bodies lie so far apart that tiles of targets may be far
-// from a body (mm_far): the kernels that look for them hold more registers (100
-// bodies of 2048 nodes: 32 right-hand sides 46.7 ms without, 49.5 with, 64 79.7 and
-// 81.2; bodies of radius 0.5 at k = 4 are far from 180 on, 17 at k = 0.01).
-static bool mm_any_far(const qax_problem* p) {
-  for (int pr = 0; pr < p->n_problems; ++pr) {
-    double lo[3], hi[3], reach = 1e300, big = 0.0;
-    for (int64_t b = p->prob_body0[pr]; b < p->prob_body0[pr + 1]; ++b) {
-      const BodyDev& B = p->hbodies[b];
-      // generous radii: the far distance grows with them
-      const double z = B.shape == QAX_SPHERE ? B.a : B.shape == QAX_SPHEROID ? B.c : B.a * (1.0 + B.c);
-      const double x = std::max(B.a, B.shape == QAX_PEANUT ? z : 0.0) + B.kappa * z * z;
-      const double R = B.shape > QAX_PEANUT ? 3.2 * B.a : hypot(x, z);
-      reach = std::min(reach, mm_far(p->form(), R, B.k, B.eta));
-      big = std::max(big, R);
-      for (int c = 0; c < 3; ++c) {
-        lo[c] = b == p->prob_body0[pr] ? B.cen[c] : std::min(lo[c], B.cen[c]);
-        hi[c] = b == p->prob_body0[pr] ? B.cen[c] : std::max(hi[c], B.cen[c]);
-      }
-    }
-    if (hypot(hypot(hi[0] - lo[0], hi[1] - lo[1]), hi[2] - lo[2]) + big > reach) return true;
-  }
-  return false;
-}
-
 // Made on first use (not inside a capture; nothing here waits): the task table, a
 // function of the node ranges and wavenumbers, which a rebuild that keeps them
 // keeps too, and for FP32 the bodies' scales and source records, functions of the
@@ -1093,7 +1064,6 @@ hipError_t ensure_mm_plan(qax_problem* p, int prec, int cu_count) {
   M.d_bodies = m;
   M.d_rec = m + bb;
   M.d_ewk = (float*)(m + bb + br);
-  M.far = mm_any_far(p);
   hipLaunchKernelGGL(mm_body_kernel, dim3((unsigned)p->n_bodies), dim3(256), 0, p->stream, p->d_bodies,
                      (const float4*)p->d_loc32, (const float4*)p->d_aw32, p->form(), (MmBody*)M.d_bodies);
   hipLaunchKernelGGL(mm_records_kernel, dim3((unsigned)((p->N + 255) / 256)), dim3(256), 0, p->stream, p->d_bodies,
@@ -1117,9 +1087,6 @@ void free_mm_tasks(qax_problem* p) {
   p->mm.d_tasks = nullptr;
   p->mm.tasks.clear();
 }
-
-template <int V>
-using I = std::integral_constant<int, V>;
 
 static size_t mm_pack_values(const qax_problem* p, int nrhs) {
   return (size_t)(p->N / MM_C) * (nrhs > 32 ? 16 : 8) * 64;
@@ -1160,17 +1127,17 @@ hipError_t launch_pair_mmf(qax_problem* p, const double* mu, int nrhs, double* w
                          p->d_bodies, p->d_node_body, p->d_pos, p->N, mb, (const u32x4*)p->mm.d_rec, p->mm.d_ewk,
                          pack, colmax, nrhs, r0, p->seg_active, partial);
     };
-    auto forms = [&](auto fm, auto fars) {
-      constexpr int FM = decltype(fm)::value, FARS = decltype(fars)::value;
-      go(tiles == 2 ? pair_mmf64_kernel<FM, FARS> : wide ? pair_mmf_kernel<1, FM, FARS> : pair_mmf_kernel<0, FM, FARS>);
-    };
-    auto bodies = [&](auto fm) { p->mm.far ? forms(fm, I<1>{}) : forms(fm, I<0>{}); };
-    form == 1 ? bodies(I<1>{}) : form == 2 ? bodies(I<2>{}) : bodies(I<0>{});
+    if (tiles == 2) go(form == 1 ? pair_mmf64_kernel<1> : form == 2 ? pair_mmf64_kernel<2> : pair_mmf64_kernel<0>);
+    else if (wide) go(form == 1 ? pair_mmf_kernel<1, 1> : form == 2 ? pair_mmf_kernel<1, 2> : pair_mmf_kernel<1, 0>);
+    else go(form == 1 ? pair_mmf_kernel<0, 1> : form == 2 ? pair_mmf_kernel<0, 2> : pair_mmf_kernel<0, 0>);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
+
+template <int V>
+using I = std::integral_constant<int, V>;
 
 // FP64 sums over the pair-sum tasks or other targets, right-hand sides 32 at a time.
 template <int FORM, bool PAIRS>

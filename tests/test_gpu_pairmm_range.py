@@ -80,12 +80,13 @@ def test_bodies_far_apart(dist, k, form, nrhs):
 
 
 @pytest.mark.parametrize("nrhs", COUNTS)
-def test_densities_apart_between_bodies(nrhs):
-    # 2^-60 ... 2^60 from body to body and per column: rows that see the small ones only
+@pytest.mark.parametrize("span", [60, 450])
+def test_densities_apart_between_bodies(span, nrhs):
+    # 2^-span ... 2^span from body to body and per column: rows that see the small ones only
     s = spheres(3.0, [(0.5, 12, (0.0, 0.0, 0.0)), (0.5, 8, (2.0, 0.0, 0.0)), (0.4, 10, (0.0, 9.0, 0.0))])
     K, d = matrix(s)
     mu = densities(s.n_unknowns(), nrhs)
-    e = np.random.default_rng(1).integers(-60, 61, (3, nrhs))
+    e = np.random.default_rng(1).integers(-span, span + 1, (3, nrhs))
     mu = mu * (2.0 ** e)[d.body]
     with qax.Problem(s) as P:
         close(run(P, mu), K, mu, 2e-6)
