@@ -86,9 +86,14 @@ __device__ __forceinline__ void sincos_2pi(double t, double* sp, double* cp) {
   *cp = __hiloint2double(__double2hiint(pc) ^ sgn, __double2loint(pc));
 }
 
-// sin and cos of 2 pi u / 512 (u in 512ths of a revolution, |u| < 2^31) from
-// a table of (sin, cos)(2 pi i / 512), i = 0..511: with m = rint(u) the
-// remainder g = u - m is exact and |g| <= 1/2, so the Taylor series of
+// x + NEAREST (|x| < 2^51) is NEAREST plus the integer nearest to x, whose low bits
+// are those of the sum.
+constexpr double NEAREST = 6755399441055744.0;     // 1.5 x 2^52
+
+// sin and cos of 2 pi u / 512 (u in 512ths of a revolution, |u| < 2^51) from
+// a table of (sin, cos)(2 pi i / 512), i = 0..511: with m the nearest integer (its
+// low bits taken from u + NEAREST: a conversion to 32 bits ends at 2^31, that is
+// k r = 2.6e7) the remainder g = u - m is exact and |g| <= 1/2, so the Taylor series of
 // sin(2 pi g / 512) through g^5 (the next term is below 7e-20) and of
 // cos(2 pi g / 512) - 1 through g^4 (the next term is below 7.5e-17, under
 // half a unit in the last place of 1) and the angle-addition formulas with
@@ -96,9 +101,9 @@ __device__ __forceinline__ void sincos_2pi(double t, double* sp, double* cp) {
 // (-1)^k (2 pi / 512)^m / m! rounded to double; the error is a few units in
 // the last place.
 __device__ __forceinline__ void sincos_tab512(double u, const double2* tab, double* sp, double* cp) {
-  const double m = rint(u);
-  const double g = u - m;
-  const double2 T = tab[(int)m & 511];
+  const double t = u + NEAREST;
+  const double g = u - (t - NEAREST);
+  const double2 T = tab[__double2loint(t) & 511];
   const double g2 = g * g;
   const double S = g * fma(fma(g2, 2.3193606829202922e-12, -3.080196845561248e-07), g2, 0.01227184630308513);
   const double Cm1 = g2 * fma(g2, 9.44992556799382e-10, -7.529910584327208e-05);
@@ -110,14 +115,9 @@ __device__ __forceinline__ void sincos_tab512(double u, const double2* tab, doub
 constexpr double U512 = 512.0 / 6.283185307179586476925;
 constexpr double U512_LOW = -5.037741228846716e-15;
 
-// x + NEAREST (|x| < 2^51) is NEAREST plus the integer nearest to x, whose low bits
-// are those of the sum.
-constexpr double NEAREST = 6755399441055744.0;     // 1.5 x 2^52
-
 // sin and cos of 2 pi (x (u + ul)) / 512 (|x u| < 2^51) from the same table, x u
 // not rounded: the remainder against its nearest integer is one fma, the part ul
-// (far below u) another.  The table's index is taken from the low bits of
-// x u + NEAREST: a conversion to 32 bits ends at 2^31, that is x = k r = 2.6e7.
+// (far below u) another.
 __device__ __forceinline__ void sincos_tab512_scaled(double x, double u, double ul, const double2* tab, double* sp,
                                                      double* cp) {
   const double t = fma(x, u, NEAREST);
