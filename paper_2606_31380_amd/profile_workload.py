@@ -11,7 +11,11 @@ scaled, then: node build, self-block assembly and inversion, the autotuner
 the launch choices are those of the benchmark, not re-timed under the
 profiler), one FP64 and one FP32 pair sum, block applies (B and B^-1 in FP64,
 B^-1 in FP32; one and eight right-hand sides), one eight-column FP32 pair sum
-and the far field on the 200 x 200 direction grid.  Every step prints a line.
+and the far field on the 200 x 200 direction grid.  The workload
+"several_rhs" instead runs the matrix-core sums: FP32 pair sums of 100 bodies
+of 2048 nodes with 16, 32 and 64 right-hand sides, FP64 ones of 40 bodies of
+1408 nodes with 2, 8, 16 and 32 and with 7 in the combined field, and the near
+field of 50 bodies at 5000 points with 8.  Every step prints a line.
 """
 from __future__ import annotations
 
@@ -19,6 +23,36 @@ import math
 import sys
 
 import numpy as np
+
+
+def several_rhs(dev) -> None:
+    import torch
+
+    from paper_2606_31380_amd import qax
+    from paper_2606_31380_amd import scenarios as sc
+
+    def density(P, nrhs):
+        g = torch.Generator(device="cpu").manual_seed(0)
+        return torch.randn(P.N * nrhs, dtype=torch.complex128, generator=g).to(dev)
+
+    def sums(P, prec, counts, what):
+        for nrhs in counts:
+            v, o = density(P, nrhs), P.vec(nrhs)
+            qax.qax_pair_sum(P.h, prec, v, o, nrhs)
+            print(f"pair sum: {what}, N = {P.N}, {nrhs} right-hand sides", flush=True)
+
+    with qax.Problem(sc.lattice_like_random(100, 0, 20.0, 6.0, 64, 2, 64)) as P:
+        sums(P, qax.QAX_MIXED, (16, 32, 64), "FP32")
+    forty = sc.lattice_like_random(40, 0, 14.0, 3.0, 32, 2, 44)
+    with qax.Problem(forty) as P:
+        sums(P, qax.QAX_FP64, (2, 8, 16, 32), "FP64")
+    with qax.Problem(forty, formulation=qax.QAX_COMBINED_FIELD) as P:
+        sums(P, qax.QAX_FP64, (7,), "FP64, combined field")
+    with qax.Problem(sc.random_mixed(50, 0, 16.0, 4.0)) as P:
+        x = np.random.default_rng(0).uniform(-9.0, 9.0, (5000, 3)) + np.array([0.0, 0.0, 25.0])
+        u = torch.zeros(5000 * 8, dtype=torch.complex128, device=dev)
+        qax.qax_nearfield(P.h, density(P, 8), x, u, 8)
+        print(f"near field: N = {P.N}, 5000 points, 8 right-hand sides", flush=True)
 
 
 def main(tune_cache=None, workload="random_mixed") -> int:
@@ -36,6 +70,10 @@ def main(tune_cache=None, workload="random_mixed") -> int:
     torch.cuda.synchronize()
     print(f"copy calibration: {n_copy * 8} bytes read, {n_copy * 8} bytes written", flush=True)
     del x, y
+    if workload == "several_rhs":
+        several_rhs(dev)
+        print("done", flush=True)
+        return 0
 
     scen = sc.WORKLOADS[workload]()
     h = qax.qax_create(0, torch.cuda.current_stream(dev).cuda_stream)
