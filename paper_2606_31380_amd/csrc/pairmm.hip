@@ -104,8 +104,11 @@ __global__ __launch_bounds__(256) void mm_body_kernel(const BodyDev* __restrict_
 }
 
 // Source records: float4 pairs (y', c |y'|^2), S (aw / 2 c, aw . y') with y'
-// the offset from the body centre and c = k^2 / 2 pi (as the reciprocal FP32
-// kernel stages them), and S eta |aw| / k^2.
+// the offset from the body centre and c = k^2 / MM_2PI (as the reciprocal FP32
+// kernel stages them), and S eta |aw| / k^2.  Near targets cancel c |y'|^2 and
+// aw . y' against the target's terms, so both are formed in FP64 from the other
+// entries as rounded, and c with the FP32 2 pi that mm_eval takes it out with.
+constexpr float MM_2PI = (float)TWO_PI;
 __global__ void mm_records_kernel(const BodyDev* __restrict__ bodies, const int32_t* __restrict__ node_body,
                                   const float4* __restrict__ loc32, const float4* __restrict__ aw32,
                                   const float* __restrict__ ew32, const MmBody* __restrict__ mb, int64_t N,
@@ -114,12 +117,13 @@ __global__ void mm_records_kernel(const BodyDev* __restrict__ bodies, const int3
   if (n >= N) return;
   const int b = node_body[n];
   const double k = bodies[b].k;
-  const double c = k * k / TWO_PI;
+  const double c = k * k / (double)MM_2PI;
   const float4 y = loc32[n], a = aw32[n];
   const float S = mb[b].S;
-  const float hw = (float)(0.5 / c) * S;
-  rec[2 * n] = make_float4(y.x, y.y, y.z, (float)c * y.w);
-  rec[2 * n + 1] = make_float4(a.x * hw, a.y * hw, a.z * hw, a.w * S);
+  const double yx = y.x, yy = y.y, yz = y.z, hw = 0.5 / c * S;
+  const float wx = (float)(a.x * hw), wy = (float)(a.y * hw), wz = (float)(a.z * hw);
+  rec[2 * n] = make_float4(y.x, y.y, y.z, (float)(c * fma(yx, yx, fma(yy, yy, yz * yz))));
+  rec[2 * n + 1] = make_float4(wx, wy, wz, (float)(2.0 * c * fma(wx, yx, fma(wy, yy, wz * yz))));
   ewk[n] = ew32[n] * (float)(1.0 / (k * k)) * S;
 }
 
@@ -234,7 +238,7 @@ struct MmTarget {   // per target and source body (see the reciprocal FP32 kerne
 template <int FORM>
 __device__ __forceinline__ int mm_target(const BodyDev& B, const MmBody& M, double x, double y, double z, double k,
                                           MmTarget& G) {
-  const double c2 = 2.0 * k * k / TWO_PI;
+  const double c2 = 2.0 * k * k / (double)MM_2PI;
   const double Dx = B.cen[0] - x, Dy = B.cen[1] - y, Dz = B.cen[2] - z;
   const double D2 = fma(Dx, Dx, fma(Dy, Dy, Dz * Dz));
   const double Dn = sqrt(D2);
@@ -244,7 +248,9 @@ __device__ __forceinline__ int mm_target(const BodyDev& B, const MmBody& M, doub
   G.my = (float)(c2 * Dy);
   G.mz = (float)(c2 * Dz);
   G.d2s = (float)(k * k * D2);
-  G.dns = (float)(k * Dn);
+  // k |D| less what makes num over k r + k |D| revolutions of 2 pi again, not of
+  // MM_2PI (r near |D|, where the phase difference counts)
+  G.dns = (float)(k * Dn * (2.0 * TWO_PI / (double)MM_2PI - 1.0));
   G.ph0 = (float)ph;
   if (__any(!(D2 >= (double)M.near2))) return -1;
   if (!__all(G.dns > M.kfar)) return 0;
@@ -262,7 +268,7 @@ template <int FORM>
 __device__ __forceinline__ void mm_eval(const float4 Y, const float4 W, float E, const MmTarget& T, float& kr,
                                         float& ki) {
   const float num = fmaf(Y.x, T.mx, fmaf(Y.y, T.my, fmaf(Y.z, T.mz, Y.w)));
-  const float r2s = fmaf((float)TWO_PI, num, T.d2s);
+  const float r2s = fmaf(MM_2PI, num, T.d2s);
   const float irs = __builtin_amdgcn_rsqf(r2s);
   const float ph = fmaf(num, __builtin_amdgcn_rcpf(fmaf(r2s, irs, T.dns)), T.ph0);
   const float sn = __builtin_amdgcn_sinf(ph);
