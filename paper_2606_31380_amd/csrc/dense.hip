@@ -66,6 +66,96 @@ __global__ __launch_bounds__(256) void block_gemv_kernel(
   }
 }
 
+// Two or three right-hand sides: a wavefront takes FEW_ROWS rows of one block
+// (orders are multiples of 16), which share the loads of the input; a lane's
+// columns are 64 apart, as with one right-hand side, so a row is 64 chains of
+// 2 ceil(n / 64) products and a tree: off by 1.4e-16 of the result at order 128,
+// 2.2e-16 at 2048, where one chain of 2 n on the matrix cores is off by 5.6e-16 and
+// 2.2e-15, which a solve near its rounding floor shows.  FP32 matrices are
+// accumulated in FP64.  Bound by the matrix's bytes, short rows by the sums across
+// lanes.  2 and 3 right-hand sides, the matrix cores first: one block of order 768
+// 46 -> 17 us (FP32 40 -> 17), 27 of 2048 383 -> 341 (231 -> 190; 5.3 TB/s), 343 of
+// 768 595 -> 541 and 606 -> 554, 4000 of 96 137 -> 131 and 139 -> 157.  Four rows
+// against one: 343 of 768 541 us against 647; two steps at once: 40 against 31 (order
+// 96, 1000 blocks of 7 shapes).
+constexpr int FEW_ROWS = 4;
+template <typename MT, int NR>
+__global__ __launch_bounds__(256) void block_few_kernel(
+    const BodyDev* __restrict__ bodies, const BlockDev* __restrict__ blocks,
+    const int32_t* __restrict__ node_body, const MT* __restrict__ pool, int64_t N,
+    const double2* __restrict__ v, double* __restrict__ out, int accumulate,
+    const int32_t* __restrict__ seg_active) {
+  typedef MT vec_t __attribute__((ext_vector_type(2)));
+  constexpr int RW = FEW_ROWS;
+  const int lane = threadIdx.x & 63;
+  const int64_t row = RW * ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6));
+  if (row >= N) return;
+  const BodyDev& B = bodies[node_body[row]];
+  if (seg_active) {
+    // converged lockstep segments: their input is zero, so is the output
+    bool any = false;
+    for (int r = 0; r < NR; ++r) any = any || seg_active[B.problem * NR + r] != 0;
+    if (!any) {
+      if (lane < 2 * NR * RW && !accumulate) out[2 * NR * row + lane] = 0.0;
+      return;
+    }
+  }
+  const BlockDev& K = blocks[B.block];
+  const int n = K.n;
+  const MT* a = pool + 2 * (K.elem_off + (row - B.off) * n);
+  const double2* vb = v + B.off * NR;
+  // the sums, the right-hand sides fastest, then real and imaginary part, then
+  // rows: the order in which the halving below deals them out
+  constexpr int S = 2 * NR * RW;
+  double acc[S];
+#pragma unroll
+  for (int i = 0; i < S; ++i) acc[i] = 0.0;
+#pragma unroll 1
+  for (int j = lane; j < n; j += 64) {
+    vec_t m[RW];
+    double2 x[NR];
+#pragma unroll
+    for (int w = 0; w < RW; ++w) m[w] = *(const vec_t*)(a + 2 * ((int64_t)w * n + j));
+#pragma unroll
+    for (int r = 0; r < NR; ++r) x[r] = vb[(int64_t)j * NR + r];
+#pragma unroll
+    for (int w = 0; w < RW; ++w)
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const double mr = (double)m[w][0], mi = (double)m[w][1];
+        acc[2 * NR * w + r] += mr * x[r].x - mi * x[r].y;
+        acc[2 * NR * w + NR + r] += mr * x[r].y + mi * x[r].x;
+      }
+  }
+  // each exchange halves the sums a lane holds, to one part of one row, then adds
+  // what is left across the last lanes
+  constexpr int H = 3;
+  static_assert(2 * RW == 1 << H, "sums dealt out by H halvings");
+  int who = 0;
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    const int half = S >> (h + 1), off = 32 >> h;
+    const bool up = (lane & off) != 0;
+    who = 2 * who + (up ? 1 : 0);
+#pragma unroll
+    for (int i = 0; i < half; ++i) {
+      const double lo = acc[i], hi = acc[half + i];
+      acc[i] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, off);
+    }
+  }
+#pragma unroll
+  for (int off = 32 >> H; off > 0; off >>= 1)
+#pragma unroll
+    for (int r = 0; r < NR; ++r) acc[r] += __shfl_xor(acc[r], off);
+  if ((lane & ((64 >> H) - 1)) == 0) {
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      double* o = out + 2 * (NR * (row + (who >> 1)) + r) + (who & 1);
+      *o = accumulate ? *o + acc[r] : acc[r];
+    }
+  }
+}
+
 // FP32 matrix, one right-hand side: GV_ROWS rows of one block per workgroup
 // (four per wavefront), the block's input vector staged in LDS in chunks of
 // GV_CH entries and shared by those rows.  The matrix streams from HBM once;
@@ -155,6 +245,28 @@ static void gemv_launch(hipStream_t s, const BodyDev* bodies, const BlockDev* bl
                      node_body, pool, N, (const double2*)v, (double2*)out, acc ? 1 : 0, seg_active);
 }
 
+template <typename MT>
+static void few_launch(hipStream_t s, const BodyDev* bodies, const BlockDev* blocks, const int32_t* node_body,
+                       const void* pool, int64_t N, const double* v, int nrhs, double* out, bool acc,
+                       const int32_t* seg_active) {
+  const dim3 grid((unsigned)((N + 4 * FEW_ROWS - 1) / (4 * FEW_ROWS)));
+  if (nrhs == 2)
+    hipLaunchKernelGGL((block_few_kernel<MT, 2>), grid, dim3(256), 0, s, bodies, blocks, node_body, (const MT*)pool, N,
+                       (const double2*)v, out, acc ? 1 : 0, seg_active);
+  else
+    hipLaunchKernelGGL((block_few_kernel<MT, 3>), grid, dim3(256), 0, s, bodies, blocks, node_body, (const MT*)pool, N,
+                       (const double2*)v, out, acc ? 1 : 0, seg_active);
+}
+
+// Two and three right-hand sides on the vector units: FP64 always (its sums); FP32,
+// whose entries are rounded to 2^-24 anyway, unless there are many short rows
+// (1500 blocks of order 96, 3 right-hand sides: 41 us on the matrix cores against
+// 54, 343 of 768 319 against 341; but 150 of 96 19 against 18, 30 of 640 47 against
+// 34, 90 of 1024 178 against 165).
+static bool few_rhs(bool f32, int nrhs, int64_t rows, int64_t n_blocks) {
+  return nrhs <= 3 && (!f32 || rows < 32768 || rows >= 1024 * n_blocks);
+}
+
 hipError_t launch_block_mm(qax_problem* p, int inverse, int prec, const double* v, double* out,
                              int nrhs, bool accumulate);
 
@@ -183,7 +295,7 @@ hipError_t launch_block_apply(qax_problem* p, int inverse, int prec, const doubl
     timing_end(p, kind);
     return hipGetLastError();
   }
-  if (nrhs > 1) {
+  if (nrhs > 1 && !few_rhs(prec == QAX_MIXED, nrhs, p->N, p->n_bodies)) {
     // several right-hand sides: on the matrix cores
     timing_begin(p, kind);
     hipError_t e = launch_block_mm(p, inverse, prec, v, out, nrhs, accumulate);
@@ -191,7 +303,14 @@ hipError_t launch_block_apply(qax_problem* p, int inverse, int prec, const doubl
     return e;
   }
   timing_begin(p, kind);
-  if (prec == QAX_MIXED) {
+  if (nrhs > 1) {
+    if (prec == QAX_MIXED)
+      few_launch<float>(p->stream, p->d_bodies, p->d_blocks, p->d_node_body, inverse ? p->d_Binv32 : p->d_B32, p->N, v,
+                        nrhs, out, accumulate, p->seg_active);
+    else
+      few_launch<double>(p->stream, p->d_bodies, p->d_blocks, p->d_node_body, inverse ? p->d_Binv : p->d_B, p->N, v,
+                         nrhs, out, accumulate, p->seg_active);
+  } else if (prec == QAX_MIXED) {
     const float* pool = inverse ? p->d_Binv32 : p->d_B32;
     if (p->tune.gemv_vec[1] == 4)
       gemv_f32_lds_launch<4>(p->stream, p->d_bodies, p->d_blocks, p->d_node_body, pool, p->N, v, out,
@@ -246,8 +365,7 @@ struct MfmaAcc<float> {
 // right-hand sides (16 in FP64), by the matrix cores beyond.  Tiles of 64 x 64
 // real outputs with both operands in LDS (and FP32 sums of FP32 matrices) cost
 // every count the time of 32: 4913 blocks of order 96, 8 right-hand sides
-// 525 -> 177 us (4.1 TB/s; FP32 265 -> 100), 32: 570 -> 377 (313 -> 307), 2:
-// 237 -> 167 (230 -> 96; four right-hand sides a row on the vector units); 343
+// 525 -> 177 us (4.1 TB/s; FP32 265 -> 100), 32: 570 -> 377 (313 -> 307); 343
 // blocks of order 768, 8: 1858 -> 663 (896 -> 354), 64: 3494 -> 2186 (1694 ->
 // 1718).
 template <typename MT, int VEC, int NT>
@@ -457,7 +575,10 @@ hipError_t launch_table_product(hipStream_t s, const GemmTask* tasks, int ntasks
   const double2* vv = (const double2*)v;
   double2* oo = (double2*)out;
   const int acc = accumulate ? 1 : 0;
-  if (nrhs > 1) {
+  if (nrhs > 1 && few_rhs(f32, nrhs, rows, rows / order)) {
+    if (f32) few_launch<float>(s, bodies, blocks, node_body, pool, rows, v, nrhs, out, accumulate, nullptr);
+    else few_launch<double>(s, bodies, blocks, node_body, pool, rows, v, nrhs, out, accumulate, nullptr);
+  } else if (nrhs > 1) {
     if (f32) block_mm_launch<float, 2>(s, tasks, ntasks, bodies, blocks, pool, v, nrhs, out, accumulate, nullptr);
     else block_mm_launch<double, 1>(s, tasks, ntasks, bodies, blocks, pool, v, nrhs, out, accumulate, nullptr);
   } else if (order <= 256) {
