@@ -989,17 +989,24 @@ static size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 // the problem's source chunks, sorted by decreasing cost: at least 24
 // workgroups per compute unit (about eight rounds of those the chip holds; with
 // four rounds the last one cost 6 % on the 100 bodies above, with more nothing
-// was gained), at least eight chunks each (the sums' FP64 step).
+// was gained), at least eight chunks each (the sums' FP64 step).  Sums too small
+// for a workgroup per compute unit that way are split further, down to single
+// chunks: 5 bodies of order 96, FP64, 2 right-hand sides 51.1 -> 22.1 us, 64
+// 188 -> 39.8 (FP32 51.0 -> 31.9, 49.2 -> 34.3); 12 of order 128 37.2 -> 28.9 and
+// 116 -> 72.3 (41.3 -> 37.9, 44.6 -> 47.6).  Up to two workgroups per compute unit
+// the 12 take 30.6 and 74.1 us (38.3, 53.2).
 static void plan_mm(qax_problem* p, int cu_count, std::vector<MmTask>& tasks) {
   auto& M = p->mm;
   int64_t tblocks = 0, cmax = 0;
   for (int pr = 0; pr < p->n_problems; ++pr) {
     const int64_t n = p->off[p->prob_body0[pr + 1]] - p->off[p->prob_body0[pr]];
     tblocks += (n + MM_T - 1) / MM_T;
-    cmax = std::max(cmax, n / MM_C);
+    if (p->prob_body0[pr + 1] - p->prob_body0[pr] > 1) cmax = std::max(cmax, n / MM_C);   // no pairs in one body
   }
-  int64_t slots = (24LL * cu_count + tblocks - 1) / std::max<int64_t>(tblocks, 1);
-  slots = std::max<int64_t>(1, std::min<int64_t>({slots, 32, cmax / 8}));
+  tblocks = std::max<int64_t>(tblocks, 1);
+  const int64_t full = std::min<int64_t>((24LL * cu_count + tblocks - 1) / tblocks, cmax / 8);
+  const int64_t small = std::min<int64_t>(cu_count / tblocks, cmax);
+  const int64_t slots = std::max<int64_t>(1, std::min<int64_t>(32, std::max(full, small)));
   M.slots = (int)slots;
   // the body that holds every target of a block, or -1
   std::vector<int32_t> body;
@@ -1186,7 +1193,9 @@ hipError_t launch_pair_mmd(qax_problem* p, const double* mu, int nrhs, double* w
 }
 
 // Ranges of the sources for `count` targets of `nprob` problems from prob0 on:
-// 24 workgroups per compute unit as for the pair sums, at least two chunks each.
+// 24 workgroups per compute unit as for the pair sums, at least two chunks each
+// (single chunks where that leaves compute units idle: 100 directions of 12 bodies
+// of order 128 34.5 us against 30.7).
 int mm_slots(const qax_problem* p, int64_t count, int prob0, int nprob, int cu_count) {
   int64_t cmax = 1;
   for (int pr = prob0; pr < prob0 + nprob; ++pr)
