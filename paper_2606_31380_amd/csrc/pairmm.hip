@@ -127,42 +127,37 @@ __global__ void mm_records_kernel(const BodyDev* __restrict__ bodies, const int3
   ewk[n] = ew32[n] * (float)(1.0 / (k * k)) * S;
 }
 
-__global__ void mm_zero_kernel(uint64_t* __restrict__ p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
-}
-
-// Largest |Re|, |Im| of mu per body and right-hand side, as the bits
-// of a non-negative double (which order like the values; NaN above infinity).
-// Workgroup: 256 consecutive nodes (of any bodies) x 8 right-hand sides; a
-// wavefront whose nodes are of one body meets in one lane per right-hand
-// side (with one maximum per lane, all on the same few addresses, calls at
-// N = 55,296 took 2635 us with 8 right-hand sides and 3836 with 32, now 2517
-// and 3608; N = 5120: 73 and 88, now 67 and 71).
-__global__ __launch_bounds__(256) void mm_colmax_kernel(const double2* __restrict__ mu, int64_t N, int nrhs,
-                                                        const int32_t* __restrict__ node_body,
-                                                        unsigned long long* __restrict__ colmax) {
-  const int r = blockIdx.y * 8 + (threadIdx.x & 7);
-  const int64_t n0 = (int64_t)blockIdx.x * 256 + (threadIdx.x >> 3) * 8;
-  const bool in = r < nrhs && n0 < N;
-  // eight consecutive nodes of one body (node counts are multiples of 32)
-  const int b = node_body[min(n0, N - 1)];
+// Largest |Re|, |Im| of mu per body and right-hand side, as the bits of a
+// non-negative double (which order like the values; NaN above infinity).
+// Workgroup: a body x two right-hand sides, in one launch; maxima met by atomics in
+// cleared memory took two: 12 bodies of order 128, 2 right-hand sides, the whole sum
+// 37.9 -> 34.7 us (the per-target kernel 36.8).  Eight right-hand sides a workgroup
+// leave two bodies of order 8192 too few (33 right-hand sides 379 us against 364).
+constexpr int MM_COLS = 2;
+__global__ __launch_bounds__(1024) void mm_colmax_kernel(const BodyDev* __restrict__ bodies,
+                                                         const double2* __restrict__ mu, int nrhs,
+                                                         unsigned long long* __restrict__ colmax) {
+  constexpr int COLS = MM_COLS, ROWS = 1024 / COLS;
+  const int groups = (nrhs + COLS - 1) / COLS, body = blockIdx.x / groups;
+  const int col = threadIdx.x % COLS, r = (int)(blockIdx.x % groups) * COLS + col;
+  const int64_t off = bodies[body].off;
+  const int n = bodies[body].n;
   unsigned long long m = 0;
-  if (in) {
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const double2 v = mu[(n0 + s) * nrhs + r];
+  if (r < nrhs)
+#pragma unroll 8
+    for (int i = threadIdx.x / COLS; i < n; i += ROWS) {
+      const double2 v = mu[(off + i) * nrhs + r];
       const unsigned long long x = __double_as_longlong(fabs(v.x)), y = __double_as_longlong(fabs(v.y));
       m = max(m, max(x, y));
     }
+  for (int s = COLS; s < 64; s <<= 1) m = max(m, (unsigned long long)__shfl_xor((long long)m, s));
+  __shared__ unsigned long long sm[16][COLS];
+  if ((threadIdx.x & 63) < COLS) sm[threadIdx.x >> 6][col] = m;
+  __syncthreads();
+  if (threadIdx.x < COLS && r < nrhs) {
+    for (int w = 1; w < 16; ++w) m = max(m, sm[w][col]);
+    colmax[(int64_t)body * nrhs + r] = m;
   }
-  bool lead = in;
-  if (__all(b == __builtin_amdgcn_readfirstlane(b))) {
-    for (int off = 8; off < 64; off <<= 1) m = max(m, (unsigned long long)__shfl_xor((long long)m, off));
-    lead = in && (threadIdx.x & 63) < 8;
-  }
-  unsigned long long* dst = colmax + (int64_t)b * nrhs + r;
-  if (lead && m > *(volatile unsigned long long*)dst) atomicMax(dst, m);
 }
 
 // log2 sigma of a body's column from its largest value (0 when that is zero or
@@ -1126,11 +1121,10 @@ hipError_t launch_pair_mmf(qax_problem* p, const double* mu, int nrhs, double* w
   u32x4* pack = (u32x4*)m;
   const int form = p->form();
   const hipStream_t s = p->stream;
-  const int64_t ncol = (int64_t)p->n_bodies * nrhs;
   const int64_t halves = p->N / 16;
-  hipLaunchKernelGGL(mm_zero_kernel, dim3((unsigned)((ncol + 255) / 256)), dim3(256), 0, s, (uint64_t*)colmax, ncol);
-  hipLaunchKernelGGL(mm_colmax_kernel, dim3((unsigned)((p->N + 255) / 256), (unsigned)((nrhs + 7) / 8)), dim3(256), 0,
-                     s, (const double2*)mu, p->N, nrhs, p->d_node_body, colmax);
+  const unsigned groups = (unsigned)((nrhs + MM_COLS - 1) / MM_COLS);
+  hipLaunchKernelGGL(mm_colmax_kernel, dim3((unsigned)p->n_bodies * groups), dim3(1024), 0, s, p->d_bodies,
+                     (const double2*)mu, nrhs, colmax);
   for (int r0 = 0; r0 < nrhs; r0 += 64) {
     const int left = nrhs - r0, wide = left > 16, tiles = left > 32 ? 2 : 1;
     hipLaunchKernelGGL(mm_pack_kernel, dim3((unsigned)((halves * 64 + 255) / 256), (unsigned)tiles), dim3(256), 0, s,
